@@ -49,12 +49,12 @@ struct MegbRec {
   unsigned long long max_trans;  // float64 bit pattern of max ||t* - t_s||^2
   float centre[12];       // R* row-major, t*
   long long n_groups[2];  // diagnostics: chunk groups scanned in shell steps per chain
-  float4 early_c[2];      // centre after the steps taken by the multi-workgroup first phase
-  // global shell of each chain (instances of the first phase): the gs_n
-  // samples at distance >= gs_theta from early_c (gs_theta = -1: every
-  // feasible sample; gs_n = -1: no shell)
-  int32_t gs_n[2];
-  float gs_theta[2];
+  // undominated samples of each chain (instances of the first phase): the
+  // dm_n samples that can be the farthest from some centre within dm_rho of
+  // dm_c (dm_rho = 0: none kept; dm_n beyond the slots: too many)
+  float4 dm_c[2];
+  int32_t dm_n[2];
+  float dm_rho[2];
   // rotation iterates C_0, C_ck, C_2ck, ... left for the backward, valid for
   // the trace whose signature is ck_hash (ck_T = 0: none)
   unsigned long long ck_hash;
@@ -65,19 +65,20 @@ struct MegbRec {
 };
 static_assert(sizeof(MegbRec) == 192, "MegbRec layout");
 
-// Instances of at least kBigInstance samples take the first kEarlySteps
-// descent steps in kEarlyWG workgroups per chain, one launch per step, and
-// then gather their global shell: the farthest samples from the centre the
-// first phase reached, at most one in kShellDiv of the instance's samples,
-// which the chain's rescans stream instead of every sample.
+// Instances of at least kBigInstance samples take their first descent steps
+// in kEarlyWG workgroups per chain, one launch per step.  The first
+// kEarlyFull steps scan every sample; the next one also gathers the
+// undominated samples (at most one in kShellDiv of the instance's, else none
+// are kept), which the later steps and the chain's rescans stream instead of
+// every sample.
 constexpr int64_t kBigInstance = 32768;
-constexpr int kEarlySteps = 32;
+constexpr int kEarlyFull = 16;
 constexpr int kEarlyWG = 64;
 constexpr int kShellBins = 256;
-constexpr int kShellDiv = 16;
+constexpr int kShellDiv = 8;
 
-// Global-shell slots of an instance: [off / kShellDiv, off / kShellDiv +
-// M / kShellDiv) in each chain's array (disjoint between instances, since
+// Slots of an instance's undominated samples: [off / kShellDiv, off / kShellDiv
+// + M / kShellDiv) in each chain's array (disjoint between instances, since
 // floor(a) + floor(b) <= floor(a + b)).
 __host__ __device__ inline int64_t gshell_stride(int64_t total_samples, int64_t max_samples) {
   return max_samples >= kBigInstance ? total_samples / kShellDiv + 1 : 0;
@@ -123,16 +124,11 @@ struct WsLayout {
 };
 
 // First-phase scratch per (instance, chain): the packed (key, ~id) argmax of
-// every workgroup for two consecutive steps, the centre for two consecutive
-// steps, every workgroup's largest distance, the global shell's histogram
-// and its fill count.
+// every workgroup for two consecutive steps and the centre for two consecutive
+// steps.
 struct EarlyScratch {
   unsigned long long part[2][kEarlyWG];
   float4 cbuf[2];
-  float dmax[kEarlyWG];
-  unsigned int hist[kShellBins];
-  int32_t count;
-  int32_t pad[3];
 };
 
 // Tile schedule of the sampler, one per launch group (3D-3D; 2D-3D with the
@@ -177,7 +173,7 @@ inline WsLayout ws_layout(int64_t n_inst, int64_t total_kp, int64_t total_sample
   L.early = o;  // [n_inst][2] first-phase scratch
   o += big ? align_up(sizeof(EarlyScratch) * 2 * (size_t)n_inst) : 0;
   const size_t gs = (size_t)gshell_stride(total_samples, max_samples);
-  L.gid = o;  // [2][stride] sample ids of the global shells
+  L.gid = o;  // [2][stride] ids of the undominated samples
   o += align_up(sizeof(int32_t) * 2 * gs);
   L.gpt = o;  // [2][stride] their points (quaternion or translation)
   o += align_up(16 * 2 * gs);

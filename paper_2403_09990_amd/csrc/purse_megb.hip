@@ -10,10 +10,13 @@
 // outside the shell is at most theta + d(C, C_ref) from the current centre C,
 // so when the shell's best exceeds that bound (with a rounding slack) the
 // shell argmax is the argmax over all samples and the step is exact; when it
-// does not, the chain rescans around the current centre.  Steps on the shell
-// run in one wavefront with shuffles only, or, once the winners keep coming
-// from a few samples, pipelined: one wavefront runs the descent ahead with
-// predicted winners and the others check each step's argmax.
+// does not, the chain rescans around the current centre.  Only undominated
+// samples enter the shell (struct Domination): those that can be the farthest
+// from some centre within a ball that holds the rest of the descent's path, a
+// few per cent of the samples after 16 steps and a few dozen after 256.  Steps
+// on the shell run in one wavefront with shuffles only, or, once the winners
+// keep coming from a few samples, pipelined: one wavefront runs the descent
+// ahead with predicted winners and the others check each step's argmax.
 #include <float.h>
 
 #include <type_traits>
@@ -30,7 +33,7 @@ namespace {
 constexpr int kBlock = 256;
 constexpr int kWaves = kBlock / 64;
 constexpr int kBins = 256;
-constexpr int kGlobalSteps = 64;
+constexpr int kScanSteps = 16;   // steps of a stage of scan steps
 // samples per thread of the per-sample passes (k_megb_prep, k_megb_radii):
 // kPassPer on instances of at least kPassPerMin samples, else one
 constexpr int kPassPer = 4;
@@ -191,8 +194,8 @@ __global__ void k_megb_init(int n_inst, MegbRec *rec) {
   rec[j].n_feasible = 0ull;
   rec[j].max_rot = 0ull;
   rec[j].max_trans = 0ull;
-  rec[j].gs_n[0] = rec[j].gs_n[1] = -1;
-  rec[j].gs_theta[0] = rec[j].gs_theta[1] = -1.f;
+  rec[j].dm_n[0] = rec[j].dm_n[1] = 0;
+  rec[j].dm_rho[0] = rec[j].dm_rho[1] = 0.f;
   rec[j].ck_hash = 0ull;
   rec[j].ck_T = 0;
   rec[j].ck_every = 0;
@@ -209,21 +212,184 @@ __device__ __forceinline__ int bin_of(float d, float lo, float rw) {
   return b < 0 ? 0 : (b >= kBins ? kBins - 1 : b);
 }
 
-static_assert(kShellBins == kBins, "one binning for the global and the chain shells");
+// ---------------------------------------------------------------------------
+// Domination.  In R^4 (unit quaternions a, b, the sign of b such that
+// C_ref . b >= 0) and in R^3 (translations) the difference of two samples'
+// squared distances |C - b|^2 is affine in the centre C, so for a witness w
+//   |C - w|^2 - |C - s|^2 >= |C_ref - w|^2 - |C_ref - s|^2 - 2 rho |s - w|
+// for every C within rho of C_ref.  A sample s for which the right side is
+// positive (by more than the keys' rounding) is nearer than w to each such
+// centre: it is no farthest sample there and can be left out.  The relation
+// is transitive, so a witness may itself be left out.  (A bound by the
+// triangle inequality instead keeps every sample within 2 rho of the radius:
+// 65,536 of 2^20 samples after 32 steps against 6,000-18,000 here, and 7,168
+// against 40-1,600 after 128.)
+//
+// Witnesses are the last distinct winners, at most eight.  C_ref is the mean
+// of the later half of the rotation iterates kept so far (checkpoints; the
+// iterates zigzag about their limit) and the current one, else the current
+// iterate.  rho is a multiple of the next step's length, h / i: the rest of
+// the path from step i on stays within 0.6-1.4 such lengths of that mean, and
+// within 1.0-2.1 of the iterate itself, on the clouds it was measured on; a
+// centre beyond it only ends the stage.
+struct Domination {
+  float4 w[8];   // witnesses, on C_ref's side
+  float xw[8];   // |C_ref - w|^2
+  float4 C;      // C_ref
+  float xmax;    // largest xw
+  float rho, rho_min;  // radius, and the least one worth a pass over the samples
+  int n;         // witnesses (0: nothing is dominated and any centre is allowed)
+};
 
-// The first kEarlySteps steps move the centre across the whole sample cloud,
-// so each needs a scan of every feasible sample.  For instances of at least
-// kBigInstance samples these scans are spread over kEarlyWG workgroups per
-// chain, one launch per step (k_megb_early); smaller instances take them
-// inside their chain's workgroup.  Host and device apply the same rule.
-constexpr int kEarlyBlock = 256;
-
-__host__ __device__ inline bool early_phase_applies(int64_t M, int T, int avg, int no_prune) {
-  return M >= kBigInstance && T > kEarlySteps + avg && !no_prune;
+// The radius with what a pass over the samples and the step's check take
+// from it.  eta covers the rounding of the float32 keys: each is within 8e-7
+// of its value relatively (and unit quaternions are so to 2e-7), and xw, xs
+// within 4e-7, against 1e-5 here.
+struct DomBall {
+  float chk;    // a centre is inside while |C - C_ref|^2 <= chk
+  float four;   // (2 rho)^2
+  float xin;    // samples nearer than this are dominated whatever their direction
+  float eta;
+};
+__device__ __forceinline__ DomBall dom_ball(const Domination &S, float rho) {
+  DomBall b;
+  if (S.n == 0) return DomBall{FLT_MAX, FLT_MAX, -1.f, FLT_MAX};
+  const float rw = __builtin_amdgcn_sqrtf(S.xmax);
+  b.chk = rho * rho * (1.f - 1e-5f);
+  b.four = 4.f * rho * rho * (1.f + 4e-5f);
+  b.eta = 1e-5f * (rw + rho) * (rw + rho);
+  // |s - w| <= |C_ref - s| + |C_ref - w|
+  const float in = rw - 2.0002f * rho - b.eta / fmaxf(rw, 1e-30f);
+  b.xin = in > 0.f ? in * in : -1.f;
+  return b;
 }
 
-// Samples [sb, se) of workgroup b of a chain: kEarlyWG ranges of a multiple
-// of kEarlyBlock samples.
+// |a - b|^2 with the sign of b that makes it smaller (chain 0), which is left in b.
+__device__ __forceinline__ float near_sq(float4 a, float4 &b, int chain) {
+  if (chain == 0) {
+    float x, y;
+    rot_chord_sq(a, b, x, y);
+    const bool flip = x > y;
+    b = flip ? make_float4(-b.x, -b.y, -b.z, -b.w) : b;
+    return flip ? y : x;
+  }
+  return sqdist(a, b, 1);
+}
+
+__device__ __forceinline__ float euclid_sq(float4 a, float4 b, int chain) {
+  const float d0 = a.x - b.x, d1 = a.y - b.y, d2 = a.z - b.z, d3 = chain == 0 ? a.w - b.w : 0.f;
+  return fmaf(d3, d3, fmaf(d2, d2, fmaf(d1, d1, d0 * d0)));
+}
+
+__device__ __forceinline__ bool dominated(const Domination &S, const DomBall &b, float4 s, int chain) {
+  const float xs = near_sq(S.C, s, chain);
+  if (xs < b.xin) return true;
+  bool dom = false;
+  for (int k = 0; k < S.n; ++k) {
+    const float gap = S.xw[k] - xs - b.eta;
+    dom = dom || (gap > 0.f && gap * gap > b.four * euclid_sq(S.w[k], s, chain));
+  }
+  return dom;
+}
+
+// Sum over the wavefront, in every lane (a fixed order).
+__device__ __forceinline__ float wave_sum(float v) {
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
+  return v;
+}
+
+// One wavefront builds S for the steps from i0 on, at the iterate C: winners
+// of the steps before come from the trace tr (the last one given as w_last
+// when the trace does not hold it yet, else -1), rotation iterates from the
+// checkpoints ckq of spacing ck.
+__device__ __forceinline__ void build_domination(Domination &S, float4 C, int i0, int w_last, const int32_t *tr,
+                                                 const float4 *D, int M, const float4 *ckq, int ck, int chain) {
+  const int lane = threadIdx.x & 63;
+  const int taken = i0 - 1;
+  int v = -1;
+  if (lane < taken) v = lane == 0 && w_last >= 0 ? w_last : tr[2 * (taken - 1 - lane)];
+  if (v >= M) v = -1;
+  unsigned long long left = __ballot(v >= 0);
+  int n = 0, id = -1;
+  while (left && n < 8) {
+    const int w = __builtin_amdgcn_readlane(v, (int)__ffsll((long long)left) - 1);
+    if (lane == n) id = w;
+    ++n;
+    left &= ~__ballot(v == w);
+  }
+  const bool mine = lane < n;
+  const float4 pw = D[mine ? id : 0];
+  // reference centre and the radius in steps
+  float4 R = C;
+  float f = 2.1f;
+  if (chain == 0 && taken >= 2) {
+    const int qhi = (taken - 1) / ck, qlo = (taken / 2 + ck - 1) / ck;
+    const int nq = min(64, qhi - qlo + 1);
+    if (nq >= 2) {
+      float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (lane < nq) a = ckq[qhi - lane];
+      a.x = wave_sum(a.x) + C.x;
+      a.y = wave_sum(a.y) + C.y;
+      a.z = wave_sum(a.z) + C.z;
+      a.w = wave_sum(a.w) + C.w;
+      const float nn = __builtin_amdgcn_rsqf(fmaf(a.w, a.w, fmaf(a.z, a.z, fmaf(a.y, a.y, a.x * a.x))));
+      R = make_float4(a.x * nn, a.y * nn, a.z * nn, a.w * nn);
+      f = i0 < 64 ? 1.5f : 1.3f;
+    }
+  }
+  const float inv = 1.f / (float)i0;
+  float4 w = pw;
+  float x = near_sq(R, w, chain);
+  float xmax = wave_max_key(mine ? x : 0.f);
+  float step = __builtin_amdgcn_sqrtf(xmax) * inv;
+  if (f < 2.f && !(euclid_sq(C, R, chain) < 1.21f * step * step)) {  // (a mean far from the iterate)
+    R = C;
+    f = 2.1f;
+    w = pw;
+    x = near_sq(R, w, chain);
+    xmax = wave_max_key(mine ? x : 0.f);
+    step = __builtin_amdgcn_sqrtf(xmax) * inv;
+  }
+  const float rho = f * step;
+  // (rotations: balls of less than about 100 degrees, where the keys order as
+  // the chords do with the margin that eta allows for)
+  const bool ok = n > 0 && rho > 0.f && (chain == 1 || xmax + 2.f * rho < 0.75f);
+  if (mine) {
+    S.w[lane] = w;
+    S.xw[lane] = x;
+  }
+  if (lane == 0) {
+    S.C = R;
+    S.xmax = xmax;
+    S.rho = rho;
+    S.rho_min = 1.2f * step;
+    S.n = ok ? n : 0;
+  }
+}
+
+// The first steps move the centre across the whole sample cloud.  For
+// instances of at least kBigInstance samples they are spread over kEarlyWG
+// workgroups per chain, one launch per step (k_megb_early): kEarlyFull scans of
+// every sample, then steps over the undominated ones until those fit a
+// chain's shell.  Smaller instances take kEarlyFull full scans inside their
+// chain's workgroup.  Host and device apply the same rule.
+constexpr int kEarlyBlock = 256;
+constexpr int kEarlyList = 4096;  // undominated samples of a workgroup held in LDS before they are written
+
+// Steps of the first phase: until the undominated samples (about 6, 1.5, 0.6
+// and 0.3 % of all after 16, 32, 48 and 64 steps) fit the shell of a chain.
+inline int early_steps(int64_t max_samples, bool wide) {
+  const int64_t m = wide ? max_samples : 4 * max_samples;
+  return m <= (1 << 17) ? kEarlyFull + 1 : (m <= (1 << 19) ? 33 : (m <= (1 << 21) ? 49 : 65));
+}
+
+__host__ __device__ inline bool early_phase_applies(int64_t M, int T, int avg, int no_prune, int n_early) {
+  return M >= kBigInstance && T > n_early + avg && !no_prune;
+}
+
+// Elements [sb, se) of workgroup b of a chain: kEarlyWG ranges of a multiple
+// of kEarlyBlock elements.
 __device__ __forceinline__ void early_range(int M, int b, int &sb, int &se) {
   const int span = ((M + kEarlyWG - 1) / kEarlyWG + kEarlyBlock - 1) / kEarlyBlock * kEarlyBlock;
   sb = min(M, b * span);
@@ -249,248 +415,156 @@ __device__ __forceinline__ unsigned long long pack_best(float k, int id) {
                                (unsigned long long)(~(unsigned)id);
 }
 
+// Completes step i of a chain's first phase from the kEarlyWG packed argmaxes
+// its launch left and the centre it started from (whole wavefront, every lane
+// gets the new centre); the winner's id in bi.
+__device__ __forceinline__ float4 early_complete(const EarlyScratch &e, int i, const float4 *D, int M, int chain,
+                                                 int &bi) {
+  static_assert(kEarlyWG == 64, "one partial per lane");
+  const unsigned long long best = wave_max_u64(e.part[i & 1][threadIdx.x & 63]);
+  bi = best ? (int)~(unsigned)(best & 0xffffffffull) : INT32_MAX;
+  const float4 Cp = e.cbuf[(i + 1) & 1];
+  return bi < M ? geodesic_step(Cp, D[bi], i, chain) : Cp;
+}
+
 // Step i of the first phase for every (instance, chain) the rule selects,
 // whose feasible samples outnumber the shell capacity (else the shell holds
-// them all and the chain's workgroup needs no full scans).  Every workgroup
-// first completes step i - 1 itself: it reduces the kEarlyWG packed argmaxes
-// the previous launch left and takes the geodesic step from the centre that
-// launch started from, so all workgroups hold the same centre with no atomic
-// or fence (kernel boundaries order the launches); workgroup 0 records the
-// trace, the checkpoint and the centre for the next launch.  Then each
+// them all and the chain's workgroup needs no scans).  Every workgroup first
+// completes step i - 1 itself, so all workgroups hold the same centre with no
+// atomic or fence (kernel boundaries order the launches); workgroup 0 records
+// the trace, the checkpoint and the centre for the next launch.  Then each
 // workgroup finds the farthest of its samples and leaves its packed argmax.
-// Launch kEarlySteps + 1 only completes the last step and, as the first pass
-// of the global shell, writes every sample's distance from that centre to
-// dref and each workgroup's largest distance.  Buffers alternate between
-// consecutive launches, so a launch never writes what it reads.
+// The chain's workgroup completes the last step.  Buffers alternate between
+// consecutive launches, so a launch never writes what it reads.  Launch
+// kEarlyFull + 1 also gathers the undominated samples about its centre (in
+// LDS, written with one atomic reservation per few thousand), and the later
+// ones scan those while the centre is in their ball.  (2^20 samples: a full
+// scan is bound by HBM, 0.36 ms for 64 instances; 64 instances of 2^20 took
+// 32 of them and three passes for a shell by distance, 12.6 ms, and take 17
+// and 32 over the undominated samples.)
 __global__ void __launch_bounds__(kEarlyBlock) k_megb_early(const int64_t *__restrict__ sample_off, int64_t total,
                                                             int64_t max_m, const float4 *__restrict__ quat,
                                                             const float4 *__restrict__ trans, MegbRec *rec,
-                                                            EarlyScratch *es, float *dref_all, int32_t *trace,
-                                                            float4 *ckpt, int ck, int T, int avg, int cap,
-                                                            int no_prune, int i) {
+                                                            EarlyScratch *es, int32_t *trace, float4 *ckpt, int ck,
+                                                            int T, int avg, int cap, int no_prune, int n_early,
+                                                            int32_t *gid_all, float4 *gpt_all, int64_t gstride,
+                                                            int i) {
   const int j = blockIdx.z, chain = blockIdx.y, b = blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int64_t off, M64;
   sample_range(sample_off, j, total, max_m, off, M64);
-  if (!early_phase_applies(M64, T, avg, no_prune)) return;
+  if (!early_phase_applies(M64, T, avg, no_prune, n_early)) return;
   const int M = (int)M64;  // >= kBigInstance here
   const int first = rec[j].first;
   if (first == INT32_MAX || (int64_t)rec[j].n_feasible <= cap) return;
   const float4 *D = (chain ? trans : quat) + off;
   EarlyScratch &e = es[2 * j + chain];
-  int sb, se;
-  early_range(M, b, sb, se);
+  int32_t *tr = trace + (int64_t)j * T * 2 + chain;
+  float4 *ckq = ckpt + (int64_t)j * ckpt_count(T, ck);
   // ---- the centre before step i (every wave reduces the partials itself)
   float4 C;
+  int w_last = -1;
   if (i == 1) {
     C = D[first];
   } else {
-    static_assert(kEarlyWG == 64, "one partial per lane");
-    const unsigned long long best = wave_max_u64(e.part[(i - 1) & 1][lane]);
-    const int bi = best ? (int)~(unsigned)(best & 0xffffffffull) : INT32_MAX;
-    const float4 Cp = e.cbuf[i & 1];
-    C = bi < M ? geodesic_step(Cp, D[bi], i - 1, chain) : Cp;
-    if (b == 0 && tid == 0) trace[((int64_t)j * T + i - 2) * 2 + chain] = bi;
+    C = early_complete(e, i - 1, D, M, chain, w_last);
+    if (b == 0 && tid == 0) tr[2 * (i - 2)] = w_last;
   }
   if (b == 0 && tid == 0) {
     e.cbuf[(i + 1) & 1] = C;
-    if (i <= kEarlySteps && chain == 0 && (i - 1) % ck == 0) ckpt[(int64_t)j * ckpt_count(T, ck) + (i - 1) / ck] = C;
-    if (i > kEarlySteps) rec[j].early_c[chain] = C;
+    if (chain == 0 && (i - 1) % ck == 0) ckq[(i - 1) / ck] = C;
   }
-  __shared__ float red_k[kEarlyBlock / 64];
-  __shared__ int red_i[kEarlyBlock / 64];
-  if (i <= kEarlySteps) {
-    // ---- step i over this workgroup's samples
-    float bk = -1.f;
-    int bi = INT32_MAX;
-    stream_rounds<kEarlyBlock>(D + sb, se - sb, make_float4(-2.f, 0.f, 0.f, 0.f), [&](const float4 *a, int s0) {
-#pragma unroll
-      for (int u = 0; u < kUnroll; ++u) {
-        const int s = sb + s0 + u * kEarlyBlock + tid;
-        if (s < se && feasible_pt(a[u], chain)) {
-          const float k = sqdist(C, a[u], chain);
-          if (better(k, s, bk, bi)) {
-            bk = k;
-            bi = s;
-          }
-        }
-      }
-    });
-    float wk;
-    int wi;
-    wave_argmax(bk, bi, wk, wi);
-    if (lane == 0) {
-      red_k[wave] = wk;
-      red_i[wave] = wi;
-    }
-    __syncthreads();
-    if (tid == 0) {
-      bk = red_k[0];
-      bi = red_i[0];
-#pragma unroll
-      for (int w = 1; w < kEarlyBlock / 64; ++w)
-        if (better(red_k[w], red_i[w], bk, bi)) {
-          bk = red_k[w];
-          bi = red_i[w];
-        }
-      e.part[i & 1][b] = pack_best(bk, bi);
-    }
-    return;
-  }
-  // ---- global shell, first pass: distances from the centre
-  float *dref = dref_all + chain * total + off;
-  float mx = 0.f;
-  stream_rounds<kEarlyBlock>(D + sb, se - sb, make_float4(-2.f, 0.f, 0.f, 0.f), [&](const float4 *a, int s0) {
-#pragma unroll
-    for (int u = 0; u < kUnroll; ++u) {
-      const int s = sb + s0 + u * kEarlyBlock + tid;
-      if (s < se) {
-        float d = -1.f;
-        if (feasible_pt(a[u], chain)) {
-          d = __builtin_amdgcn_sqrtf(sqdist(C, a[u], chain));
-          mx = fmaxf(mx, d);
-        }
-        dref[s] = d;
-      }
-    }
-  });
-  mx = wave_max(mx);
-  if (lane == 0) red_k[wave] = mx;
-  if (b == 0) {
-    for (int k = tid; k < kShellBins; k += kEarlyBlock) e.hist[k] = 0u;
-    if (tid == 0) e.count = 0;
-  }
-  __syncthreads();
-  if (tid == 0) {
-#pragma unroll
-    for (int w = 1; w < kEarlyBlock / 64; ++w) mx = fmaxf(mx, red_k[w]);
-    e.dmax[b] = fmaxf(mx, red_k[0]);
-  }
-}
-
-// Histogram bin width of a chain's global shell: the largest distance over
-// kShellBins (every workgroup computes it the same way); 0 when every
-// feasible sample sits at the centre.
-__device__ __forceinline__ float gshell_width(const EarlyScratch &e) {
-  static_assert(kEarlyWG == 64, "one entry per lane");
-  return wave_max(e.dmax[threadIdx.x & 63]) / (float)kShellBins;
-}
-
-// Global shell, second pass: histogram of the distances over [0, max].
-__global__ void __launch_bounds__(kEarlyBlock) k_megb_gshell_hist(const int64_t *__restrict__ sample_off,
-                                                                  int64_t total, int64_t max_m, MegbRec *rec,
-                                                                  EarlyScratch *es, const float *dref_all, int T,
-                                                                  int avg, int cap, int no_prune) {
-  const int j = blockIdx.z, chain = blockIdx.y, b = blockIdx.x;
-  const int tid = threadIdx.x;
-  int64_t off, M64;
-  sample_range(sample_off, j, total, max_m, off, M64);
-  if (!early_phase_applies(M64, T, avg, no_prune)) return;
-  if (rec[j].first == INT32_MAX || (int64_t)rec[j].n_feasible <= cap) return;
-  EarlyScratch &e = es[2 * j + chain];
-  const float w = gshell_width(e);
-  if (!(w > 0.f)) return;
-  const float rw = 1.f / w;
-  __shared__ unsigned int h[kShellBins];
-  for (int k = tid; k < kShellBins; k += kEarlyBlock) h[k] = 0u;
-  __syncthreads();
-  int sb, se;
-  early_range((int)M64, b, sb, se);
-  const float *dref = dref_all + chain * total + off;
-  stream_rounds<kEarlyBlock, 16>(dref + sb, se - sb, -1.f, [&](const float *dd, int) {
-#pragma unroll
-    for (int u = 0; u < 16; ++u)
-      if (dd[u] >= 0.f) atomicAdd(&h[bin_of(dd[u], 0.f, rw)], 1u);
-  });
-  __syncthreads();
-  for (int k = tid; k < kShellBins; k += kEarlyBlock)
-    if (h[k]) atomicAdd(&e.hist[k], h[k]);
-}
-
-// Global shell, third pass: the threshold (the lowest bin edge above which at
-// most M / kShellDiv samples lie) and the members, compacted into the
-// chain's slots: each workgroup counts its members per wave, reserves its
-// range with one atomic, and writes them wave by wave in sample order.  The
-// order of the workgroups' ranges varies from run to run; every use of the
-// shell is order-independent (argmax ties go to the lowest sample id).
-__global__ void __launch_bounds__(kEarlyBlock) k_megb_gshell_collect(const int64_t *__restrict__ sample_off,
-                                                                     int64_t total, int64_t max_m,
-                                                                     const float4 *__restrict__ quat,
-                                                                     const float4 *__restrict__ trans,
-                                                                     MegbRec *rec, EarlyScratch *es,
-                                                                     const float *dref_all, int32_t *gid_all,
-                                                                     float4 *gpt_all, int64_t gstride, int T,
-                                                                     int avg, int cap, int no_prune) {
-  const int j = blockIdx.z, chain = blockIdx.y, b = blockIdx.x;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  int64_t off, M64;
-  sample_range(sample_off, j, total, max_m, off, M64);
-  if (!early_phase_applies(M64, T, avg, no_prune)) return;
-  if (rec[j].first == INT32_MAX || (int64_t)rec[j].n_feasible <= cap) return;
-  EarlyScratch &e = es[2 * j + chain];
-  const float w = gshell_width(e);
-  if (!(w > 0.f)) return;  // no shell (gs_n stays -1)
-  const float rw = 1.f / w;
-  const int M = (int)M64;
-  const int G = M / kShellDiv;
-  __shared__ int sh_bstar, sh_n;
-  __shared__ int wcount[kEarlyBlock / 64], wbase[kEarlyBlock / 64];
-  if (tid == 0) {
-    int cum = 0, bb = kShellBins - 1;
-    for (; bb >= 0; --bb) {
-      if (cum + (int)e.hist[bb] > G) break;
-      cum += (int)e.hist[bb];
-    }
-    // bb < 0: every feasible sample fits; bb = kShellBins - 1: the top bin
-    // alone is too large (no shell)
-    sh_bstar = bb + 1;
-    sh_n = cum;
-    if (b == 0) {
-      rec[j].gs_n[chain] = bb == kShellBins - 1 ? -1 : cum;
-      rec[j].gs_theta[chain] = bb < 0 ? -1.f : (float)(bb + 1) * w;
-    }
-  }
-  __syncthreads();
-  const int bstar = sh_bstar;
-  if (bstar >= kShellBins) return;
-  int sb, se;
-  early_range(M, b, sb, se);
-  // each wave takes a contiguous quarter of the range
-  const int q = ((se - sb + kEarlyBlock / 64 - 1) / (kEarlyBlock / 64) + 63) / 64 * 64;
-  const int wb = min(se, sb + wave * q), we = min(se, wb + q);
-  const float *dref = dref_all + chain * total + off;
-  auto member = [&](float d) { return d >= 0.f && bin_of(d, 0.f, rw) >= bstar; };
-  int cnt = 0;
-  for (int s = wb + lane; s < we; s += 64) cnt += member(dref[s]) ? 1 : 0;
-  for (int o = 32; o >= 1; o >>= 1) cnt += __shfl_xor(cnt, o, 64);
-  if (lane == 0) wcount[wave] = cnt;
-  __syncthreads();
-  if (tid == 0) {
-    int t = 0;
-    for (int k = 0; k < kEarlyBlock / 64; ++k) {
-      wbase[k] = t;
-      t += wcount[k];
-    }
-    const int base = t ? atomicAdd(&e.count, t) : 0;
-    for (int k = 0; k < kEarlyBlock / 64; ++k) wbase[k] += base;
-  }
-  __syncthreads();
-  const float4 *D = (chain ? trans : quat) + off;
+  const bool gather = i == kEarlyFull + 1;
+  const int slots = M / kShellDiv;
   int32_t *gid = gid_all + chain * gstride + off / kShellDiv;
   float4 *gpt = gpt_all + chain * gstride + off / kShellDiv;
-  int pos = wbase[wave];
-  for (int s0 = wb; s0 < we; s0 += 64) {
-    const int s = s0 + lane;
-    const bool m = s < we && member(dref[s]);
-    const unsigned long long mk = __ballot(m);
-    const int p = pos + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(mk >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mk, 0u));
-    if (m && p < G) {
-      gid[p] = s;
-      gpt[p] = D[s];
-    }
-    pos += __popcll(mk);
+  const float rho = rec[j].dm_rho[chain];
+  const int n_dm = rec[j].dm_n[chain];
+  const bool pruned = !gather && i > kEarlyFull && rho > 0.f && n_dm <= slots &&
+                      euclid_sq(C, rec[j].dm_c[chain], chain) <= rho * rho * (1.f - 1e-5f);
+  const float4 *src = pruned ? gpt : D;
+  const int n_src = pruned ? n_dm : M;
+  int sb, se;
+  early_range(n_src, b, sb, se);
+  __shared__ float red_k[kEarlyBlock / 64];
+  __shared__ int red_i[kEarlyBlock / 64];
+  __shared__ Domination dom;
+  __shared__ int list[kEarlyList];
+  __shared__ int n_list, base_s;
+  if (gather) {
+    if (wave == 0) build_domination(dom, C, i, w_last, tr, D, M, ckq, ck, chain);
+    if (tid == 0) n_list = 0;
+    __syncthreads();
   }
-  (void)sh_n;
+  const bool keep = gather && dom.n > 0;
+  DomBall ball = DomBall{0.f, 0.f, 0.f, 0.f};
+  if (keep) ball = dom_ball(dom, dom.rho);
+  auto flush = [&]() {  // (whole workgroup)
+    const int n = n_list;
+    if (tid == 0) base_s = n ? atomicAdd(&rec[j].dm_n[chain], n) : 0;
+    __syncthreads();
+    const int base = base_s;
+    for (int p = tid; p < n; p += kEarlyBlock)
+      if (base + p < slots) {
+        const int s = list[p];
+        gid[base + p] = s;
+        gpt[base + p] = D[s];
+      }
+    __syncthreads();
+    if (tid == 0) n_list = 0;
+    __syncthreads();
+  };
+  float bk = -1.f;
+  int bi = INT32_MAX;
+  stream_rounds<kEarlyBlock>(src + sb, se - sb, make_float4(-2.f, 0.f, 0.f, 0.f), [&](const float4 *a, int s0) {
+#pragma unroll
+    for (int u = 0; u < kUnroll; ++u) {
+      const int q = sb + s0 + u * kEarlyBlock + tid;
+      if (q < se && feasible_pt(a[u], chain)) {
+        const float k = sqdist(C, a[u], chain);
+        const int s = pruned ? gid[q] : q;
+        if (better(k, s, bk, bi)) {
+          bk = k;
+          bi = s;
+        }
+        if (keep && !dominated(dom, ball, a[u], chain)) list[atomicAdd(&n_list, 1)] = q;
+      }
+    }
+    if (keep) {
+      static_assert(kEarlyList >= 2 * kEarlyBlock * kUnroll, "a round fits a list at most half full");
+      __syncthreads();
+      const bool full = n_list > kEarlyList - kEarlyBlock * kUnroll;
+      __syncthreads();  // (every thread has read n_list before the next round adds to it)
+      if (full) flush();
+    }
+  });
+  if (keep) {
+    __syncthreads();
+    flush();
+    if (b == 0 && tid == 0) {
+      rec[j].dm_c[chain] = dom.C;
+      rec[j].dm_rho[chain] = dom.rho;
+    }
+  }
+  float wk;
+  int wi;
+  wave_argmax(bk, bi, wk, wi);
+  if (lane == 0) {
+    red_k[wave] = wk;
+    red_i[wave] = wi;
+  }
+  __syncthreads();
+  if (tid == 0) {
+    bk = red_k[0];
+    bi = red_i[0];
+#pragma unroll
+    for (int w = 1; w < kEarlyBlock / 64; ++w)
+      if (better(red_k[w], red_i[w], bk, bi)) {
+        bk = red_k[w];
+        bi = red_i[w];
+      }
+    e.part[i & 1][b] = pack_best(bk, bi);
+  }
 }
 
 // Per sample: quaternion (w >= 0; w = -2 marks an infeasible sample) and
@@ -567,10 +641,11 @@ __global__ void __launch_bounds__(kBlock) k_megb_prep(const int64_t *__restrict_
   }
 }
 
-// A chain's global shell (the state only rescans read) and its diagnostics.
-struct ChainGs {
-  int n, built_at, n_built;
-  float theta;
+// A chain's undominated samples in global memory (the state only rescans and
+// scan steps read) and its diagnostics.
+struct ChainDm {
+  int n, n_built;
+  float rho;
   float4 C;
 };
 struct ChainDiag {
@@ -578,6 +653,38 @@ struct ChainDiag {
   long long n_groups;
   uint64_t t_start;
 };
+
+// One wavefront: entries of the histogram h summed from the top bin down, each
+// lane holding four bins (bin kBins - 1 - 4 lane first); returns the sum over
+// the bins above the lane's.
+__device__ __forceinline__ unsigned int bins_above(const unsigned int *h, unsigned int c[4]) {
+  static_assert(kBins == 256, "four bins per lane");
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) c[k] = h[kBins - 1 - 4 * lane - k];
+  const unsigned int own = c[0] + c[1] + c[2] + c[3];
+  unsigned int inc = own;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const unsigned int up = __shfl_up(inc, o, 64);
+    if (lane >= o) inc += up;
+  }
+  return inc - own;
+}
+
+// One wavefront: the highest bin whose entries no longer fit cap together
+// with those of the bins above it (-1: all of them fit).
+__device__ __forceinline__ int first_bin_over(const unsigned int *h, unsigned int cap) {
+  unsigned int c[4];
+  unsigned int cum = bins_above(h, c);
+  int over = -1;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    cum += c[k];
+    if (over < 0 && cum > cap) over = kBins - 1 - 4 * (int)(threadIdx.x & 63) - k;
+  }
+  return wave_max_i32(over);
+}
 
 // Shared state of one chain's workgroup.
 struct ChainShared {
@@ -595,12 +702,13 @@ __device__ __forceinline__ void chain_run(const ChainShared &S, const int64_t *_
                                           int64_t max_m, const float4 *__restrict__ pts, MegbRec *rec,
                                           float *dref_all, int64_t total_samples, int32_t *trace,
                                           float4 *ckpt_all, int ck, int T, int avg, int cap, int no_prune,
-                                          int32_t *__restrict__ gid_all, float4 *__restrict__ gpt_all,
-                                          int64_t gstride) {
+                                          int n_early, const EarlyScratch *es, int32_t *__restrict__ gid_all,
+                                          float4 *__restrict__ gpt_all, int64_t gstride) {
   __shared__ float4 st_C;
   __shared__ int st_i;
-  __shared__ float st_theta, st_lo, st_w, st_rref;
-  __shared__ int st_bstar;
+  __shared__ float st_theta, st_lo, st_w;
+  __shared__ int st_bstar, st_kept;
+  __shared__ Domination dom;
   __shared__ int st_mode;  // 0 shell in LDS, 1 scan of every sample
   __shared__ unsigned int sh_n;
   // pipelined shell steps
@@ -638,35 +746,38 @@ __device__ __forceinline__ void chain_run(const ChainShared &S, const int64_t *_
     return;
   }
   const int n_feas = (int)rec[j].n_feasible;
-  // the first steps were taken by k_megb_early when the rule selects it,
-  // which also gathered the global shell: the gs_n samples at distance
-  // >= gs_theta from C_g (gs_theta = -1: every feasible sample).  Samples
-  // outside it lie within gs_theta + d(C, C_g) of any centre C, so rescans
-  // stream the shell alone while that bound stays below the farthest member.
-  const bool ep = early_phase_applies(M64, T, avg, no_prune) && n_feas > cap;
+  // the first steps were taken by k_megb_early when the rule selects it, which
+  // also gathered the undominated samples
+  const bool ep = early_phase_applies(M64, T, avg, no_prune, n_early) && n_feas > cap;
   int32_t *gid = gid_all + chain * gstride + off / kShellDiv;
   float4 *gpt = gpt_all + chain * gstride + off / kShellDiv;
-  // A global shell that no longer certifies any step (the centre has moved
-  // too far from C_g) is rebuilt around the centre of the next full rescan,
-  // from the distances that rescan computes, at most once per kMinShellSteps
-  // steps.  Its state, which only rescans read, and the diagnostics live in
-  // LDS (thread 0 writes them between barriers), so that the stepping loops
-  // keep their registers.
-  const int gs_cap = M / kShellDiv;
-  __shared__ ChainGs sg;
+  // Undominated samples whose ball the centre has left are gathered again by
+  // the next pass over every sample.  Their state, which only rescans and scan
+  // steps read, and the diagnostics live in LDS (thread 0 writes them between
+  // barriers), so that the stepping loops keep their registers.
+  const int slots = ep ? M / kShellDiv : 0;
+  __shared__ ChainDm sg;
   __shared__ ChainDiag sdg;
-  if (tid == 0) {
-    st_C = ep ? rec[j].early_c[chain] : D[first];
-    st_i = ep ? kEarlySteps + 1 : 1;
-    sg.n = ep ? rec[j].gs_n[chain] : -1;
-    sg.theta = ep ? rec[j].gs_theta[chain] : -1.f;
-    sg.C = rec[j].early_c[chain];
-    sg.built_at = ep ? -kMinShellSteps : INT32_MAX;
-    sg.n_built = 0;
-    sdg = ChainDiag{0, 0, 0, 0, 0, 0ll, __builtin_amdgcn_s_memrealtime()};
+  if (wave == 0) {
+    float4 C1 = D[first];
+    if (ep) {
+      int bi;
+      C1 = early_complete(es[2 * j + chain], n_early, D, M, chain, bi);
+      if (lane == 0) tr[2 * (n_early - 1)] = bi;
+    }
+    if (lane == 0) {
+      st_C = C1;
+      st_i = ep ? n_early + 1 : 1;
+      sg.n = ep && rec[j].dm_n[chain] <= slots ? rec[j].dm_n[chain] : 0;
+      sg.rho = ep ? rec[j].dm_rho[chain] : 0.f;
+      sg.C = rec[j].dm_c[chain];
+      sg.n_built = 0;
+      sdg = ChainDiag{0, 0, 0, 0, 0, 0ll, __builtin_amdgcn_s_memrealtime()};
+    }
   }
   __syncthreads();
-  bool use_gs = sg.n > 0;
+  bool use_dm = sg.rho > 0.f && sg.n > 0;
+  auto in_dm = [&](float4 c) { return euclid_sq(c, sg.C, chain) <= sg.rho * sg.rho * (1.f - 1e-5f); };
   float acc[9];
 #pragma unroll
   for (int k = 0; k < 9; ++k) acc[k] = 0.f;
@@ -675,126 +786,117 @@ __device__ __forceinline__ void chain_run(const ChainShared &S, const int64_t *_
   int stage_groups = 0;
 
   while (true) {
-    const float4 Cref = st_C;
+    const float4 C0 = st_C;  // the centre; distances and bounds are about Cref, near it
     const int i0 = st_i;
     if (i0 > T) break;
-    const bool early = i0 <= kEarlySteps;
+    const bool early = i0 <= kEarlyFull;
     const bool global = (no_prune || stalled || early) && n_feas > cap;
+    if (use_dm && !in_dm(C0)) use_dm = false;
+    float4 Cref = C0;
+    DomBall ball = DomBall{FLT_MAX, FLT_MAX, -1.f, FLT_MAX};
+    float rref = 0.f;
     if (!global) {
       // -------------------------------------------------------------- rescan
-      if (tid == 0) ++sdg.n_rescan;
-      // entries: the global shell's or every sample
-      const bool from_gs = use_gs;  // (a rebuild below does not change this rescan's source)
-      const float4 *src = from_gs ? gpt : D;
-      const int n_src = from_gs ? sg.n : M;
-      const int n_src_feas = from_gs ? sg.n : n_feas;
+      if (wave == 0) build_domination(dom, C0, i0, -1, tr, D, M, ckq, ck, chain);
+      if (tid == 0) {
+        ++sdg.n_rescan;
+        st_kept = 0;
+      }
+      __syncthreads();
+      // entries: the undominated samples (the ball of this rescan then lies
+      // within theirs) or every sample
+      float rho = dom.rho;
+      if (use_dm) {
+        const float room = sg.rho - 1.00002f * __builtin_amdgcn_sqrtf(euclid_sq(dom.C, sg.C, chain));
+        if (dom.n > 0 && room >= dom.rho_min)
+          rho = fminf(rho, room);
+        else
+          use_dm = false;
+      }
+      const bool from_dm = use_dm;  // (gathering anew below does not change this rescan's source)
+      if (dom.n > 0) {
+        ball = dom_ball(dom, rho);
+        Cref = dom.C;
+      }
+      const float4 *src = from_dm ? gpt : D;
+      const int n_src = from_dm ? sg.n : M;
       recentre = recentre_chunks(n_src);
-      float mx = 0.f;
+      float mx = 0.f, mn = FLT_MAX;
+      int kept = 0;
+      const bool any_dom = dom.n > 0;
       stream_rounds<BLK>(src, n_src, make_float4(-2.f, 0.f, 0.f, 0.f), [&](const float4 *a, int s0) {
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) {
           int s = s0 + u * BLK + tid;
           if (s < n_src) {
             float d = -1.f;
-            if (feasible_pt(a[u], chain)) {
+            if (feasible_pt(a[u], chain) && !(any_dom && dominated(dom, ball, a[u], chain))) {
               d = __builtin_amdgcn_sqrtf(sqdist(Cref, a[u], chain));  // within the slack
               mx = fmaxf(mx, d);
+              mn = fminf(mn, d);
+              ++kept;
             }
             dref[s] = d;
           }
         }
       });
       mx = wave_max(mx);
-      if (lane == 0) S.red_k[0][wave] = mx;
+      mn = __int_as_float(wave_min_i32(__float_as_int(mn)));
+#pragma unroll
+      for (int o = 32; o >= 1; o >>= 1) kept += __shfl_xor(kept, o, 64);
+      if (lane == 0) {
+        S.red_k[0][wave] = mx;
+        S.red_k[1][wave] = mn;
+        atomicAdd(&st_kept, kept);
+      }
       __syncthreads();
-      float rref = 0.f;
 #pragma unroll
-      for (int k = 0; k < NW; ++k) rref = fmaxf(rref, S.red_k[0][k]);
-      // (the narrow variant, which runs batches of more chains than compute
-      // units, keeps its registers for four chains per compute unit and
-      // leaves a stale global shell to full rescans)
-      if (V == kChainWide && ep && !use_gs && i0 - sg.built_at >= kMinShellSteps) {
-        // ---------------------------------- rebuild the global shell at C_ref
-        const float gw = rref / (float)kShellBins;
-        if (gw > 0.f) {
-          const float grw = 1.f / gw;
-          for (int k = tid; k < kBins; k += BLK) S.hist[k] = 0u;
-          __syncthreads();
-          // (a short unroll: the rebuild is rare, and its registers would
-          // otherwise be taken from the stepping loops)
-          stream_rounds<BLK, kUnroll>(dref, M, -1.f, [&](const float *dd, int) {
-#pragma unroll
-            for (int u = 0; u < kUnroll; ++u)
-              if (dd[u] >= 0.f) atomicAdd(&S.hist[bin_of(dd[u], 0.f, grw)], 1u);
-          });
-          __syncthreads();
-          if (tid == 0) {
-            int cum = 0, bb = kShellBins - 1;
-            for (; bb >= 0; --bb) {
-              if (cum + (int)S.hist[bb] > gs_cap) break;
-              cum += (int)S.hist[bb];
-            }
-            st_bstar = bb == kShellBins - 1 ? -1 : bb + 1;  // -1: the top bin alone is too large
-            sh_n = 0u;
-            if (st_bstar < 0) sg.n = -1;
-          }
-          __syncthreads();
-          const int gb = st_bstar;
-          if (gb >= 0) {
-            stream_rounds<BLK, kUnroll>(dref, M, -1.f, [&](const float *dd, int s0) {
-#pragma unroll
-              for (int u = 0; u < kUnroll; ++u) {
-                const int s = s0 + u * BLK + tid;
-                if (dd[u] >= 0.f && bin_of(dd[u], 0.f, grw) >= gb) {
-                  const unsigned int pos = atomicAdd(&sh_n, 1u);
-                  if (pos < (unsigned)gs_cap) {
-                    gid[pos] = s;
-                    gpt[pos] = D[s];
-                  }
-                }
-              }
-            });
-            __syncthreads();
-            if (tid == 0) {
-              sg.n = min((int)sh_n, gs_cap);
-              sg.theta = gb == 0 ? -1.f : (float)gb * gw;
-              sg.C = Cref;
-              ++sg.n_built;
-            }
-          }
-        }
-        if (tid == 0) sg.built_at = i0;
+      for (int k = 0; k < NW; ++k) {
+        rref = fmaxf(rref, S.red_k[0][k]);
+        mn = fminf(mn, S.red_k[1][k]);
+      }
+      const int n_kept = st_kept;
+      if (ep && !from_dm && any_dom && n_kept <= slots) {
+        // ------------------------------ gather the undominated samples anew
+        if (tid == 0) sh_n = 0u;
         __syncthreads();
-        use_gs = sg.n > 0;
-      }
-      // bound of every sample outside the global shell
-      float theta_out = -1.f;
-      if (from_gs && sg.theta >= 0.f) {
-        theta_out = sg.theta + __builtin_amdgcn_sqrtf(sqdist(Cref, sg.C, chain));
-        if (!(theta_out < rref)) {
-          // the shell can no longer certify a step: rescan every sample
-          use_gs = false;
-          __syncthreads();  // (S.red_k is read above and written by the next rescan)
-          continue;
+        // (a short unroll: this is rare, and its registers would otherwise be
+        // taken from the stepping loops)
+        stream_rounds<BLK, kUnroll>(dref, M, -1.f, [&](const float *dd, int s0) {
+#pragma unroll
+          for (int u = 0; u < kUnroll; ++u) {
+            const int s = s0 + u * BLK + tid;
+            if (dd[u] >= 0.f) {
+              const unsigned int pos = atomicAdd(&sh_n, 1u);
+              if (pos < (unsigned)slots) {
+                gid[pos] = s;
+                gpt[pos] = D[s];
+              }
+            }
+          }
+        });
+        __syncthreads();
+        if (tid == 0) {
+          sg.n = min((int)sh_n, slots);
+          sg.rho = rho;
+          sg.C = Cref;
+          ++sg.n_built;
         }
+        __syncthreads();
+        use_dm = sg.n > 0;
       }
-      // Shell membership: d >= theta and (coarse) bin >= bstar of the
-      // histogram (lo, w); theta = -1 when every feasible sample fits.  The
-      // global shell's entries lie at least gs_theta - d(C_ref, C_g) from
-      // C_ref, so its histogram starts there (spread over all the bins, not
-      // piled into the top few); an entry rounded below lo is within
-      // theta_out, which the stage's bound includes.
+      // Shell membership: undominated, and when those do not all fit, d >=
+      // theta and (coarse) bin >= bstar of the histogram (lo, w); theta = -1
+      // when they fit.
       if (tid == 0) {
-        const float lo0 = from_gs && theta_out >= 0.f ? fmaxf(0.f, 2.f * sg.theta - theta_out - 1e-5f * rref) : 0.f;
         st_mode = 0;
         st_theta = -1.f;
-        st_lo = lo0;
-        st_w = (rref - lo0) / (float)kBins;
+        st_lo = mn;
+        st_w = (rref - mn) / (float)kBins;
         st_bstar = 0;
-        st_rref = rref;
       }
       __syncthreads();
-      if (n_src_feas > cap) {
+      if (n_kept > cap) {
         for (int level = 0; level < 2; ++level) {
           const float lo = st_lo, wdt = st_w;
           if (!(wdt > 0.f)) {
@@ -811,38 +913,35 @@ __device__ __forceinline__ void chain_run(const ChainShared &S, const int64_t *_
               if (dd[u] >= lo && dd[u] >= 0.f) atomicAdd(&S.hist[bin_of(dd[u], lo, rw)], 1u);
           });
           __syncthreads();
-          if (tid == 0) {
-            int cum = 0, bb = kBins - 1;
-            for (; bb >= 0; --bb) {
-              if (cum + (int)S.hist[bb] > cap) break;
-              cum += (int)S.hist[bb];
-            }
-            if (bb < 0) {  // everything at or above lo fits
-              st_bstar = 0;
-              st_theta = level == 0 ? -1.f : lo;
-            } else if (bb < kBins - 1) {
-              st_bstar = bb + 1;
-              st_theta = lo + (float)(bb + 1) * wdt;
-            } else if (level == 0) {  // the top bin alone overflows: refine inside it
-              st_lo = lo + (float)(kBins - 1) * wdt;
-              st_w = wdt / (float)kBins;
-              st_theta = -2.f;
-            } else {
-              st_mode = 1;
+          if (wave == 0) {
+            const int bb = first_bin_over(S.hist, (unsigned)cap);
+            if (lane == 0) {
+              st_theta = -1.f;
+              if (bb < 0) {  // everything at or above lo fits
+                st_bstar = 0;
+                st_theta = level == 0 ? -1.f : lo;
+              } else if (bb < kBins - 1) {
+                st_bstar = bb + 1;
+                st_theta = lo + (float)(bb + 1) * wdt;
+              } else if (level == 0) {  // the top bin alone overflows: refine inside it
+                st_lo = lo + (float)(kBins - 1) * wdt;
+                st_w = wdt / (float)kBins;
+                st_theta = -2.f;
+              } else {
+                st_mode = 1;
+              }
             }
           }
           __syncthreads();
           if (st_theta != -2.f || st_mode == 1) break;
         }
       }
-      // samples outside the global shell are bounded by theta_out
-      if (from_gs && tid == 0 && st_mode == 0) st_theta = fmaxf(st_theta, theta_out);
       __syncthreads();
       // ---------------- collect, ordered by fine bins over [max(theta,0), rref]
       if (st_mode == 0) {
         const float lo = st_lo, wdt = st_w, theta = st_theta;
         const int bstar = st_bstar;
-        const float flo = fmaxf(theta, 0.f);
+        const float flo = fmaxf(theta, mn);
         const float fw = (rref - flo) / (float)kBins;
         const bool fine = fw > 0.f;
         const float rw = wdt > 0.f ? 1.f / wdt : 0.f, rfw = fine ? 1.f / fw : 0.f;
@@ -858,15 +957,19 @@ __device__ __forceinline__ void chain_run(const ChainShared &S, const int64_t *_
             if (member(dd[u])) atomicAdd(&S.hist[fbin(dd[u])], 1u);
         });
         __syncthreads();
-        if (tid == 0) {
+        if (wave == 0) {
           // entries in decreasing fine-bin order: cursor[b] = first slot of bin b
-          unsigned int c = 0;
-          for (int bb = kBins - 1; bb >= 0; --bb) {
-            S.cursor[bb] = c;
-            c += S.hist[bb];
+          unsigned int c[4];
+          unsigned int at = bins_above(S.hist, c);
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            S.cursor[kBins - 1 - 4 * lane - k] = at;
+            at += c[k];
           }
-          sh_n = c;
-          if (c > (unsigned)cap) st_mode = 1;
+          if (lane == 63) {
+            sh_n = at;
+            if (at > (unsigned)cap) st_mode = 1;
+          }
         }
         __syncthreads();
         if (st_mode == 0) {
@@ -883,8 +986,8 @@ __device__ __forceinline__ void chain_run(const ChainShared &S, const int64_t *_
             }
           });
           __syncthreads();
-          // (global shell: the entry index becomes the sample id)
-          if (from_gs) {
+          // (undominated samples: the entry index becomes the sample id)
+          if (from_dm) {
             for (int e = tid; e < (int)sh_n; e += BLK) {
               const int x = S.id[e];
               S.pt[e] = gpt[x];
@@ -895,42 +998,53 @@ __device__ __forceinline__ void chain_run(const ChainShared &S, const int64_t *_
           }
           __syncthreads();
           // upper bound of d_ref over each chunk of 64 entries: the upper edge
-          // of the fine bin holding its first entry (the top bin's is rref)
+          // of the fine bin holding its first entry (the top bin's is rref);
+          // cursor[b] is the end of bin b's entries now
           const int K = (int)sh_n;
           for (int c = tid; c * 64 < K && c < kMaxChunks; c += BLK) {
             const unsigned int e = (unsigned)c * 64u;
-            unsigned int acc_n = 0;
-            int bb = kBins - 1;
-            for (; bb > 0; --bb) {
-              if (e < acc_n + S.hist[bb]) break;
-              acc_n += S.hist[bb];
+            int lo_b = 0, hi_b = kBins - 1;  // the highest bin that ends beyond e
+            while (lo_b < hi_b) {
+              const int mid = (lo_b + hi_b + 1) >> 1;
+              if (S.cursor[mid] > e)
+                lo_b = mid;
+              else
+                hi_b = mid - 1;
             }
-            S.chunk_ub[c] = (bb >= kBins - 1 || !fine) ? rref : flo + (float)(bb + 1) * fw;
+            S.chunk_ub[c] = (lo_b >= kBins - 1 || !fine) ? rref : flo + (float)(lo_b + 1) * fw;
           }
         }
         __syncthreads();
       }
     }
     if (global || st_mode == 1) {
-      // ---------------------------------------------------- global-scan steps
-      // every feasible sample, all waves; a bounded number of steps per stage
-      float4 C = Cref;
+      // ------------------------------------------------------------ scan steps
+      // every feasible sample (the undominated ones while the centre is in
+      // their ball), all waves; a bounded number of steps per stage
+      float4 C = C0;
       int i = i0;
       int par = 0;
       if (tid == 0) ++sdg.n_global;
-      const int i_end = no_prune ? T : (early ? min(T, kEarlySteps) : min(T, i0 + kGlobalSteps - 1));
+      const bool from_dm = use_dm && !no_prune;
+      const float4 *src = from_dm ? gpt : D;
+      const int n_src = from_dm ? sg.n : M;
+      const int i_end = no_prune ? T : (early ? min(T, kEarlyFull) : min(T, i0 + kScanSteps - 1));
       while (i <= i_end) {
+        if (from_dm && !in_dm(C)) break;  // (never on the stage's first step)
         float bk = -1.f;
         int bi = INT32_MAX;
-        stream_rounds<BLK>(D, M, make_float4(-2.f, 0.f, 0.f, 0.f), [&](const float4 *a, int s0) {
+        stream_rounds<BLK>(src, n_src, make_float4(-2.f, 0.f, 0.f, 0.f), [&](const float4 *a, int s0) {
 #pragma unroll
           for (int u = 0; u < kUnroll; ++u) {
-            int s = s0 + u * BLK + tid;
-            if (s < M && feasible_pt(a[u], chain)) {
-              float k = sqdist(C, a[u], chain);
-              if (better(k, s, bk, bi)) {
-                bk = k;
-                bi = s;
+            const int q = s0 + u * BLK + tid;
+            if (q < n_src && feasible_pt(a[u], chain)) {
+              const float k = sqdist(C, a[u], chain);
+              if (k >= bk) {
+                const int s = from_dm ? gid[q] : q;
+                if (better(k, s, bk, bi)) {
+                  bk = k;
+                  bi = s;
+                }
               }
             }
           }
@@ -1000,7 +1114,10 @@ __device__ __forceinline__ void chain_run(const ChainShared &S, const int64_t *_
       // starting iterate and a sequential segment redoes the step.
       const int K = (int)sh_n;
       const float theta = st_theta;
-      const float slack = 4e-6f * st_rref + 1e-30f;
+      const float slack = 4e-6f * rref + 1e-30f;
+      // a shell of several chunks is cut down again once the steps have become
+      // half as long
+      const int refine_end = ball.chk < FLT_MAX && (int)sh_n > 64 ? min(T, max(2 * i0, kEarlyFull + 1) - 1) : T;
       const int nchunks = (K + 63) / 64;
       const float4 p0 = S.pt[lane < K ? lane : 0], p1 = S.pt[64 + lane < K ? 64 + lane : 0];
       const int q0 = S.id[lane < K ? lane : 0], q1 = S.id[64 + lane < K ? 64 + lane : 0];
@@ -1014,24 +1131,26 @@ __device__ __forceinline__ void chain_run(const ChainShared &S, const int64_t *_
       // square root is within the slack).  Rotation: |C + C_ref|^2 = 4 -
       // |C - C_ref|^2 for unit quaternions (C stays near C_ref within a stage;
       // the form only feeds bounds).
-      auto drift = [&](float4 Cc) {
+      auto drift = [&](float4 Cc, bool &inside) {  // inside: C is in the ball the shell holds for
         float dC2;
         if (CHAIN == 0) {
           const float e0 = Cc.x - Cref.x, e1 = Cc.y - Cref.y, e2 = Cc.z - Cref.z, e3 = Cc.w - Cref.w;
           const float xc = fmaf(e3, e3, fmaf(e2, e2, fmaf(e1, e1, e0 * e0)));
+          inside = xc <= ball.chk;
           dC2 = (2.f * xc) * (4.f - xc);
         } else {
           dC2 = sqdist(Cc, Cref, chain);
+          inside = dC2 <= ball.chk;
         }
         return __builtin_amdgcn_sqrtf(dC2);
       };
       // wave-0 state carried across the segments of the stage
-      float4 C = Cref;
+      float4 C = C0;
       int i = i0;
       int misses = 0;                // one-chunk steps that needed more
       bool wide = false, ended = false;
       int backoff = kPipeMinSeq;     // steps with no new winner before a pipelined segment
-      const int last_plain = T - avg;  // steps after this one accumulate their iterate
+      const int last_plain = min(T - avg, refine_end);  // steps after T - avg accumulate their iterate
       // wave 0: candidate winners in lanes 0..7 (id -1: empty, its point C_ref,
       // which is never the farthest), the slot the next new winner takes, and
       // the steps since a new winner appeared
@@ -1065,7 +1184,8 @@ __device__ __forceinline__ void chain_run(const ChainShared &S, const int64_t *_
                 inv_tab = 1.f / (float)(ib + lane);
               }
               const float inv = readlane_f(inv_tab, i - ib);
-              const float dC = drift(C);
+              bool inside;
+              const float dC = drift(C, inside);
               auto beats = [&](float key, float ub) {
                 const float b = ub + dC + slack;
                 return key > b * b;
@@ -1086,8 +1206,9 @@ __device__ __forceinline__ void chain_run(const ChainShared &S, const int64_t *_
               float wk = wave_max_key(bk);
               unsigned long long win = __ballot(bk == wk);
               const bool bounded = W == 2 ? (!need_ub2 || beats(wk, ubf2)) : (!need_ub1 || beats(wk, ubf1));
-              if (!(bounded && __popcll(win) == 1)) {
+              if (!(bounded && inside && __popcll(win) == 1)) {
                 // -------------------------------------------- uncommon step
+                if (!inside) return kStageEnds;  // the shell no longer holds
                 if (W == 1 && nchunks > 1 && !beats(wk, ub1)) {
                   take(sqdist(C, p1, chain), q1, p1);
                   wk = wave_max_key(bk);
@@ -1171,9 +1292,9 @@ __device__ __forceinline__ void chain_run(const ChainShared &S, const int64_t *_
           };
           const int long_end = min(T, kShortSeriesStep - 1);
           run_range(std::false_type(), std::false_type(), min(long_end, last_plain));
-          run_range(std::false_type(), std::true_type(), long_end);
-          run_range(std::true_type(), std::false_type(), last_plain);
-          run_range(std::true_type(), std::true_type(), T);
+          if (i > T - avg) run_range(std::false_type(), std::true_type(), min(long_end, refine_end));
+          if (i > long_end) run_range(std::true_type(), std::false_type(), last_plain);
+          if (i > T - avg && i > long_end) run_range(std::true_type(), std::true_type(), refine_end);
           if (lane < i - ib) tr[2 * (ib - 1 + lane)] = trv;
           if (lane == 0) sdg.n_groups += stage_groups;
           stage_groups = 0;
@@ -1304,7 +1425,8 @@ __device__ __forceinline__ void chain_run(const ChainShared &S, const int64_t *_
             for (int k = vw; k < n_p; k += kVerifiers) {
               const float4 Cv = pl_C[pslot][k];
               const int pid = pl_W[pslot][k];
-              const float dC = drift(Cv);
+              bool inside;
+              const float dC = drift(Cv, inside);
               auto beats = [&](float key, float ub) {
                 const float b = ub + dC + slack;
                 return key > b * b;
@@ -1318,7 +1440,7 @@ __device__ __forceinline__ void chain_run(const ChainShared &S, const int64_t *_
               };
               take(sqdist(Cv, p1, chain), q1);
               float wk = wave_max_key(bk);
-              bool ok = true;
+              bool ok = inside;
               if (need_ub2 && !beats(wk, ubf2)) {
                 // further chunks until one bounds the rest, then the samples
                 // outside the shell
@@ -1377,10 +1499,8 @@ __device__ __forceinline__ void chain_run(const ChainShared &S, const int64_t *_
         // the next write to either follows the barrier that ends the next
         // sequential segment)
       }
-      // a stage that made no step: with the global shell, rescan every
-      // sample next; else a stage of full scans
-      stalled = st_i == i0 && !use_gs;
-      if (st_i == i0) use_gs = false;
+      // after a stage that made no step, a stage of scan steps
+      stalled = st_i == i0;
     }
   }
   // ------------------------------------------------------------------ centre
@@ -1421,8 +1541,9 @@ __global__ void __launch_bounds__(chain_block<V>(), V == kChainWide ? 1 : 4) k_m
                                                             const float4 *__restrict__ trans, MegbRec *rec,
                                                             float *dref_all, int64_t total_samples,
                                                             int32_t *trace, float4 *ckpt, int ck, int T, int avg,
-                                                            int cap, int no_prune, int32_t *gid,
-                                                            float4 *gpt, int64_t gstride) {
+                                                            int cap, int no_prune, int n_early,
+                                                            const EarlyScratch *es, int32_t *gid, float4 *gpt,
+                                                            int64_t gstride) {
   extern __shared__ float4 sh_pt[];
   __shared__ unsigned int hist[kBins];
   __shared__ unsigned int cursor[kBins];
@@ -1432,10 +1553,10 @@ __global__ void __launch_bounds__(chain_block<V>(), V == kChainWide ? 1 : 4) k_m
   const ChainShared S{sh_pt, reinterpret_cast<int *>(sh_pt + cap), hist, cursor, chunk_ub, red_k, red_i};
   if (blockIdx.x & 1)
     chain_run<1, V>(S, sample_off, max_m, trans, rec, dref_all, total_samples, trace, ckpt, ck, T, avg, cap,
-                       no_prune, gid, gpt, gstride);
+                       no_prune, n_early, es, gid, gpt, gstride);
   else
     chain_run<0, V>(S, sample_off, max_m, quat, rec, dref_all, total_samples, trace, ckpt, ck, T, avg, cap,
-                       no_prune, gid, gpt, gstride);
+                       no_prune, n_early, es, gid, gpt, gstride);
 }
 
 // float64 radii about the centre: max ||R* - R_s||_F^2 and ||t* - t_s||^2.
@@ -1952,25 +2073,22 @@ void launch_megb(const DevBatch &b, const DevParams &p, const float *poses, cons
   const size_t lds = (size_t)cap * (sizeof(float4) + sizeof(int));
   const int no_prune = (p.flags & PURSE_FLAG_NO_PRUNING) ? 1 : 0;
   const int64_t gstride = gshell_stride(total_samples, max_samples);
-  if (early_phase_applies(max_samples, p.megb_iters, p.megb_avg, no_prune)) {
+  const int n_early = early_steps(max_samples, wide);
+  if (early_phase_applies(max_samples, p.megb_iters, p.megb_avg, no_prune, n_early)) {
     const dim3 eg((unsigned)kEarlyWG, 2u, (unsigned)n);
-    for (int i = 1; i <= kEarlySteps + 1; ++i)
+    for (int i = 1; i <= n_early; ++i)
       hipLaunchKernelGGL(k_megb_early, eg, dim3(kEarlyBlock), 0, stream, b.sample_off, total_samples, max_samples,
-                         quat, trans, rec, es, dref, trace, ckpt, ck, p.megb_iters, p.megb_avg, cap, no_prune, i);
-    hipLaunchKernelGGL(k_megb_gshell_hist, eg, dim3(kEarlyBlock), 0, stream, b.sample_off, total_samples,
-                       max_samples, rec, es, dref, p.megb_iters, p.megb_avg, cap, no_prune);
-    hipLaunchKernelGGL(k_megb_gshell_collect, eg, dim3(kEarlyBlock), 0, stream, b.sample_off, total_samples,
-                       max_samples, quat, trans, rec, es, dref, gid, gpt, gstride, p.megb_iters, p.megb_avg, cap,
-                       no_prune);
+                         quat, trans, rec, es, trace, ckpt, ck, p.megb_iters, p.megb_avg, cap, no_prune, n_early, gid,
+                         gpt, gstride, i);
   }
   if (wide)
     hipLaunchKernelGGL(k_megb_chain<kChainWide>, dim3(2 * n), dim3(chain_block<kChainWide>()), lds, stream,
                        b.sample_off, max_samples, quat, trans, rec, dref, total_samples, trace, ckpt, ck, p.megb_iters,
-                       p.megb_avg, cap, no_prune, gid, gpt, gstride);
+                       p.megb_avg, cap, no_prune, n_early, es, gid, gpt, gstride);
   else
     hipLaunchKernelGGL(k_megb_chain<kChainNarrow>, dim3(2 * n), dim3(chain_block<kChainNarrow>()), lds, stream,
                        b.sample_off, max_samples, quat, trans, rec, dref, total_samples, trace, ckpt, ck, p.megb_iters,
-                       p.megb_avg, cap, no_prune, gid, gpt, gstride);
+                       p.megb_avg, cap, no_prune, n_early, es, gid, gpt, gstride);
   hipLaunchKernelGGL(k_megb_sign, dim3(n), dim3(kBlock), 0, stream, b.sample_off, total_samples, max_samples, poses,
                      trace, rec, p.megb_iters, ck);
   if (p.flags & PURSE_FLAG_EXACT_MEB)
