@@ -226,9 +226,9 @@ __device__ __forceinline__ int bin_of(float d, float lo, float rw) {
 // against 40-1,600 after 128.)
 //
 // Witnesses are the last distinct winners, at most eight.  C_ref is the mean
-// of the later half of the rotation iterates kept so far (checkpoints; the
-// iterates zigzag about their limit) and the current one, else the current
-// iterate.  rho is a multiple of the next step's length, h / i: the rest of
+// of the iterates of the later half of the steps taken (the iterates zigzag
+// about their limit): of the kept ones (checkpoints) for rotations, of at most
+// the last 64 for translations, else the current iterate.  rho is a multiple of the next step's length, h / i: the rest of
 // the path from step i on stays within 0.6-1.4 such lengths of that mean, and
 // within 1.0-2.1 of the iterate itself, on the clouds it was measured on; a
 // centre beyond it only ends the stage.
@@ -338,6 +338,28 @@ __device__ __forceinline__ void build_domination(Domination &S, float4 C, int i0
       f = i0 < 64 ? 1.5f : 1.3f;
     }
   }
+  if (chain == 1 && taken >= 4) {
+    // c_m is the mean of the first m winners, so going back from C the sums
+    // m c_m lose one winner at a time
+    const float4 p = D[v >= 0 ? v : 0];
+    float4 a = v >= 0 ? p : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const float ux = __shfl_up(a.x, o, 64), uy = __shfl_up(a.y, o, 64), uz = __shfl_up(a.z, o, 64);
+      a.x += lane >= o ? ux : 0.f;
+      a.y += lane >= o ? uy : 0.f;
+      a.z += lane >= o ? uz : 0.f;
+    }
+    // lane l: a is the sum of the last l + 1 winners, for c_(taken - l - 1)
+    const int m = taken - lane - 1, back = min(63, taken / 2);
+    const bool use = lane < back && v >= 0 && m >= 1;
+    const float im = use ? 1.f / (float)m : 0.f, tk = (float)taken;
+    const float inv_n = 1.f / (1.f + wave_sum(use ? 1.f : 0.f));
+    R.x = (wave_sum(use ? (tk * C.x - a.x) * im : 0.f) + C.x) * inv_n;
+    R.y = (wave_sum(use ? (tk * C.y - a.y) * im : 0.f) + C.y) * inv_n;
+    R.z = (wave_sum(use ? (tk * C.z - a.z) * im : 0.f) + C.z) * inv_n;
+    f = i0 < 64 ? 1.5f : 1.3f;
+  }
   const float inv = 1.f / (float)i0;
   float4 w = pw;
   float x = near_sq(R, w, chain);
@@ -378,10 +400,12 @@ constexpr int kEarlyBlock = 256;
 constexpr int kEarlyList = 4096;  // undominated samples of a workgroup held in LDS before they are written
 
 // Steps of the first phase: until the undominated samples (about 6, 1.5, 0.6
-// and 0.3 % of all after 16, 32, 48 and 64 steps) fit the shell of a chain.
+// and 0.3 % of all after 16, 32, 48 and 64 steps) are few enough for one
+// workgroup to scan them as fast as a launch takes its step (5 us, about
+// 20,000 entries in the wide variant).
 inline int early_steps(int64_t max_samples, bool wide) {
   const int64_t m = wide ? max_samples : 4 * max_samples;
-  return m <= (1 << 17) ? kEarlyFull + 1 : (m <= (1 << 19) ? 33 : (m <= (1 << 21) ? 49 : 65));
+  return m <= (1 << 19) ? kEarlyFull + 1 : (m <= (1 << 21) ? 49 : 65);
 }
 
 __host__ __device__ inline bool early_phase_applies(int64_t M, int T, int avg, int no_prune, int n_early) {
@@ -641,6 +665,130 @@ __global__ void __launch_bounds__(kBlock) k_megb_prep(const int64_t *__restrict_
   }
 }
 
+// ---------------------------------------------------------------------------
+// The rotation step with the quaternion's components across lanes, for the
+// one wavefront that runs a descent ahead: lane l holds component l & 3 of
+// the iterate and of one candidate winner, lanes with bit 2 clear form
+// |a - b|^2 and the others |a + b|^2, and every group of eight lanes (row of
+// sixteen with four candidates, half with two) takes the step toward its own
+// candidate.  The same operations in the same order as
+// geodesic_step_inv<true>, so bitwise its results.  A lone wavefront issues one
+// instruction every 4 to 6 cycles whatever it does, so the step is bound by
+// its instruction count.  Measured alone on a compute unit: 442 cycles with
+// eight candidates, 424 with four, 300 with the winner known, against 548 with
+// one candidate per lane and the whole quaternion in it.
+template <int CTRL>
+__device__ __forceinline__ float dpp_f(float x) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), CTRL, 0xF, 0xF, true));
+}
+
+// Sum of the squares of a quad's four lanes, in every lane of the quad.
+__device__ __forceinline__ float quad_norm_sq(float m) {
+  const float m0 = dpp_f<0x00>(m), m1 = dpp_f<0x55>(m), m2 = dpp_f<0xAA>(m), m3 = dpp_f<0xFF>(m);
+  return fmaf(m3, m3, fmaf(m2, m2, fmaf(m1, m1, m0 * m0)));
+}
+
+struct RotLane {
+  float b, bm;  // candidate's component; +b where |a + b|^2 is formed, else -b
+  bool plus;    // (lane & 4) != 0
+};
+__device__ __forceinline__ RotLane rot_lane(float4 b) {
+  const int c = threadIdx.x & 3;
+  RotLane r;
+  r.b = c == 0 ? b.x : (c == 1 ? b.y : (c == 2 ? b.z : b.w));
+  r.plus = (threadIdx.x & 4) != 0;
+  r.bm = r.plus ? r.b : -r.b;
+  return r;
+}
+
+// inv4: 4 / i.  key: the candidate's key (sqdist of chain 0).
+__device__ __forceinline__ float rot_lane_step(float a, const RotLane &r, float inv4, float &key) {
+  const float v = quad_norm_sq(a + r.bm);
+  const float o = dpp_f<0x141>(v);  // row_half_mirror: the group's other quad
+  RotChords c;
+  c.xs = fminf(v, o);
+  const float ys = fmaxf(v, o);
+  key = (2.f * c.xs) * ys;
+  c.rx = __builtin_amdgcn_sqrtf(c.xs);
+  c.ry = __builtin_amdgcn_sqrtf(ys);
+  const float bs = (r.plus ? o : v) > c.xs ? -r.b : r.b;  // a . b < 0: |a - b|^2 is the larger
+  const float th = atan_eighth(c.rx * __builtin_amdgcn_rcpf(2.f + c.ry)) * inv4;
+  float st, ct;
+  sincos_small(th, st, ct);
+  const float sh = (0.5f * c.rx) * c.ry;
+  const float chh = fmaf(-0.5f, c.xs, 1.f);
+  const float cb = st * __builtin_amdgcn_rcpf(fmaxf(sh, 1e-30f));
+  const float ca = fmaf(-chh, cb, ct);
+  const float q = fmaf(cb, bs, ca * a);
+  float n = q * __builtin_amdgcn_rsqf(quad_norm_sq(q));
+  // (rounded here: the next step's a + bm must not be fused with this product)
+  __asm__("" : "+v"(n));
+  return n;
+}
+
+// The value of the lane group with the larger key, of two rows of sixteen
+// lanes (ROW) or two halves of the wavefront; ties take the lower one.
+template <bool ROW>
+__device__ __forceinline__ void swap_pair(float x, float &lo, float &hi) {
+  const unsigned u = __float_as_uint(x);
+  const auto p = ROW ? __builtin_amdgcn_permlane16_swap(u, u, false, false)
+                     : __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  lo = __uint_as_float(p[0]);
+  hi = __uint_as_float(p[1]);
+}
+
+// n steps from the iterate whose component a holds, each toward the candidate
+// with the largest key, the one of the lowest lanes among equal keys; the
+// starting iterates' components go to rec[4 k].  inv4_tab: 4 / i of step `lane`.
+template <int NC>
+__device__ __forceinline__ float rot_lane_run(float a, const RotLane &r, float inv4_tab, int n, float *rec) {
+  const int upper = (threadIdx.x >> 3) & 1;
+#pragma unroll 2
+  for (int k = 0; k < n; ++k) {
+    rec[4 * k] = a;
+    float key;
+    float v = rot_lane_step(a, r, readlane_f(inv4_tab, k), key);
+    float lo, hi;
+    if (NC == 8) {
+      // row_ror:8: the row's other group (keys are not negative, so their bits
+      // order like the values)
+      const float ko = dpp_f<0x128>(key), vo = dpp_f<0x128>(v);
+      v = __float_as_int(ko) + upper > __float_as_int(key) ? vo : v;
+      key = fmaxf(key, ko);
+    }
+    if (NC >= 4) {
+      swap_pair<true>(key, lo, hi);
+      const bool row = hi > lo;
+      key = fmaxf(lo, hi);
+      swap_pair<true>(v, lo, hi);
+      v = row ? hi : lo;
+    }
+    swap_pair<false>(key, lo, hi);
+    const bool half = hi > lo;
+    swap_pair<false>(v, lo, hi);
+    a = half ? hi : lo;
+  }
+  return a;
+}
+
+// The same with known winners: r0 on even steps, r1 on odd ones.
+__device__ __forceinline__ float rot_lane_alternate(float a, const RotLane &r0, const RotLane &r1, float inv4_tab,
+                                                    int n, float *rec) {
+  float key;
+  int k = 0;
+  for (; k + 1 < n; k += 2) {
+    rec[4 * k] = a;
+    a = rot_lane_step(a, r0, readlane_f(inv4_tab, k), key);
+    rec[4 * k + 4] = a;
+    a = rot_lane_step(a, r1, readlane_f(inv4_tab, k + 1), key);
+  }
+  if (k < n) {
+    rec[4 * k] = a;
+    a = rot_lane_step(a, r0, readlane_f(inv4_tab, k), key);
+  }
+  return a;
+}
+
 // A chain's undominated samples in global memory (the state only rescans and
 // scan steps read) and its diagnostics.
 struct ChainDm {
@@ -713,7 +861,8 @@ __device__ __forceinline__ void chain_run(const ChainShared &S, const int64_t *_
   __shared__ unsigned int sh_n;
   // pipelined shell steps
   __shared__ float4 pl_C[3][kPipeSteps];  // starting iterate of each step of a round (3 rounds in flight)
-  __shared__ int pl_W[3][kPipeSteps];     // and its predicted winner
+  __shared__ int pl_W[3][kPipeSteps];     // and its winner, from the check
+  __shared__ int pl_cand[8], pl_two;      // the candidates of the predictions
   __shared__ int pl_fail[3];              // first step of a round whose prediction failed
   __shared__ float4 pl_Cend;
   __shared__ int pl_go;
@@ -896,7 +1045,13 @@ __device__ __forceinline__ void chain_run(const ChainShared &S, const int64_t *_
         st_bstar = 0;
       }
       __syncthreads();
-      if (n_kept > cap) {
+      // Early, when the undominated samples that do not fit the shell will soon
+      // be fewer, a few scans of them (3-4 us each) come first.
+      const bool scan_first = n_kept > cap && n_kept <= 4 * cap && use_dm && i0 < 8 * kEarlyFull;
+      if (scan_first) {
+        if (tid == 0) st_mode = 1;
+        __syncthreads();
+      } else if (n_kept > cap) {
         for (int level = 0; level < 2; ++level) {
           const float lo = st_lo, wdt = st_w;
           if (!(wdt > 0.f)) {
@@ -1116,8 +1271,9 @@ __device__ __forceinline__ void chain_run(const ChainShared &S, const int64_t *_
       const float theta = st_theta;
       const float slack = 4e-6f * rref + 1e-30f;
       // a shell of several chunks is cut down again once the steps have become
-      // half as long
-      const int refine_end = ball.chk < FLT_MAX && (int)sh_n > 64 ? min(T, max(2 * i0, kEarlyFull + 1) - 1) : T;
+      // half as long (the first one, which has no witnesses yet, after kEarlyFull steps)
+      const int refine_end = (ball.chk < FLT_MAX || early) && (int)sh_n > 64 ? min(T, max(2 * i0, kEarlyFull + 1) - 1)
+                                                                             : T;
       const int nchunks = (K + 63) / 64;
       const float4 p0 = S.pt[lane < K ? lane : 0], p1 = S.pt[64 + lane < K ? 64 + lane : 0];
       const int q0 = S.id[lane < K ? lane : 0], q1 = S.id[64 + lane < K ? 64 + lane : 0];
@@ -1158,6 +1314,7 @@ __device__ __forceinline__ void chain_run(const ChainShared &S, const int64_t *_
       float4 cand_p = Cref;
       int nins = 0, stable = 0;
       int last_w = -1;  // winner of the last sequential step
+      int turn_fails = 0;  // two candidates are taken in turn, until that has failed twice
       while (true) {
         if (wave == 0) {
           int ib = i;                                 // first step of the block of 64
@@ -1311,23 +1468,60 @@ __device__ __forceinline__ void chain_run(const ChainShared &S, const int64_t *_
         const int pi0 = st_i, pend = last_plain;
         const int nrounds = (pend - pi0 + kPipeSteps) / kPipeSteps;
         float4 Cs = st_C;                       // wave 0: the iterate ahead
-        float4 cv = Cs;                         // wave 0: starting iterate of step (round start + lane)
-        int pv = 0;                             // wave 0: predicted winner of that step
         int fail_step = INT32_MAX;
         float4 fail_C = Cs;
         // wave 0: when only two samples have won since the stage began the
         // winners alternate; the first predicted winner is then the one not
         // taken last
-        const unsigned long long vm = __ballot(cand_id >= 0) & 0xFFull;
-        const bool two = __popcll(vm) == 2;
+        unsigned long long vm = __ballot(cand_id >= 0) & 0xFFull;
+        // (in increasing order of the ids, so that the lowest lane of equal
+        // keys is the argmax's choice; empty slots last)
+        {
+          const int n_cand = __popcll(vm);
+          int rank = cand_id >= 0 ? 0 : n_cand + __popcll(~vm & ((1ull << (lane & 7)) - 1ull));
+#pragma unroll
+          for (int c = 0; c < 8; ++c) {
+            const int o = __builtin_amdgcn_readlane(cand_id, c);
+            rank += cand_id >= 0 && o >= 0 && o < cand_id ? 1 : 0;
+          }
+          const int to = lane < 8 ? 4 * rank : 4 * lane;
+          cand_id = __builtin_amdgcn_ds_permute(to, cand_id);
+          cand_p.x = __int_as_float(__builtin_amdgcn_ds_permute(to, __float_as_int(cand_p.x)));
+          cand_p.y = __int_as_float(__builtin_amdgcn_ds_permute(to, __float_as_int(cand_p.y)));
+          cand_p.z = __int_as_float(__builtin_amdgcn_ds_permute(to, __float_as_int(cand_p.z)));
+          cand_p.w = __int_as_float(__builtin_amdgcn_ds_permute(to, __float_as_int(cand_p.w)));
+          nins = n_cand & 7;
+          vm = (1ull << n_cand) - 1ull;
+        }
+        const bool pair = __popcll(vm) == 2, two = pair && turn_fails < 2;
         const int l0 = (int)__ffsll((long long)vm) - 1, l1 = (int)__ffsll((long long)(vm & (vm - 1ull))) - 1;
         const bool zero_last = __builtin_amdgcn_readlane(cand_id, two ? l0 : 0) == last_w;
         const int la = two ? (zero_last ? l1 : l0) : 0, lb = two ? (zero_last ? l0 : l1) : 0;
-        const int idA = __builtin_amdgcn_readlane(cand_id, la), idB = __builtin_amdgcn_readlane(cand_id, lb);
         const float4 pA = make_float4(readlane_f(cand_p.x, la), readlane_f(cand_p.y, la), readlane_f(cand_p.z, la),
                                       readlane_f(cand_p.w, la));
         const float4 pB = make_float4(readlane_f(cand_p.x, lb), readlane_f(cand_p.y, lb), readlane_f(cand_p.z, lb),
                                       readlane_f(cand_p.w, lb));
+        // the candidates of a round's prediction, for its check: the two in
+        // turn, or eight (empty ones -1)
+        const bool four = __popcll(vm) <= 4;
+        if (wave == 0) {
+          if (lane < 8) pl_cand[lane] = two ? (lane == 0 ? __builtin_amdgcn_readlane(cand_id, la)
+                                                         : (lane == 1 ? __builtin_amdgcn_readlane(cand_id, lb) : -1))
+                                            : cand_id;
+          if (lane == 0) pl_two = two ? 1 : 0;
+        }
+        // rotation chain: the iterate's component and the lanes' candidates
+        // (candidates fill the slots from 0 on, so at most four are in 0..3)
+        RotLane rl = rot_lane(pA), rl1 = rot_lane(pB);
+        float al = 0.f;
+        if (CHAIN == 0) {
+          al = (lane & 3) == 0 ? Cs.x : ((lane & 3) == 1 ? Cs.y : ((lane & 3) == 2 ? Cs.z : Cs.w));
+          if (!two) {
+            const int slot_of = pair ? lane >> 5 : (four ? lane >> 4 : lane >> 3);
+            rl = rot_lane(make_float4(__shfl(cand_p.x, slot_of, 64), __shfl(cand_p.y, slot_of, 64),
+                                      __shfl(cand_p.z, slot_of, 64), __shfl(cand_p.w, slot_of, 64)));
+          }
+        }
         for (int r = 0; r <= nrounds; ++r) {
           const int s_r = pi0 + r * kPipeSteps;
           const int slot = r % 3;
@@ -1337,134 +1531,111 @@ __device__ __forceinline__ void chain_run(const ChainShared &S, const int64_t *_
               const int n_r = min(kPipeSteps, pend - s_r + 1);
               const float pinv_tab = 1.f / (float)(s_r + lane);  // 1/i of step s_r + lane
               // (kPipeSteps is even: step k of every round takes A when k is even)
-              if (two) {
+              float *rec_c = reinterpret_cast<float *>(&pl_C[slot][0]) + (lane & 3);
+              if constexpr (CHAIN == 0) {
+                const float inv4 = 4.f * pinv_tab;
+                al = two ? rot_lane_alternate(al, rl, rl1, inv4, n_r, rec_c)
+                         : (pair ? rot_lane_run<2>(al, rl, inv4, n_r, rec_c)
+                                 : (four ? rot_lane_run<4>(al, rl, inv4, n_r, rec_c)
+                                         : rot_lane_run<8>(al, rl, inv4, n_r, rec_c)));
+              } else if (two) {
                 for (int k = 0; k < n_r; ++k) {
                   const float inv = readlane_f(pinv_tab, k);
-                  const bool odd = (k & 1) != 0;
-                  const float4 pp = odd ? pB : pA;
-                  const bool mine = lane == k;
-                  cv = make_float4(mine ? Cs.x : cv.x, mine ? Cs.y : cv.y, mine ? Cs.z : cv.z, mine ? Cs.w : cv.w);
-                  pv = mine ? (odd ? idB : idA) : pv;
-                  Cs = geodesic_step_inv<true>(Cs, pp, inv, chain);
+                  if (lane == 0) pl_C[slot][k] = Cs;
+                  Cs = geodesic_step_inv<true>(Cs, (k & 1) ? pB : pA, inv, chain);
                 }
-              } else
-              for (int k = 0; k < n_r; ++k) {
-                const float inv = readlane_f(pinv_tab, k);
-                // predicted winner: the argmax over the candidates (lanes
-                // 0..7) with the keys and tie rule of the full argmax, near
-                // convergence the candidates being almost equidistant
-                // The step toward every candidate, one per lane, alongside
-                // the argmax (sharing the chords of the keys): the winner's
-                // lane holds bitwise the step toward the winner.  For the
-                // rotation chain the stages of the step are placed between
-                // those of the argmax's reduction (scheduling barriers), so
-                // that the two dependent chains overlap in the one wave.
-                float u;
-                float4 Cn;
-                int ub;
-                if constexpr (CHAIN == 0) {
-                  float x, y;
-                  rot_chord_sq(Cs, cand_p, x, y);
-                  u = (2.f * x) * y;  // the key of sqdist
-                  ub = __float_as_int(u);
-                  ub = max(ub, __builtin_amdgcn_update_dpp(INT32_MIN, ub, 0xB1, 0xF, 0xF, false));   // quad_perm [1,0,3,2]
-                  // (the empty asm statements keep each stage where it is
-                  // written: without them the compiler moves the step's
-                  // stages below the argmax, to their first use)
-                  RotChords rc = rot_chords(x, y);
-                  __asm__ volatile("" : "+v"(rc.xs), "+v"(rc.rx), "+v"(rc.ry));
-                  __builtin_amdgcn_sched_barrier(0);
-                  ub = max(ub, __builtin_amdgcn_update_dpp(INT32_MIN, ub, 0x4E, 0xF, 0xF, false));   // quad_perm [2,3,0,1]
-                  float th = rot_step_angle(rc, inv);
-                  __asm__ volatile("" : "+v"(th));
-                  __builtin_amdgcn_sched_barrier(0);
-                  ub = max(ub, __builtin_amdgcn_update_dpp(INT32_MIN, ub, 0x141, 0xF, 0xF, false));  // row_half_mirror
-                  Cn = rot_interp<true>(rc, th, Cs, cand_p);
-                  __asm__ volatile("" : "+v"(Cn.x), "+v"(Cn.y), "+v"(Cn.z), "+v"(Cn.w));
-                } else {
-                  u = sqdist(Cs, cand_p, chain);
-                  Cn = geodesic_step_inv<true>(Cs, cand_p, inv, chain);
-                  ub = __float_as_int(u);
+              } else {
+                for (int k = 0; k < n_r; ++k) {
+                  const float inv = readlane_f(pinv_tab, k);
+                  // predicted winner: the argmax over the candidates (lanes
+                  // 0..7) with the keys of the full argmax; the step toward
+                  // every candidate, one per lane, alongside it
+                  const float u = sqdist(Cs, cand_p, chain);
+                  const float4 Cn = geodesic_step_inv<true>(Cs, cand_p, inv, chain);
+                  int ub = __float_as_int(u);
                   ub = max(ub, __builtin_amdgcn_update_dpp(INT32_MIN, ub, 0xB1, 0xF, 0xF, false));
                   ub = max(ub, __builtin_amdgcn_update_dpp(INT32_MIN, ub, 0x4E, 0xF, 0xF, false));
                   ub = max(ub, __builtin_amdgcn_update_dpp(INT32_MIN, ub, 0x141, 0xF, 0xF, false));
+                  const int umax = __builtin_amdgcn_readlane(ub, 0);
+                  const unsigned long long at_max = __ballot(__float_as_int(u) == umax) & 0xFFull;
+                  const int wl = at_max ? (int)__ffsll((long long)at_max) - 1 : 0;
+                  if (lane == 0) pl_C[slot][k] = Cs;
+                  Cs = make_float4(readlane_f(Cn.x, wl), readlane_f(Cn.y, wl), readlane_f(Cn.z, wl),
+                                   readlane_f(Cn.w, wl));
                 }
-                const int umax = __builtin_amdgcn_readlane(ub, 0);
-                const bool at_max = __float_as_int(u) == umax;
-                unsigned long long tie = __ballot(at_max) & 0xFFull;
-                if (__popcll(tie) > 1) {  // equal keys: the lowest sample id
-                  int iv = at_max ? cand_id : INT32_MAX;
-                  iv = min(iv, __builtin_amdgcn_update_dpp(INT32_MAX, iv, 0xB1, 0xF, 0xF, false));
-                  iv = min(iv, __builtin_amdgcn_update_dpp(INT32_MAX, iv, 0x4E, 0xF, 0xF, false));
-                  iv = min(iv, __builtin_amdgcn_update_dpp(INT32_MAX, iv, 0x141, 0xF, 0xF, false));
-                  const int imin = __builtin_amdgcn_readlane(iv, 0);
-                  tie = __ballot(at_max && cand_id == imin) & 0xFFull;
-                }
-                const int wl = (int)__ffsll((long long)tie) - 1;
-                const int pid = __builtin_amdgcn_readlane(cand_id, wl);
-                const bool mine = lane == k;
-                cv = make_float4(mine ? Cs.x : cv.x, mine ? Cs.y : cv.y, mine ? Cs.z : cv.z, mine ? Cs.w : cv.w);
-                pv = mine ? pid : pv;
-                Cs = make_float4(readlane_f(Cn.x, wl), readlane_f(Cn.y, wl), readlane_f(Cn.z, wl), readlane_f(Cn.w, wl));
               }
-              if (lane < n_r) {
-                pl_C[slot][lane] = cv;
-                pl_W[slot][lane] = pv;
-                // (a checkpoint from a step found wrong later is rewritten
-                // when the step is redone)
-                const int im1 = s_r + lane - 1;
-                if (CHAIN == 0 && im1 % ck == 0) ckq[im1 / ck] = cv;
-              }
+              // (a checkpoint from a step found wrong later is rewritten
+              // when the step is redone)
+              if (CHAIN == 0 && lane < n_r && (s_r + lane - 1) % ck == 0)
+                ckq[(s_r + lane - 1) / ck] = pl_C[slot][lane];
+              if (CHAIN == 0) {
+                if (r == nrounds - 1 && lane < 4) reinterpret_cast<float *>(&pl_Cend)[lane] = al;
+              } else
               if (r == nrounds - 1 && lane == 0) pl_Cend = Cs;
             }
           } else if (r >= 1 && wave != kSkipWave) {
-            // check the steps of round r - 1, one wave per step
+            // check the steps of round r - 1, sixteen at a time: four lanes
+            // per step, each scanning every fourth entry of a chunk, until the
+            // bounds rule out the rest for all sixteen
             const int s_p = s_r - kPipeSteps, n_p = min(kPipeSteps, pend - s_p + 1);
             const int pslot = (r + 2) % 3;
             const int vw = wave < kSkipWave ? wave - 1 : wave - 2;
-            for (int k = vw; k < n_p; k += kVerifiers) {
+            const int sub = lane & 3;
+            for (int k0 = 16 * vw; k0 < n_p; k0 += 16 * kVerifiers) {
+              const int k = min(k0 + (lane >> 2), n_p - 1);
               const float4 Cv = pl_C[pslot][k];
-              const int pid = pl_W[pslot][k];
               bool inside;
               const float dC = drift(Cv, inside);
               auto beats = [&](float key, float ub) {
                 const float b = ub + dC + slack;
                 return key > b * b;
               };
-              float bk = sqdist(Cv, p0, chain);
-              int bi = q0;
-              auto take = [&](float kk, int q) {
-                const bool t = (kk > bk) | ((kk == bk) & (q < bi));
-                bk = t ? kk : bk;
-                bi = t ? q : bi;
-              };
-              take(sqdist(Cv, p1, chain), q1);
-              float wk = wave_max_key(bk);
+              // argmax (key desc, id asc) over the lane's entries, then the quad's
+              float bk = -1.f, wk = -1.f;
+              int bi = INT32_MAX, wi = INT32_MAX;
               bool ok = inside;
-              if (need_ub2 && !beats(wk, ubf2)) {
-                // further chunks until one bounds the rest, then the samples
-                // outside the shell
-                int g = 2;
-                while (g < nchunks) {
-                  const float4 p = S.pt[g * 64 + lane];
-                  const int q = S.id[g * 64 + lane];
-                  take(g * 64 + lane < K ? sqdist(Cv, p, chain) : -1.f, q);
-                  wk = wave_max_key(bk);
-                  ++g;
-                  if (g < nchunks && beats(wk, S.chunk_ub[g])) break;
+              for (int g = 0;;) {
+                const int e1 = min(K, 64 * g + 64);
+#pragma unroll 4
+                for (int e = 64 * g + sub; e < e1; e += 4) {
+                  const float kk = sqdist(Cv, S.pt[e], chain);
+                  const int q = S.id[e];
+                  const bool t = (kk > bk) | ((kk == bk) & (q < bi));
+                  bi = t ? q : bi;
+                  bk = t ? kk : bk;
                 }
-                if (theta >= 0.f && !beats(wk, theta)) ok = false;
-                // a step that needs many chunks goes to a sequential segment,
-                // which re-centres the shell
-                if (g > recentre && s_p + k - i0 > kMinShellSteps) ok = false;
+                wk = bk;
+                wi = bi;
+#pragma unroll
+                for (int st = 0; st < 2; ++st) {
+                  const float ko = st ? dpp_f<0x4E>(wk) : dpp_f<0xB1>(wk);
+                  const int io = __float_as_int(st ? dpp_f<0x4E>(__int_as_float(wi)) : dpp_f<0xB1>(__int_as_float(wi)));
+                  const bool t = better(ko, io, wk, wi);
+                  wi = t ? io : wi;
+                  wk = t ? ko : wk;
+                }
+                ++g;
+                const float rest = g < nchunks ? S.chunk_ub[g] : theta;
+                const bool open = (g < nchunks || theta >= 0.f) && !beats(wk, rest);
+                if (__ballot(open) == 0ull) break;
+                if (g >= nchunks || (g > recentre && s_p + k0 - i0 > kMinShellSteps)) {
+                  // (samples outside the shell may win, or a step needs many
+                  // chunks: a sequential segment redoes it and re-centres)
+                  ok = ok && !open;
+                  break;
+                }
               }
-              if (ok) {
-                const unsigned long long win = __ballot(bk == wk);
-                const int wi = __popcll(win) > 1 ? wave_min_i32(bk == wk ? bi : INT32_MAX)
-                                                 : __builtin_amdgcn_readlane(bi, (int)__ffsll((long long)win) - 1);
-                ok = wi == pid;
+              // the winner is the predicted one if it is among the candidates,
+              // which were compared by the same keys and rule
+              bool hit = false;
+              if (pl_two) {
+                hit = wi == pl_cand[k & 1];
+              } else {
+#pragma unroll
+                for (int c = 0; c < 8; ++c) hit = hit || wi == pl_cand[c];
               }
-              if (!ok && lane == 0) atomicMin(&pl_fail[pslot], k);
+              if (!(ok && hit) && sub == 0) atomicMin(&pl_fail[pslot], k);
+              if (sub == 0) pl_W[pslot][k] = wi;
             }
           }
           __syncthreads();
@@ -1492,7 +1663,10 @@ __device__ __forceinline__ void chain_run(const ChainShared &S, const int64_t *_
         } else {
           C = fail_C;
           i = fail_step;
-          backoff = min(2 * backoff, kPipeMaxSeq);
+          if (two)
+            ++turn_fails;
+          else
+            backoff = min(2 * backoff, kPipeMaxSeq);
           stable = 0;
         }
         // (pl_Cend and the failing slot are read before any later write:
@@ -1505,6 +1679,11 @@ __device__ __forceinline__ void chain_run(const ChainShared &S, const int64_t *_
   }
   // ------------------------------------------------------------------ centre
   if (tid == 0) {
+    if (ep) {  // (as they may have been gathered anew)
+      rec[j].dm_n[chain] = sg.n;
+      rec[j].dm_rho[chain] = sg.rho;
+      rec[j].dm_c[chain] = sg.C;
+    }
     rec[j].n_rescan[chain] = sdg.n_rescan;
     rec[j].n_global[chain] = sdg.n_global | (sg.n_built << 16);
     rec[j].n_groups[chain] = sdg.n_groups;
@@ -1559,15 +1738,57 @@ __global__ void __launch_bounds__(chain_block<V>(), V == kChainWide ? 1 : 4) k_m
                        no_prune, n_early, es, gid, gpt, gstride);
 }
 
-// float64 radii about the centre: max ||R* - R_s||_F^2 and ||t* - t_s||^2.
+// Signature of an instance's descent, stored with the checkpoints it left, so
+// that the backward uses them only for this descent: the sum of a term per
+// step of (step, winner, the bits of the winner's rotation), and one for the
+// start (the first feasible sample), which determine the iterates.  One
+// workgroup, beside those of the radii (its 4,096 gathers are all latency:
+// 17 us as a launch of its own).
+__device__ __forceinline__ void sign_descent(int64_t off, int64_t M, const float *__restrict__ poses,
+                                             const int32_t *__restrict__ tr, MegbRec &rec, int T, int ck) {
+  const int first = rec.first;
+  unsigned long long h = 0ull;
+  if (first != INT32_MAX)
+    for (int i = (int)threadIdx.x; i <= T; i += kBlock) {
+      const int id = i == 0 ? first : tr[2 * (i - 1)];
+      if (id >= 0 && id < M) {
+        uint32_t R[9];
+        const float *P = poses + 12 * (off + id);
+        for (int k = 0; k < 9; ++k) R[k] = __float_as_uint(P[k]);
+        h += step_sig_term(i, id, R);
+      } else {
+        h += trace_mix(i, id);
+      }
+    }
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) h += __shfl_xor(h, o, 64);
+  __shared__ unsigned long long part[kWaves];
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = h;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    unsigned long long t = 0ull;
+    for (int w = 0; w < kWaves; ++w) t += part[w];
+    rec.ck_hash = t;
+    rec.ck_T = first != INT32_MAX ? T : 0;
+    rec.ck_every = ck;
+  }
+}
+
+// float64 radii about the centre: max ||R* - R_s||_F^2 and ||t* - t_s||^2
+// (the first workgroup of each instance signs its descent instead).
 template <int PER>
 __global__ void __launch_bounds__(kBlock) k_megb_radii(const int64_t *__restrict__ sample_off, int64_t total,
                                                        int64_t max_m, const float *__restrict__ poses,
-                                                       const uint8_t *__restrict__ mask, MegbRec *rec) {
+                                                       const uint8_t *__restrict__ mask, MegbRec *rec,
+                                                       const int32_t *__restrict__ trace, int T, int ck) {
   const int j = blockIdx.y;
   int64_t off, M;
   sample_range(sample_off, j, total, max_m, off, M);
-  const int64_t s0 = (int64_t)blockIdx.x * (kBlock * PER) + threadIdx.x;
+  if (blockIdx.x == 0) {
+    sign_descent(off, M, poses, trace + (int64_t)j * T * 2, rec[j], T, ck);
+    return;
+  }
+  const int64_t s0 = (int64_t)(blockIdx.x - 1) * (kBlock * PER) + threadIdx.x;
   __shared__ double red[2][kWaves];
   double fr = 0.0, ft = 0.0;
   if (rec[j].first != INT32_MAX) {
@@ -1633,45 +1854,6 @@ __global__ void __launch_bounds__(kBlock) k_megb_radii(const int64_t *__restrict
   }
 }
 
-// Signature of each instance's descent, stored with the checkpoints it left,
-// so that the backward uses them only for this descent: the sum of a term
-// per step of (step, winner, the bits of the winner's rotation), and one for
-// the start (the first feasible sample), which determine the iterates.
-__global__ void __launch_bounds__(kBlock) k_megb_sign(const int64_t *__restrict__ sample_off, int64_t total,
-                                                      int64_t max_m, const float *__restrict__ poses,
-                                                      const int32_t *__restrict__ trace, MegbRec *rec, int T, int ck) {
-  const int j = blockIdx.x;
-  int64_t off, M;
-  sample_range(sample_off, j, total, max_m, off, M);
-  const int first = rec[j].first;
-  const int32_t *tr = trace + (int64_t)j * T * 2;
-  unsigned long long h = 0ull;
-  if (first != INT32_MAX)
-    for (int i = (int)threadIdx.x; i <= T; i += kBlock) {
-      const int id = i == 0 ? first : tr[2 * (i - 1)];
-      if (id >= 0 && id < M) {
-        uint32_t R[9];
-        const float *P = poses + 12 * (off + id);
-        for (int k = 0; k < 9; ++k) R[k] = __float_as_uint(P[k]);
-        h += step_sig_term(i, id, R);
-      } else {
-        h += trace_mix(i, id);
-      }
-    }
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) h += __shfl_xor(h, o, 64);
-  __shared__ unsigned long long part[kWaves];
-  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = h;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    unsigned long long t = 0ull;
-    for (int w = 0; w < kWaves; ++w) t += part[w];
-    rec[j].ck_hash = t;
-    rec[j].ck_T = first != INT32_MAX ? T : 0;
-    rec[j].ck_every = ck;
-  }
-}
-
 // ---------------------------------------------------------------------------
 // Step III of the paper ("The CLOSURE Algorithm"): the exact minimum enclosing
 // ball of the feasible samples, translations in R^3 and rotations as unit
@@ -1693,6 +1875,13 @@ __global__ void __launch_bounds__(kBlock) k_megb_sign(const int64_t *__restrict_
 // shell's minimum ball.  Every sample is then checked against it; any sample
 // outside is added to the shell and the iteration resumes, so the final ball
 // encloses all samples and is the minimum ball of a subset: the exact one.
+//
+// Where the descent left undominated samples in global memory (instances of
+// the first phase), "all samples" are those: any other one is nearer than one
+// of them to every centre in their ball, so a ball around such a centre that
+// encloses them encloses it too.  A centre outside it (checked at the end)
+// restarts the search over every sample.  (One workgroup's passes over
+// 262,144 samples took 1.36 ms, over 10,000-20,000 undominated ones 0.2 ms.)
 constexpr int kExactShell = 1024;   // staged at first
 constexpr int kExactCap = 2048;     // shell capacity including samples added by the checks
 constexpr int kExactRounds = 16;    // check-and-add rounds before giving up (the descent's centre is kept)
@@ -1776,14 +1965,17 @@ __device__ __forceinline__ bool exact_circumsphere(const double P[5][4], int k, 
 
 __global__ void __launch_bounds__(kBlock) k_megb_exact(const int64_t *__restrict__ sample_off, int64_t total,
                                                        int64_t max_m, const float4 *__restrict__ quat,
-                                                       const float4 *__restrict__ trans, MegbRec *rec) {
+                                                       const float4 *__restrict__ trans, MegbRec *rec,
+                                                       const float4 *__restrict__ gpt_all, int64_t gstride) {
   const int j = blockIdx.x >> 1, chain = blockIdx.x & 1;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int64_t off, M64;
   sample_range(sample_off, j, total, max_m, off, M64);
-  const int M = (int)M64;
   if (rec[j].first == INT32_MAX) return;  // empty instance (whole workgroup)
-  const float4 *D = (chain ? trans : quat) + off;
+  const float dm_rho = rec[j].dm_rho[chain];
+  const int dm_n = rec[j].dm_n[chain];
+  const float4 dm_c = rec[j].dm_c[chain];
+  bool pruned = dm_rho > 0.f && dm_n > 0 && dm_n <= (int)(M64 / kShellDiv);
   const int dim = chain ? 3 : 4;
   __shared__ double pts[kExactCap][4];
   __shared__ int hist[kExactBins];
@@ -1832,176 +2024,190 @@ __global__ void __launch_bounds__(kBlock) k_megb_exact(const int64_t *__restrict
       }
     __syncthreads();
   };
-  double dmax = -1.0;
-  int imax = INT32_MAX;
-  for (int s = tid; s < M; s += kBlock) {
-    if (!feasible_pt(D[s], chain)) continue;
-    double x[4];
-    exact_point(D, s, chain, ref, x);
-    const double d = exact_d2(x, ref);
-    if (d > dmax) {
-      dmax = d;
-      imax = s;
-    }
-  }
-  double r2hat;
-  int ihat;
-  block_max(dmax, imax, r2hat, ihat);
-  const double rhat = sqrt(fmax(r2hat, 0.0));
-  for (int k = tid; k < kExactBins; k += kBlock) hist[k] = 0;
-  __syncthreads();
-  // bins of the distance over [0, rhat]; the threshold keeps at most
-  // kExactShell samples (all of them when there are fewer)
-  const double binw = rhat > 0.0 ? rhat / kExactBins : 1.0;
-  for (int s = tid; s < M; s += kBlock) {
-    if (!feasible_pt(D[s], chain)) continue;
-    double x[4];
-    exact_point(D, s, chain, ref, x);
-    const int bin = min(kExactBins - 1, (int)(sqrt(exact_d2(x, ref)) / binw));
-    atomicAdd(&hist[bin], 1);
-  }
-  __syncthreads();
-  if (tid == 0) {
-    int acc = 0, b = kExactBins;
-    while (b > 0 && acc + hist[b - 1] <= kExactShell) acc += hist[--b];
-    thr_s = b == kExactBins ? rhat : b * binw;  // (a top bin over capacity: its farthest sample only)
-    n_s = 0;
-    fail_s = 0;
-  }
-  __syncthreads();
-  const double thr = thr_s;
-  for (int s = tid; s < M; s += kBlock) {
-    if (!feasible_pt(D[s], chain)) continue;
-    double x[4];
-    exact_point(D, s, chain, ref, x);
-    if (sqrt(exact_d2(x, ref)) >= thr || s == ihat) {
-      const int k = atomicAdd(&n_s, 1);
-      if (k < kExactShell)
-        for (int q = 0; q < 4; ++q) pts[k][q] = x[q];
-    }
-  }
-  __syncthreads();
-  if (tid == 0) {
-    n_s = min(n_s, kExactShell);
-    // start: the ball of the single farthest sample
-    double x[4];
-    exact_point(D, ihat, chain, ref, x);
-    for (int q = 0; q < 4; ++q) {
-      B_s[0][q] = x[q];
-      c_s[q] = x[q];
-    }
-    nb_s = 1;
-    r2_s = 0.0;
-  }
-  __syncthreads();
-  const double eps = 1e-12;
-  for (int round = 0; round < kExactRounds; ++round) {
-    // ---- support-set iteration on the shell
-    for (int step = 0; step < 4 * kExactCap; ++step) {
-      const double c[4] = {c_s[0], c_s[1], c_s[2], c_s[3]};
-      const double r2 = r2_s;
-      double bv = -1.0;
-      int bi = INT32_MAX;
-      for (int k = tid; k < n_s; k += kBlock) {
-        const double d = exact_d2(pts[k], c);
-        if (d > bv) {
-          bv = d;
-          bi = k;
-        }
+  for (;;) {
+    const float4 *D = pruned ? gpt_all + chain * gstride + off / kShellDiv : (chain ? trans : quat) + off;
+    const int M = pruned ? dm_n : (int)M64;
+    double dmax = -1.0;
+    int imax = INT32_MAX;
+    for (int s = tid; s < M; s += kBlock) {
+      if (!feasible_pt(D[s], chain)) continue;
+      double x[4];
+      exact_point(D, s, chain, ref, x);
+      const double d = exact_d2(x, ref);
+      if (d > dmax) {
+        dmax = d;
+        imax = s;
       }
-      double fv;
-      int fi;
-      block_max(bv, bi, fv, fi);
-      if (fi == INT32_MAX || fv <= r2 * (1.0 + eps) + 1e-300) break;
-      // smallest ball with p on its boundary enclosing B and p (wave 0: one
-      // subset of B per lane)
-      if (wave == 0) {
-        const int nb = nb_s;
-        double best_r2 = INFINITY, best_c[4] = {0, 0, 0, 0};
-        int best_m = -1;
-        if (lane < (1 << nb)) {
-          double P[5][4];
-          int k = 0;
-          for (int q = 0; q < 4; ++q) P[k][q] = pts[fi][q];
-          ++k;
-          for (int i = 0; i < nb; ++i)
-            if ((lane >> i) & 1) {
-              if (k < dim + 1)
-                for (int q = 0; q < 4; ++q) P[k][q] = B_s[i][q];
-              ++k;
-            }
-          double cc[4], rr2;
-          if (k <= dim + 1 && exact_circumsphere(P, k, cc, rr2)) {
-            bool encl = true;
-            for (int i = 0; i < nb; ++i) encl = encl && exact_d2(B_s[i], cc) <= rr2 * (1.0 + 1e-10) + 1e-300;
-            if (encl) {
-              best_r2 = rr2;
-              best_m = lane;
-              for (int q = 0; q < 4; ++q) best_c[q] = cc[q];
-            }
+    }
+    double r2hat;
+    int ihat;
+    block_max(dmax, imax, r2hat, ihat);
+    const double rhat = sqrt(fmax(r2hat, 0.0));
+    for (int k = tid; k < kExactBins; k += kBlock) hist[k] = 0;
+    __syncthreads();
+    // bins of the distance over [0, rhat]; the threshold keeps at most
+    // kExactShell samples (all of them when there are fewer)
+    const double binw = rhat > 0.0 ? rhat / kExactBins : 1.0;
+    for (int s = tid; s < M; s += kBlock) {
+      if (!feasible_pt(D[s], chain)) continue;
+      double x[4];
+      exact_point(D, s, chain, ref, x);
+      const int bin = min(kExactBins - 1, (int)(sqrt(exact_d2(x, ref)) / binw));
+      atomicAdd(&hist[bin], 1);
+    }
+    __syncthreads();
+    if (tid == 0) {
+      int acc = 0, b = kExactBins;
+      while (b > 0 && acc + hist[b - 1] <= kExactShell) acc += hist[--b];
+      thr_s = b == kExactBins ? rhat : b * binw;  // (a top bin over capacity: its farthest sample only)
+      n_s = 0;
+      fail_s = 0;
+    }
+    __syncthreads();
+    const double thr = thr_s;
+    for (int s = tid; s < M; s += kBlock) {
+      if (!feasible_pt(D[s], chain)) continue;
+      double x[4];
+      exact_point(D, s, chain, ref, x);
+      if (sqrt(exact_d2(x, ref)) >= thr || s == ihat) {
+        const int k = atomicAdd(&n_s, 1);
+        if (k < kExactShell)
+          for (int q = 0; q < 4; ++q) pts[k][q] = x[q];
+      }
+    }
+    __syncthreads();
+    if (tid == 0) {
+      n_s = min(n_s, kExactShell);
+      // start: the ball of the single farthest sample
+      double x[4];
+      exact_point(D, ihat, chain, ref, x);
+      for (int q = 0; q < 4; ++q) {
+        B_s[0][q] = x[q];
+        c_s[q] = x[q];
+      }
+      nb_s = 1;
+      r2_s = 0.0;
+    }
+    __syncthreads();
+    const double eps = 1e-12;
+    for (int round = 0; round < kExactRounds; ++round) {
+      // ---- support-set iteration on the shell
+      for (int step = 0; step < 4 * kExactCap; ++step) {
+        const double c[4] = {c_s[0], c_s[1], c_s[2], c_s[3]};
+        const double r2 = r2_s;
+        double bv = -1.0;
+        int bi = INT32_MAX;
+        for (int k = tid; k < n_s; k += kBlock) {
+          const double d = exact_d2(pts[k], c);
+          if (d > bv) {
+            bv = d;
+            bi = k;
           }
         }
-        // smallest radius, then the lower subset index
-        double v = -best_r2;
-        int m = best_m < 0 ? INT32_MAX : best_m;
-        for (int o = 32; o >= 1; o >>= 1) {
-          const double v2 = __shfl_xor(v, o, 64);
-          const int m2 = __shfl_xor(m, o, 64);
-          if (v2 > v || (v2 == v && m2 < m)) {
-            v = v2;
-            m = m2;
+        double fv;
+        int fi;
+        block_max(bv, bi, fv, fi);
+        if (fi == INT32_MAX || fv <= r2 * (1.0 + eps) + 1e-300) break;
+        // smallest ball with p on its boundary enclosing B and p (wave 0: one
+        // subset of B per lane)
+        if (wave == 0) {
+          const int nb = nb_s;
+          double best_r2 = INFINITY, best_c[4] = {0, 0, 0, 0};
+          int best_m = -1;
+          if (lane < (1 << nb)) {
+            double P[5][4];
+            int k = 0;
+            for (int q = 0; q < 4; ++q) P[k][q] = pts[fi][q];
+            ++k;
+            for (int i = 0; i < nb; ++i)
+              if ((lane >> i) & 1) {
+                if (k < dim + 1)
+                  for (int q = 0; q < 4; ++q) P[k][q] = B_s[i][q];
+                ++k;
+              }
+            double cc[4], rr2;
+            if (k <= dim + 1 && exact_circumsphere(P, k, cc, rr2)) {
+              bool encl = true;
+              for (int i = 0; i < nb; ++i) encl = encl && exact_d2(B_s[i], cc) <= rr2 * (1.0 + 1e-10) + 1e-300;
+              if (encl) {
+                best_r2 = rr2;
+                best_m = lane;
+                for (int q = 0; q < 4; ++q) best_c[q] = cc[q];
+              }
+            }
+          }
+          // smallest radius, then the lower subset index
+          double v = -best_r2;
+          int m = best_m < 0 ? INT32_MAX : best_m;
+          for (int o = 32; o >= 1; o >>= 1) {
+            const double v2 = __shfl_xor(v, o, 64);
+            const int m2 = __shfl_xor(m, o, 64);
+            if (v2 > v || (v2 == v && m2 < m)) {
+              v = v2;
+              m = m2;
+            }
+          }
+          if (m == INT32_MAX) {
+            if (lane == 0) fail_s = 1;
+          } else if (lane == m) {
+            double nB[5][4];
+            int k = 0;
+            for (int q = 0; q < 4; ++q) nB[k][q] = pts[fi][q];
+            ++k;
+            for (int i = 0; i < nb; ++i)
+              if ((m >> i) & 1) {
+                for (int q = 0; q < 4; ++q) nB[k][q] = B_s[i][q];
+                ++k;
+              }
+            for (int i = 0; i < k; ++i)
+              for (int q = 0; q < 4; ++q) B_s[i][q] = nB[i][q];
+            nb_s = k;
+            for (int q = 0; q < 4; ++q) c_s[q] = best_c[q];
+            r2_s = best_r2;
           }
         }
-        if (m == INT32_MAX) {
-          if (lane == 0) fail_s = 1;
-        } else if (lane == m) {
-          double nB[5][4];
-          int k = 0;
-          for (int q = 0; q < 4; ++q) nB[k][q] = pts[fi][q];
-          ++k;
-          for (int i = 0; i < nb; ++i)
-            if ((m >> i) & 1) {
-              for (int q = 0; q < 4; ++q) nB[k][q] = B_s[i][q];
-              ++k;
-            }
-          for (int i = 0; i < k; ++i)
-            for (int q = 0; q < 4; ++q) B_s[i][q] = nB[i][q];
-          nb_s = k;
-          for (int q = 0; q < 4; ++q) c_s[q] = best_c[q];
-          r2_s = best_r2;
+        __syncthreads();
+        if (fail_s) break;
+      }
+      if (fail_s) break;
+      // ---- every sample against the ball; samples outside join the shell
+      if (tid == 0) add_s = 0;
+      __syncthreads();
+      {
+        const double c[4] = {c_s[0], c_s[1], c_s[2], c_s[3]};
+        const double lim = r2_s * (1.0 + 1e-9) + 1e-300;
+        for (int s = tid; s < M; s += kBlock) {
+          if (!feasible_pt(D[s], chain)) continue;
+          double x[4];
+          exact_point(D, s, chain, ref, x);
+          if (exact_d2(x, c) > lim) {
+            const int k = atomicAdd(&add_s, 1);
+            const int slot = n_s + k;
+            if (slot < kExactCap)
+              for (int q = 0; q < 4; ++q) pts[slot][q] = x[q];
+          }
         }
       }
       __syncthreads();
-      if (fail_s) break;
-    }
-    if (fail_s) break;
-    // ---- every sample against the ball; samples outside join the shell
-    if (tid == 0) add_s = 0;
-    __syncthreads();
-    {
-      const double c[4] = {c_s[0], c_s[1], c_s[2], c_s[3]};
-      const double lim = r2_s * (1.0 + 1e-9) + 1e-300;
-      for (int s = tid; s < M; s += kBlock) {
-        if (!feasible_pt(D[s], chain)) continue;
-        double x[4];
-        exact_point(D, s, chain, ref, x);
-        if (exact_d2(x, c) > lim) {
-          const int k = atomicAdd(&add_s, 1);
-          const int slot = n_s + k;
-          if (slot < kExactCap)
-            for (int q = 0; q < 4; ++q) pts[slot][q] = x[q];
-        }
+      if (add_s == 0) break;
+      if (tid == 0) {
+        if (n_s + add_s > kExactCap) fail_s = 1;  // (the shell is full: the descent's centre is kept)
+        n_s = min(kExactCap, n_s + add_s);
       }
+      __syncthreads();
+      if (fail_s) break;
+      if (round == kExactRounds - 1 && tid == 0) fail_s = 1;
     }
     __syncthreads();
-    if (add_s == 0) break;
-    if (tid == 0) {
-      if (n_s + add_s > kExactCap) fail_s = 1;  // (the shell is full: the descent's centre is kept)
-      n_s = min(kExactCap, n_s + add_s);
-    }
-    __syncthreads();
-    if (fail_s) break;
-    if (round == kExactRounds - 1 && tid == 0) fail_s = 1;
+    if (!pruned) break;
+    // the centre lies in the undominated samples' ball (quaternions up to sign)
+    const double dc[4] = {dm_c.x, dm_c.y, dm_c.z, chain ? 0.0 : dm_c.w};
+    const double nc[4] = {-dc[0], -dc[1], -dc[2], -dc[3]}, cc[4] = {c_s[0], c_s[1], c_s[2], c_s[3]};
+    const double d2 = chain ? exact_d2(cc, dc) : fmin(exact_d2(cc, dc), exact_d2(cc, nc));
+    const bool inside = d2 <= (double)dm_rho * dm_rho * (1.0 - 1e-5);
+    __syncthreads();  // (every thread has read the centre)
+    if (!fail_s && inside) break;
+    pruned = false;
   }
   __syncthreads();
   if (tid == 0 && !fail_s) {
@@ -2052,7 +2258,8 @@ void launch_megb(const DevBatch &b, const DevParams &p, const float *poses, cons
   // atomics; one on small ones, whose passes are latency-bound)
   const bool per4 = max_samples >= kPassPerMin;
   const int per = per4 ? kPassPer : 1;
-  dim3 grid((unsigned)((max_samples + kBlock * per - 1) / (kBlock * per)), (unsigned)n);
+  const dim3 grid((unsigned)((max_samples + kBlock * per - 1) / (kBlock * per)), (unsigned)n);
+  const dim3 rgrid(grid.x + 1, grid.y);  // (and one workgroup per instance for its signature)
   if (per4)
     hipLaunchKernelGGL(k_megb_prep<kPassPer>, grid, dim3(kBlock), 0, stream, b.sample_off, total_samples,
                        max_samples, poses, mask, rec, quat, trans);
@@ -2089,17 +2296,15 @@ void launch_megb(const DevBatch &b, const DevParams &p, const float *poses, cons
     hipLaunchKernelGGL(k_megb_chain<kChainNarrow>, dim3(2 * n), dim3(chain_block<kChainNarrow>()), lds, stream,
                        b.sample_off, max_samples, quat, trans, rec, dref, total_samples, trace, ckpt, ck, p.megb_iters,
                        p.megb_avg, cap, no_prune, n_early, es, gid, gpt, gstride);
-  hipLaunchKernelGGL(k_megb_sign, dim3(n), dim3(kBlock), 0, stream, b.sample_off, total_samples, max_samples, poses,
-                     trace, rec, p.megb_iters, ck);
   if (p.flags & PURSE_FLAG_EXACT_MEB)
     hipLaunchKernelGGL(k_megb_exact, dim3(2 * n), dim3(kBlock), 0, stream, b.sample_off, total_samples, max_samples,
-                       quat, trans, rec);
+                       quat, trans, rec, gpt, gstride);
   if (per4)
-    hipLaunchKernelGGL(k_megb_radii<kPassPer>, grid, dim3(kBlock), 0, stream, b.sample_off, total_samples,
-                       max_samples, poses, mask, rec);
+    hipLaunchKernelGGL(k_megb_radii<kPassPer>, rgrid, dim3(kBlock), 0, stream, b.sample_off, total_samples,
+                       max_samples, poses, mask, rec, trace, p.megb_iters, ck);
   else
-    hipLaunchKernelGGL(k_megb_radii<1>, grid, dim3(kBlock), 0, stream, b.sample_off, total_samples, max_samples,
-                       poses, mask, rec);
+    hipLaunchKernelGGL(k_megb_radii<1>, rgrid, dim3(kBlock), 0, stream, b.sample_off, total_samples, max_samples,
+                       poses, mask, rec, trace, p.megb_iters, ck);
   hipLaunchKernelGGL(k_megb_final, dim3((n + 255) / 256), dim3(256), 0, stream, n, rec, centre, radii,
                      n_feasible, inst_status);
 }
