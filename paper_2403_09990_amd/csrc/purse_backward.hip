@@ -64,22 +64,71 @@ __device__ __forceinline__ void hat_d(const D w[3], D W[9]) {
   W[8] = 0;
 }
 
-// One descent step C_i = C Exp(Log(C^T R) / i), over float64 or its dual numbers.
-template <typename T>
-__device__ __forceinline__ void step_rot_t(const T C[9], const T R[9], int i, T Cn[9]) {
-  T Y[9];
+// (1 - cos x) / x^2 and (x - sin x) / x^3 from z = x^2: their Taylor series for
+// |x| <= 1/2 (truncation below 1e-17), else by half angles.
+__device__ __forceinline__ void exp_coeffs_bd(D z, D &B, D &Dc, D &A) {
+  if (z <= 0.25) {
+    B = 0.5 + z * (-1.0 / 24 + z * (1.0 / 720 + z * (-1.0 / 40320 + z * (1.0 / 3628800 + z * (-1.0 / 479001600 +
+        z * (1.0 / 87178291200.0))))));
+    Dc = 1.0 / 6 + z * (-1.0 / 120 + z * (1.0 / 5040 + z * (-1.0 / 362880 + z * (1.0 / 39916800 +
+         z * (-1.0 / 6227020800.0 + z * (1.0 / 1307674368000.0))))));
+    A = 1.0 - z * Dc;
+  } else {
+    const D x = sqrt(z);
+    D s, c, sh, ch;
+    sincos(x, &s, &c);
+    sincos(0.5 * x, &sh, &ch);
+    A = s / x;
+    B = 2.0 * sh * sh / z;
+    Dc = (1.0 - A) / z;
+  }
+}
+
+// (1 - (x / 2) cot(x / 2)) / x^2 from z = x^2 (coefficients |B_2k| / (2k)!).
+__device__ __forceinline__ D log_coeff(D z) {
+  if (z <= 0.25)
+    return 1.0 / 12 + z * (1.0 / 720 + z * (1.0 / 30240 + z * (1.0 / 1209600 + z * (1.0 / 47900160 +
+           z * (691.0 / 1307674368000.0 + z * (1.0 / 74724249600.0))))));
+  const D h = 0.5 * sqrt(z);
+  D s, c;
+  sincos(h, &s, &c);
+  return (1.0 - h * c / s) / z;
+}
+
+// One descent step C_i = C Exp(s phi), phi = Log(C^T R), s = 1 / i, and its
+// Jacobians in right-trivialised tangents: J_C (w.r.t. C Exp(d)) and J_R
+// (w.r.t. R Exp(e)).  With the right Jacobian J_r of Exp,
+//   J_R = s J_r(s phi) J_r(phi)^-1,
+//   J_C = Exp(-s phi) - s J_r(s phi) J_r(-phi)^-1,
+// all of them polynomials in K = [phi]x, K^3 = -|phi|^2 K.
+__device__ __forceinline__ void step_jacobians(const D C[9], const D R[9], int i, D Ci[9], D JC[9], D JR[9]) {
+  D Y[9], phi[3];
+  matmul_tn(C, R, Y);
+  log_so3<D>(Y, phi);
+  const D s = 1.0 / (D)i;
+  const D z = phi[0] * phi[0] + phi[1] * phi[1] + phi[2] * phi[2];
+  D B, Dc, A;
+  exp_coeffs_bd(s * s * z, B, Dc, A);
+  const D b = s * B, d = s * s * Dc, e = log_coeff(z);
+  // coefficients of K and K^2 in J_r(s phi) J_r(+-phi)^-1 and in Exp(-s phi)
+  const D kr = 0.5 - b - z * (0.5 * d - b * e), kr2 = e - 0.5 * b + d - z * d * e;
+  const D kc = -0.5 - b + z * (b * e + 0.5 * d), kc2 = e + 0.5 * b + d - z * d * e;
+  const D c0 = 1.0 - s, c1 = -s * A - s * kc, c2 = s * b - s * kc2;
+  const D r1 = s * kr, r2 = s * kr2, e1 = s * A, e2 = s * b;
+  D K[9], K2[9], E[9];
+  hat_d(phi, K);
 #pragma unroll
   for (int r = 0; r < 3; ++r)
 #pragma unroll
-    for (int c = 0; c < 3; ++c) Y[3 * r + c] = C[r] * R[c] + C[3 + r] * R[3 + c] + C[6 + r] * R[6 + c];
-  T w[3], phi[3], E[9];
-  log_so3<T>(Y, w);
-  const double inv = 1.0 / (double)i;
-  phi[0] = w[0] * inv;
-  phi[1] = w[1] * inv;
-  phi[2] = w[2] * inv;
-  exp_so3<T>(phi, E);
-  matmul3<T>(C, E, Cn);
+    for (int c = 0; c < 3; ++c) K2[3 * r + c] = phi[r] * phi[c] - (r == c ? z : 0.0);
+#pragma unroll
+  for (int k = 0; k < 9; ++k) {
+    const bool dg = k % 4 == 0;
+    JC[k] = (dg ? c0 : 0.0) + c1 * K[k] + c2 * K2[k];
+    JR[k] = (dg ? s : 0.0) + r1 * K[k] + r2 * K2[k];
+    E[k] = (dg ? 1.0 : 0.0) + e1 * K[k] + e2 * K2[k];
+  }
+  matmul3<D>(C, E, Ci);
 }
 
 // Rotation matrix of a (renormalised) float quaternion (w, x, y, z), in float64.
@@ -123,7 +172,7 @@ __global__ void __launch_bounds__(kBwdBlock) k_bwd_megb(DevBatch b, DevParams p,
   __shared__ float pact[kMaxActive][12];       // poses of the active samples
   __shared__ float4 qact[kMaxActive];          // their rotations as quaternions
   __shared__ uint8_t tslot[2 * kLdsTrace];     // trace as active-set slots
-  __shared__ double jac[kBwdBlock][2][9];      // J_C, J_R of the steps of one chunk
+  __shared__ double jac[kBwdBlock][9];         // J_C of the steps of one chunk
   __shared__ double jadd[kBwdBlock][3];        // averaged-iterate terms of those steps, then rho terms
   __shared__ double gstep[kBwdBlock][3];       // g at each step of the chunk
   __shared__ int cslot[kBwdBlock];             // active slot of each step of the chunk (rotation)
@@ -500,10 +549,9 @@ __global__ void __launch_bounds__(kBwdBlock) k_bwd_megb(DevBatch b, DevParams p,
   // Rotation chain.  Thread 0 turns the cotangents of R* and the rotation
   // radius into S_bar = dL/dS (S = sum of the last iterates).  Then the T
   // steps are swept backwards in chunks of kBwdBlock: every thread takes one
-  // step i of the chunk, recomputes C_{i-1} from its checkpoint and, in dual
-  // numbers, the 3x3 Jacobians of C_i = C_{i-1} Exp(Log(C_{i-1}^T R) / i) in
-  // right-trivialised tangents, J_C (w.r.t. C_{i-1} Exp(d)) and J_R (w.r.t.
-  // R Exp(e)); thread 0 then runs the chunk's recurrence
+  // step i of the chunk, recomputes C_{i-1} from its checkpoint and forms the
+  // 3x3 Jacobians J_C and J_R of C_i = C_{i-1} Exp(Log(C_{i-1}^T R) / i)
+  // (step_jacobians); the chunk's recurrence
   //   g_i += vskew(C_i^T S_bar) (i among the averaged iterates),
   //   rho_{s_i} += J_R^T g_i,  g_{i-1} = J_C^T g_i,
   // so the serial part is 3x3 products only.  g_0 belongs to the first
@@ -600,6 +648,7 @@ __global__ void __launch_bounds__(kBwdBlock) k_bwd_megb(DevBatch b, DevParams p,
     for (int i_hi = T; i_hi >= 1; i_hi -= kBwdBlock) {
       const int i_lo = max(1, i_hi - kBwdBlock + 1);
       const int i = i_lo + tid;
+      D JR[9] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
       if (i <= i_hi) {
         // C_{i-1}: the forward's float32 steps from the checkpoint C_{q ck}, q = (i - 1) / ck
         const int q = (i - 1) / ck;
@@ -609,8 +658,8 @@ __global__ void __launch_bounds__(kBwdBlock) k_bwd_megb(DevBatch b, DevParams p,
         rot_of_quat_d(Cf, C);
         D R[9];
         load_act(slot_of(2 * (i - 1)), R);
-        D Ci[9];
-        step_rot_t<D>(C, R, i, Ci);
+        D Ci[9], JC[9];
+        step_jacobians(C, R, i, Ci, JC, JR);
         // ambient term of the averaged iterates
         D a[3] = {0.0, 0.0, 0.0};
         if (i > T - avg) {
@@ -619,35 +668,7 @@ __global__ void __launch_bounds__(kBwdBlock) k_bwd_megb(DevBatch b, DevParams p,
           matmul_tn(Ci, Sb, X);
           vskew(X, a);
         }
-        // Jacobian columns from right perturbations of C_{i-1} and of R
-        for (int which = 0; which < 2; ++which)
-          for (int c = 0; c < 3; ++c) {
-            Dual<D> Cd[9], Rd[9], Cnd[9];
-            for (int k = 0; k < 9; ++k) {
-              Cd[k] = Dual<D>(C[k], 0.0);
-              Rd[k] = Dual<D>(R[k], 0.0);
-            }
-            // X [e_c]x: column c2 of X [e]x is X (e x e_c2)
-            Dual<D> *X = which == 0 ? Cd : Rd;
-            const D *Xv = which == 0 ? C : R;
-            for (int r = 0; r < 3; ++r) {
-              const D x0 = Xv[3 * r], x1 = Xv[3 * r + 1], x2 = Xv[3 * r + 2];
-              // [e_c]x columns: e_c x e_0, e_c x e_1, e_c x e_2
-              D d0 = 0, d1 = 0, d2 = 0;
-              if (c == 0) { d1 = x2; d2 = -x1; }
-              if (c == 1) { d0 = -x2; d2 = x0; }
-              if (c == 2) { d0 = x1; d1 = -x0; }
-              X[3 * r].d = d0;
-              X[3 * r + 1].d = d1;
-              X[3 * r + 2].d = d2;
-            }
-            step_rot_t<Dual<D>>(Cd, Rd, i, Cnd);
-            D dC[9], Y[9], v[3];
-            for (int k = 0; k < 9; ++k) dC[k] = Cnd[k].d;
-            matmul_tn(Ci, dC, Y);
-            vskew(Y, v);
-            for (int r = 0; r < 3; ++r) jac[tid][which][3 * r + c] = 0.5 * v[r];
-          }
+        for (int k = 0; k < 9; ++k) jac[tid][k] = JC[k];
         for (int k = 0; k < 3; ++k) jadd[tid][k] = a[k];
       }
       __syncthreads();
@@ -662,21 +683,21 @@ __global__ void __launch_bounds__(kBwdBlock) k_bwd_megb(DevBatch b, DevParams p,
         D M[9], bv[3], at[3];
         if (tid < n) {
           for (int r = 0; r < 3; ++r)
-            for (int c = 0; c < 3; ++c) M[3 * r + c] = jac[tid][0][3 * c + r];  // J_C^T
+            for (int c = 0; c < 3; ++c) M[3 * r + c] = jac[tid][3 * c + r];  // J_C^T
           for (int k = 0; k < 3; ++k) at[k] = jadd[tid][k];
           for (int r = 0; r < 3; ++r) bv[r] = M[3 * r] * at[0] + M[3 * r + 1] * at[1] + M[3 * r + 2] * at[2];
         }
         for (int d = 1; d < n; d <<= 1) {
           __syncthreads();
           if (tid < n) {
-            for (int k = 0; k < 9; ++k) jac[tid][0][k] = M[k];
+            for (int k = 0; k < 9; ++k) jac[tid][k] = M[k];
             for (int k = 0; k < 3; ++k) gstep[tid][k] = bv[k];
           }
           __syncthreads();
           if (tid + d < n) {
             // S_t o S_{t+d}: S_{t+d} (the steps above) first
             D M2[9], b2[3], Mn[9];
-            for (int k = 0; k < 9; ++k) M2[k] = jac[tid + d][0][k];
+            for (int k = 0; k < 9; ++k) M2[k] = jac[tid + d][k];
             for (int k = 0; k < 3; ++k) b2[k] = gstep[tid + d][k];
             for (int r = 0; r < 3; ++r) {
               for (int c = 0; c < 3; ++c) Mn[3 * r + c] = M[3 * r] * M2[c] + M[3 * r + 1] * M2[3 + c] + M[3 * r + 2] * M2[6 + c];
@@ -687,14 +708,14 @@ __global__ void __launch_bounds__(kBwdBlock) k_bwd_megb(DevBatch b, DevParams p,
         }
         __syncthreads();
         if (tid < n) {
-          for (int k = 0; k < 9; ++k) jac[tid][0][k] = M[k];
+          for (int k = 0; k < 9; ++k) jac[tid][k] = M[k];
           for (int k = 0; k < 3; ++k) gstep[tid][k] = bv[k];
         }
         __syncthreads();
         const D g0[3] = {gvec[0], gvec[1], gvec[2]};
         D gb[3] = {g0[0], g0[1], g0[2]}, gout[3];
         if (tid + 1 < n) {
-          const D *Mu = jac[tid + 1][0];
+          const D *Mu = jac[tid + 1];
           const D *bu = gstep[tid + 1];
           for (int r = 0; r < 3; ++r) gb[r] = Mu[3 * r] * g0[0] + Mu[3 * r + 1] * g0[1] + Mu[3 * r + 2] * g0[2] + bu[r];
         }
@@ -711,7 +732,6 @@ __global__ void __launch_bounds__(kBwdBlock) k_bwd_megb(DevBatch b, DevParams p,
       // active sample in step order (deterministic; every term read by every
       // summing thread, selected by its slot)
       if (i <= i_hi) {
-        const D *JR = jac[tid][1];
         for (int c = 0; c < 3; ++c) jadd[tid][c] = JR[c] * gstep[tid][0] + JR[3 + c] * gstep[tid][1] + JR[6 + c] * gstep[tid][2];
         cslot[tid] = slot_of(2 * (i - 1));
         D h = hsum;
@@ -873,8 +893,48 @@ struct ObsDual {
   }
 };
 
-// Tangent of the centre, pivot and anchor along one input direction.
-// (It reads nothing k_bwd_megb writes, so the two run concurrently.)
+// Gradient terms g of one keypoint of the 2D-3D centre fit about the pivot:
+// sum over the two whitened residuals rt_k of rt_k (pt x d_k, d_k) (the
+// right side of the Gauss-Newton step; zero in sum at the fit).
+template <typename T>
+__device__ __forceinline__ void centre_grad(const T P[3], const T pt[3], const T z[2], const T w[3],
+                                            const float K[4], T g[6]) {
+  const double fx = K[0], fy = K[1], cx = K[2], cy = K[3];
+  const T iz = drcp(P[2]);
+  const T nx = P[0] * iz, ny = P[1] * iz;
+  const T r0 = z[0] - (T(fx) * nx + T(cx)), r1 = z[1] - (T(fy) * ny + T(cy));
+  const T q0 = w[0] * r0 + w[1] * r1, q1 = w[2] * r1;
+  // sum_k rt_k d_k = (c0 fx iz, c1 fy iz, -(c0 fx nx + c1 fy ny) iz)
+  const T c0 = w[0] * q0 * T(fx) * iz, c1 = (w[1] * q0 + w[2] * q1) * T(fy) * iz;
+  const T s[3] = {c0, c1, -(c0 * nx + c1 * ny)};
+  cross3(pt, s, g);
+  g[3] = s[0];
+  g[4] = s[1];
+  g[5] = s[2];
+}
+
+// The centre fit in dual numbers from its start, along one input direction
+// (2D-3D): for fits that were stopped before they converged.
+__device__ void centre_fit_dual(const float *a, const float *cz, const float *L, int n, const float K[4], int steps,
+                                double z_min, const double R0[9], const double t0[3], int i_d, int c, Dual<double> R[9],
+                                Dual<double> t[3]) {
+  for (int k = 0; k < 9; ++k) R[k] = Dual<double>(R0[k], 0.0);
+  for (int k = 0; k < 3; ++k) t[k] = Dual<double>(t0[k], 0.0);
+  const ObsDual od{cz, L, i_d, c};
+  gn_centre_2d<Dual<double>>(a, od, n, K, steps, z_min, R, t);
+}
+
+// Tangents of the centre, pivot and anchor along every input direction of an
+// instance.  (It reads nothing k_bwd_megb writes, so the two run
+// concurrently.)  The centre is a stationary point, so its tangent is that of
+// the equation it solves: wavefront 0 takes the forward's centre to float64
+// convergence (from its float32 value, two or three steps) and forms the
+// equation's 6x6 (2D-3D) or 3x3 (3D-3D) derivative once; a direction then
+// takes the terms of its own keypoint and one solve.  (Re-running the fit in
+// dual numbers from its start for each of up to 384 directions took 2.3 ms
+// on the 512-instance batch and 0.28 ms for one instance of 12 keypoints.)
+// A 2D-3D fit that the forward stopped before it converged (a small cap) is
+// still re-run.
 __global__ void __launch_bounds__(kMaxDirs) k_bwd_frame(DevBatch b, DevParams p, const InstRec *__restrict__ inst,
                                                        const KpRec *__restrict__ kprec, float *tan_all,
                                                        int max_dirs) {
@@ -890,15 +950,116 @@ __global__ void __launch_bounds__(kMaxDirs) k_bwd_frame(DevBatch b, DevParams p,
   const float *a = b.model_pts + 3 * I.kp_off;
   const float *cz = b.centres + 3 * I.kp_off;
   const float *L = b.shapes + 4 * I.kp_off;
-  // 2D-3D: the forward's choice between the two starts, made once for all
-  // directions: wavefront 0 fits from the DLT start, wavefront 1 from the
-  // weak-perspective start (whitening factors cached), as the prologue does
   __shared__ double w_s[3 * PURSE_MAX_KP];
+  __shared__ double R_s[9], t_s[3], ab_s[3];  // centre, model centroid
+  __shared__ double L_s[21], dinv_s[6];       // 2D-3D: Cholesky factor of -dg/dx; 3D-3D: (tr(S) I - S)^-1
   __shared__ double st_R[2][9], st_t[2][3], st_cost[2];
-  __shared__ int st_ok[2];
-  if (is2d) {
-    for (int i = d; i < n; i += blockDim.x) whiten_factor<double>(L + 4 * i, w_s + 3 * i);
-    __syncthreads();
+  __shared__ int st_ok[2], rerun_s;
+  if (d < 64) {
+    const bool mine = d < n;
+    const int i = mine ? d : 0;
+    double m[3] = {a[3 * i], a[3 * i + 1], a[3 * i + 2]}, ab[3];
+    for (int r = 0; r < 3; ++r) ab[r] = mine ? m[r] : 0.0;
+    for (int o = 32; o >= 1; o >>= 1)
+      for (int r = 0; r < 3; ++r) ab[r] += __shfl_xor(ab[r], o, 64);
+    for (int r = 0; r < 3; ++r) ab[r] /= n;
+    double R[9], t[3];
+    for (int k = 0; k < 9; ++k) R[k] = I.Rc[k];
+    for (int k = 0; k < 3; ++k) t[k] = I.tc[k];
+    reorthonormalise(R);
+    reorthonormalise(R);
+    bool ok;
+    if (is2d) {
+      if (mine) whiten_factor<double>(L + 4 * i, w_s + 3 * i);
+      __builtin_amdgcn_wave_barrier();
+      const ObsCached obs{cz, w_s};
+      ok = gn_centre_2d_wave(a, obs, n, I.K, p.centre_gn, (double)p.z_min, R, t);
+      // the forward had converged: its centre is this one to float32 rounding
+      double off = 0.0, tm = 0.0;
+      for (int k = 0; k < 9; ++k) off = fmax(off, fabs(R[k] - (double)I.Rc[k]));
+      for (int k = 0; k < 3; ++k) tm = fmax(tm, fabs(t[k]));
+      for (int k = 0; k < 3; ++k) off = fmax(off, fabs(t[k] - (double)I.tc[k]) / (1.0 + tm));
+      ok = ok && off <= 1e-6;
+      double P[3], pt[3], zz[2], w[3];
+      obs(i, zz, w);
+      double o[3];
+      matvec3(R, ab, o);
+      matvec3(R, m, P);
+      for (int r = 0; r < 3; ++r) o[r] += t[r];
+      for (int r = 0; r < 3; ++r) P[r] += t[r];
+      for (int r = 0; r < 3; ++r) pt[r] = P[r] - o[r];
+      double A[21], Lf[21], dinv[6];
+#pragma unroll
+      for (int e = 0; e < 6; ++e) {
+        // P moves by w x pt (rotation e < 3) or by e_(e - 3)
+        Dual<double> Pd[3], ptd[3], zd[2], wd[3], g[6];
+        double v[3] = {0.0, 0.0, 0.0};
+        if (e < 3) {
+          const double ax[3] = {e == 0 ? 1.0 : 0.0, e == 1 ? 1.0 : 0.0, e == 2 ? 1.0 : 0.0};
+          cross3(ax, pt, v);
+        } else {
+          v[e - 3] = 1.0;
+        }
+        for (int r = 0; r < 3; ++r) {
+          Pd[r] = Dual<double>(P[r], v[r]);
+          ptd[r] = Dual<double>(pt[r], v[r]);
+          wd[r] = Dual<double>(w[r], 0.0);
+        }
+        for (int r = 0; r < 2; ++r) zd[r] = Dual<double>(zz[r], 0.0);
+        centre_grad<Dual<double>>(Pd, ptd, zd, wd, I.K, g);
+#pragma unroll
+        for (int k = e; k < 6; ++k) {
+          double x = mine ? -g[k].d : 0.0;
+          for (int q = 32; q >= 1; q >>= 1) x += __shfl_xor(x, q, 64);
+          A[tri(k, e)] = x;
+        }
+      }
+      ok = ok && chol6_factor<double>(A, Lf, dinv);
+      if (d == 0 && ok) {
+        for (int k = 0; k < 21; ++k) L_s[k] = Lf[k];
+        for (int k = 0; k < 6; ++k) dinv_s[k] = dinv[k];
+      }
+    } else {
+      // R maximises tr(R^T H): Newton steps from the forward's
+      double bb[3], H[9];
+      const double bi[3] = {cz[3 * i], cz[3 * i + 1], cz[3 * i + 2]};
+      for (int r = 0; r < 3; ++r) bb[r] = mine ? bi[r] : 0.0;
+      for (int o = 32; o >= 1; o >>= 1)
+        for (int r = 0; r < 3; ++r) bb[r] += __shfl_xor(bb[r], o, 64);
+      for (int r = 0; r < 3; ++r) bb[r] /= n;
+      for (int r = 0; r < 3; ++r)
+        for (int q = 0; q < 3; ++q) H[3 * r + q] = mine ? (bi[r] - bb[r]) * (m[q] - ab[q]) : 0.0;
+      for (int o = 32; o >= 1; o >>= 1)
+        for (int k = 0; k < 9; ++k) H[k] += __shfl_xor(H[k], o, 64);
+      for (int it = 0; it < 3; ++it) polar_newton<double>(H, R);
+      double S[9];
+      matmul_tn(R, H, S);
+      const double tr = S[0] + S[4] + S[8];
+      const double h00 = tr - S[0], h11 = tr - S[4], h22 = tr - S[8];
+      const double h01 = -0.5 * (S[1] + S[3]), h02 = -0.5 * (S[2] + S[6]), h12 = -0.5 * (S[5] + S[7]);
+      const double a00 = h11 * h22 - h12 * h12, a01 = h02 * h12 - h01 * h22, a02 = h01 * h12 - h02 * h11;
+      const double a11 = h00 * h22 - h02 * h02, a12 = h01 * h02 - h00 * h12, a22 = h00 * h11 - h01 * h01;
+      const double id = 1.0 / (h00 * a00 + h01 * a01 + h02 * a02);
+      if (d == 0) {
+        const double inv[9] = {a00, a01, a02, a01, a11, a12, a02, a12, a22};
+        for (int k = 0; k < 9; ++k) L_s[k] = inv[k] * id;
+      }
+      ok = true;
+    }
+    if (d == 0) {
+      for (int k = 0; k < 9; ++k) R_s[k] = R[k];
+      for (int k = 0; k < 3; ++k) {
+        t_s[k] = t[k];
+        ab_s[k] = ab[k];
+      }
+      rerun_s = ok ? 0 : 1;
+    }
+  }
+  __syncthreads();
+  const bool rerun = rerun_s != 0;
+  if (rerun) {
+    // the forward's choice between the two starts: wavefront 0 fits from the
+    // DLT start, wavefront 1 from the weak-perspective start
     if (d == 0 || d == 64) {
       const int f = d >> 6;
       const ObsCached obs{cz, w_s};
@@ -917,36 +1078,49 @@ __global__ void __launch_bounds__(kMaxDirs) k_bwd_frame(DevBatch b, DevParams p,
   if (d >= n * dpk) return;
   const int i_d = d / dpk, c = d % dpk;
   Dual<double> Rd[9], td[3];
-  if (!is2d) {
-    // Arun's fit with b_{i_d} perturbed
-    double ab[3] = {0, 0, 0};
-    Dual<double> bb[3] = {0.0, 0.0, 0.0};
-    for (int i = 0; i < n; ++i)
-      for (int r = 0; r < 3; ++r) {
-        ab[r] += a[3 * i + r];
-        bb[r] += Dual<double>((double)cz[3 * i + r], (i == i_d && r == c) ? 1.0 : 0.0);
-      }
-    for (int r = 0; r < 3; ++r) {
-      ab[r] /= n;
-      bb[r] = bb[r] / (double)n;
-    }
-    Dual<double> H[9];
-    for (int k = 0; k < 9; ++k) H[k] = Dual<double>(0.0, 0.0);
-    for (int i = 0; i < n; ++i)
-      for (int r = 0; r < 3; ++r) {
-        Dual<double> br = Dual<double>((double)cz[3 * i + r], (i == i_d && r == c) ? 1.0 : 0.0) - bb[r];
-        for (int q = 0; q < 3; ++q) H[3 * r + q] += br * ((double)a[3 * i + q] - ab[q]);
-      }
-    polar_so3<Dual<double>>(H, Rd, 12);
-    for (int r = 0; r < 3; ++r) td[r] = bb[r] - (Rd[3 * r] * ab[0] + Rd[3 * r + 1] * ab[1] + Rd[3 * r + 2] * ab[2]);
-  } else {
+  if (rerun) {
     // from the start whose fit the forward kept (lower cost; ties: the DLT one)
     const bool ok1 = st_ok[0] != 0, ok2 = st_ok[1] != 0;
     const int f = (ok2 && (!ok1 || st_cost[1] < st_cost[0])) ? 1 : 0;
-    for (int k = 0; k < 9; ++k) Rd[k] = Dual<double>(st_R[f][k], 0.0);
-    for (int k = 0; k < 3; ++k) td[k] = Dual<double>(st_t[f][k], 0.0);
-    const ObsDual od{cz, L, i_d, c};
-    gn_centre_2d<Dual<double>>(a, od, n, I.K, p.centre_gn, (double)p.z_min, Rd, td);
+    centre_fit_dual(a, cz, L, n, I.K, p.centre_gn, (double)p.z_min, st_R[f], st_t[f], i_d, c, Rd, td);
+  } else {
+    double dR[9], dt[3];
+    const double m[3] = {a[3 * i_d], a[3 * i_d + 1], a[3 * i_d + 2]};
+    if (is2d) {
+      double P[3], o[3], Wh[9], y[6];
+      matvec3(R_s, m, P);
+      matvec3(R_s, ab_s, o);
+      Dual<double> Pd[3], ptd[3], zd[2], wd[3], g[6];
+      for (int r = 0; r < 3; ++r) {
+        o[r] += t_s[r];
+        Pd[r] = Dual<double>(P[r] + t_s[r], 0.0);
+        ptd[r] = Dual<double>(P[r] + t_s[r] - o[r], 0.0);
+      }
+      ObsDual{cz, L, i_d, c}(i_d, zd, wd);
+      centre_grad<Dual<double>>(Pd, ptd, zd, wd, I.K, g);
+      double gd[6];
+      for (int k = 0; k < 6; ++k) gd[k] = g[k].d;
+      chol6_subst<double>(L_s, dinv_s, gd, y);
+      hat_d(y, Wh);
+      matmul3<double>(Wh, R_s, dR);
+      const double arm[3] = {t_s[0] - o[0], t_s[1] - o[1], t_s[2] - o[2]};
+      cross3(y, arm, dt);
+      for (int r = 0; r < 3; ++r) dt[r] += y[3 + r];
+    } else {
+      // dH = e_c (a_i - abar)^T for c < 3 (the bound moves nothing):
+      // R^T dH - dH^T R = [u]x, dR = R [y]x, (tr(S) I - S) y = u
+      double X[9], u[3], y[3], Yh[9], v[3];
+      for (int r = 0; r < 3; ++r)
+        for (int q = 0; q < 3; ++q) X[3 * r + q] = c < 3 ? R_s[3 * c + r] * (m[q] - ab_s[q]) : 0.0;
+      vskew(X, u);
+      matvec3(L_s, u, y);
+      hat_d(y, Yh);
+      matmul3<double>(R_s, Yh, dR);
+      matvec3(dR, ab_s, v);
+      for (int r = 0; r < 3; ++r) dt[r] = (r == c ? 1.0 / n : 0.0) - v[r];
+    }
+    for (int k = 0; k < 9; ++k) Rd[k] = Dual<double>(R_s[k], dR[k]);
+    for (int k = 0; k < 3; ++k) td[k] = Dual<double>(t_s[k], dt[k]);
   }
   FrameT<Dual<float>> F;
   for (int k = 0; k < 9; ++k) F.Rc[k] = Dual<float>(I.Rc[k], (float)Rd[k].d);
