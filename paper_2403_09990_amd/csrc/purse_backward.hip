@@ -11,7 +11,8 @@
 //    chunk of steps at a time, each step's iterate recomputed from its
 //    checkpoint, and their products composed by a log-depth scan.
 // 2. k_bwd_frame: per input direction, the tangent of the centre fit, pivot
-//    and anchor (the fit re-run in float64 dual numbers from its start).
+//    and anchor (of a converged fit by implicit differentiation of its normal
+//    equations; else the fit re-run in float64 dual numbers from its start).
 // 3. k_bwd_traj: per (active sample, input direction), the trajectory re-run
 //    in float32 dual numbers gives the tangent of the sample's pose, dotted
 //    with its cotangent.
@@ -1516,6 +1517,127 @@ __host__ __device__ constexpr size_t rev_lds(int passes, int iters) {
          (size_t)kRevSamples * kRevGroup * (size_t)(iters > 0 ? iters : 1);
 }
 
+// Reciprocal and reciprocal square root of the sweeps' recomputation: in
+// float64 the hardware approximation (2^-26 or better) and two Newton steps, a
+// few units in the last place and a third of the instructions of the
+// correctly rounded forms (arguments are depths, squared radii and pivots, far
+// from the ends of the range).
+__device__ __forceinline__ float rev_rcp(float x) { return drcp(x); }
+__device__ __forceinline__ float rev_rsq(float x) { return drsqrt(x); }
+__device__ __forceinline__ double rev_rcp(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  r = fma(fma(-x, r, 1.0), r, r);
+  return fma(fma(-x, r, 1.0), r, r);
+}
+__device__ __forceinline__ double rev_rsq(double x) {
+  double r = __builtin_amdgcn_rsq(x);
+  r = fma(0.5 * fma(-x * r, r, 1.0), r, r);
+  return fma(0.5 * fma(-x * r, r, 1.0), r, r);
+}
+
+// Exp of so(3) in float64: the Taylor series of its coefficients for angles up
+// to 1/2 (no square root or trigonometric call), else the general form.
+__device__ __forceinline__ void rev_exp_so3(const double w[3], double E[9]) {
+  const double z = w[0] * w[0] + w[1] * w[1] + w[2] * w[2];
+  if (z <= 0.25) {
+    double B, Dc, A;
+    exp_coeffs_bd(z, B, Dc, A);
+    const double C = 1.0 - z * B;
+    const double b0 = B * w[0], b1 = B * w[1], a0 = A * w[0], a1 = A * w[1], a2 = A * w[2];
+    E[0] = C + b0 * w[0];
+    E[4] = C + b1 * w[1];
+    E[8] = C + B * w[2] * w[2];
+    E[1] = b0 * w[1] - a2;
+    E[3] = b0 * w[1] + a2;
+    E[2] = b0 * w[2] + a1;
+    E[6] = b0 * w[2] - a1;
+    E[5] = b1 * w[2] - a0;
+    E[7] = b1 * w[2] + a0;
+  } else {
+    exp_so3<double>(w, E);
+  }
+}
+
+// The Gauss-Newton solve and update of the recomputation, in float64: false
+// (and the pose as it was) when a pivot is not positive.
+__device__ __forceinline__ bool rev_step(const double A[21], const double g[6], const double o[3], double R[9],
+                                         double t[3]) {
+  double L[21], dinv[6], d[6];
+  bool ok = true;
+#pragma unroll
+  for (int j = 0; j < 6; ++j) {
+    double v = A[tri(j, j)];
+#pragma unroll
+    for (int k = 0; k < j; ++k) v -= L[tri(j, k)] * L[tri(j, k)];
+    ok = ok && v > 0.0;
+    dinv[j] = rev_rsq(v);
+#pragma unroll
+    for (int i = j + 1; i < 6; ++i) {
+      double x = A[tri(i, j)];
+#pragma unroll
+      for (int k = 0; k < j; ++k) x -= L[tri(i, k)] * L[tri(j, k)];
+      L[tri(i, j)] = x * dinv[j];
+    }
+  }
+  if (!ok) return false;
+  chol6_subst<double>(L, dinv, g, d);  // (it reads no diagonal entry of L)
+  double E[9], Rn[9], arm[3], e[3];
+  rev_exp_so3(d, E);
+  matmul3(E, R, Rn);
+#pragma unroll
+  for (int r = 0; r < 3; ++r) arm[r] = t[r] - o[r];
+  matvec3(E, arm, e);
+#pragma unroll
+  for (int r = 0; r < 3; ++r) t[r] = e[r] + o[r] + d[3 + r];
+#pragma unroll
+  for (int k = 0; k < 9; ++k) R[k] = Rn[k];
+  return true;
+}
+
+// R <- proj_SO3(M) in float64 from the previous iteration's rotation in R, by
+// Newton steps of max tr(R^T M) (polar_newton's): near the maximum their
+// error squares, so a last step below 1e-8 leaves rounding.  When they leave
+// the maximum's neighbourhood, the Jacobi iteration.  (Ten Jacobi sweeps were
+// three quarters of the 3D-3D recomputation.)
+__device__ __forceinline__ void rev_polar(const double M[9], double R[9]) {
+  double X[9];
+#pragma unroll
+  for (int k = 0; k < 9; ++k) X[k] = R[k];
+  bool done = false;
+  for (int it = 0; it < 8; ++it) {
+    double Y[9];
+    matmul_tn(X, M, Y);
+    const double g[3] = {Y[7] - Y[5], Y[2] - Y[6], Y[3] - Y[1]};
+    const double tr = Y[0] + Y[4] + Y[8];
+    const double h00 = tr - Y[0], h11 = tr - Y[4], h22 = tr - Y[8];
+    const double h01 = -0.5 * (Y[1] + Y[3]), h02 = -0.5 * (Y[2] + Y[6]), h12 = -0.5 * (Y[5] + Y[7]);
+    const double a00 = h11 * h22 - h12 * h12, a01 = h02 * h12 - h01 * h22, a02 = h01 * h12 - h02 * h11;
+    const double a11 = h00 * h22 - h02 * h02, a12 = h01 * h02 - h00 * h12, a22 = h00 * h11 - h01 * h01;
+    const double det = h00 * a00 + h01 * a01 + h02 * a02;
+    // positive definite (leading minors), and not nearly singular
+    if (!(h00 > 0.0 && a22 > 0.0 && det > 1e-9 * tr * tr * tr)) break;
+    const double id = rev_rcp(det);
+    const double w[3] = {(a00 * g[0] + a01 * g[1] + a02 * g[2]) * id, (a01 * g[0] + a11 * g[1] + a12 * g[2]) * id,
+                         (a02 * g[0] + a12 * g[1] + a22 * g[2]) * id};
+    double E[9], Xn[9];
+    rev_exp_so3(w, E);
+    matmul3(X, E, Xn);
+#pragma unroll
+    for (int k = 0; k < 9; ++k) X[k] = Xn[k];
+    if (fmax(fabs(w[0]), fmax(fabs(w[1]), fabs(w[2]))) < 1e-8) {
+      done = true;
+      break;
+    }
+  }
+  if (done) {
+    reorthonormalise(X);
+#pragma unroll
+    for (int k = 0; k < 9; ++k) R[k] = X[k];
+  } else {
+    polar_so3<double>(M, R, 10);
+  }
+}
+
 template <typename T>
 struct RevPoseT {
   T R[9], t[3];
@@ -1528,6 +1650,17 @@ __device__ __forceinline__ void rev_round(const RevPoseT<T> &x, RevPose &y) {
   for (int m = 0; m < 9; ++m) y.R[m] = (float)x.R[m];
 #pragma unroll
   for (int m = 0; m < 3; ++m) y.t[m] = (float)x.t[m];
+}
+
+template <typename T>
+__device__ __forceinline__ void rev_project2d(const T R[9], const T t[3], const KpRec &k, const float K[4], T P[3],
+                                              T &iz, T &u, T &v) {
+#pragma unroll
+  for (int r = 0; r < 3; ++r)
+    P[r] = R[3 * r] * T(k.m[0]) + R[3 * r + 1] * T(k.m[1]) + R[3 * r + 2] * T(k.m[2]) + t[r];
+  iz = rev_rcp(P[2]);
+  u = T(K[0]) * (P[0] * iz) + T(K[2]);
+  v = T(K[1]) * (P[1] * iz) + T(K[3]);
 }
 
 // Group-summed normal equations of one pass at x (targets from xk for the
@@ -1549,7 +1682,7 @@ __device__ __forceinline__ bool rev_normal_eqs(const KpRec *__restrict__ kp, int
     const KpRec k = kp[i];
     const T w[3] = {T(k.w[0]), T(k.w[1]), T(k.w[2])};
     T P[3], iz, u, v;
-    project2d(x.R, x.t, k, K, P, iz, u, v);
+    rev_project2d(x.R, x.t, k, K, P, iz, u, v);
     ok = ok && (P[2] > T(z_min));
     T rt0, rt1;
     if (FIRST) {
@@ -1557,17 +1690,17 @@ __device__ __forceinline__ bool rev_normal_eqs(const KpRec *__restrict__ kp, int
       const T et0 = w[0] * e0 + w[1] * e1, et1 = w[2] * e1;
       const T r2 = et0 * et0 + et1 * et1;
       if (!use_cl && !(r2 <= T(k.kb2) * T(band))) cl |= 1u << rr;
-      const T s = ((cl >> rr) & 1u) ? T(k.kb) * drsqrt(r2) : T(1);
+      const T s = ((cl >> rr) & 1u) ? T(k.kb) * rev_rsq(r2) : T(1);
       rt0 = (s - T(1)) * et0;
       rt1 = (s - T(1)) * et1;
     } else {
       T Pk[3], izk, uk, vk;
-      project2d(xk.R, xk.t, k, K, Pk, izk, uk, vk);
+      rev_project2d(xk.R, xk.t, k, K, Pk, izk, uk, vk);
       const T e0 = uk - T(k.c[0]), e1 = vk - T(k.c[1]);
       const T et0 = w[0] * e0 + w[1] * e1, et1 = w[2] * e1;
       const T r2 = et0 * et0 + et1 * et1;
       if (!use_cl && !(r2 <= T(k.kb2) * T(band))) cl |= 1u << rr;
-      const T s = ((cl >> rr) & 1u) ? T(k.kb) * drsqrt(r2) : T(1);
+      const T s = ((cl >> rr) & 1u) ? T(k.kb) * rev_rsq(r2) : T(1);
       const T r0 = T(k.c[0]) + s * e0 - u, r1 = T(k.c[1]) + s * e1 - v;
       rt0 = w[0] * r0 + w[1] * r1;
       rt1 = w[2] * r1;
@@ -1582,20 +1715,32 @@ __device__ __forceinline__ bool rev_normal_eqs(const KpRec *__restrict__ kp, int
   return group_and<kRevGroup>(ok);
 }
 
-// <E_bar, dExp(w)/dw_k> for k = 0, 1, 2 (the literal exp_so3 differentiated
-// by dual numbers, as the forward-mode kernels do).
-__device__ __forceinline__ void rev_exp_adjoint(const float w[3], const float Eb[9], float wb[3]) {
+// w_bar of E = Exp(w) from E_bar: dE = [J_l(w) dw]x E, so w_bar = J_l(w)^T v
+// with v = vee(X - X^T), X = E_bar E^T, and J_l(w)^T = I - B [w]x + D [w]x^2,
+// B = (1 - cos th) / th^2, D = (th - sin th) / th^3 (series for th^2 <= 1/4).
+__device__ __forceinline__ void rev_exp_adjoint(const float w[3], const float E[9], const float Eb[9], float wb[3]) {
+  float v[3];
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
-    Dual<float> wd[3] = {Dual<float>(w[0], k == 0 ? 1.f : 0.f), Dual<float>(w[1], k == 1 ? 1.f : 0.f),
-                         Dual<float>(w[2], k == 2 ? 1.f : 0.f)};
-    Dual<float> E[9];
-    exp_so3(wd, E);
-    float acc = 0.f;
-#pragma unroll
-    for (int m = 0; m < 9; ++m) acc += Eb[m] * E[m].d;
-    wb[k] = acc;
+    const int a = (k + 2) % 3, b = (k + 1) % 3;
+    v[k] = (Eb[3 * a] * E[3 * b] + Eb[3 * a + 1] * E[3 * b + 1] + Eb[3 * a + 2] * E[3 * b + 2]) -
+           (Eb[3 * b] * E[3 * a] + Eb[3 * b + 1] * E[3 * a + 1] + Eb[3 * b + 2] * E[3 * a + 2]);
   }
+  const float z = w[0] * w[0] + w[1] * w[1] + w[2] * w[2];
+  float B, Dc;
+  if (z <= 0.25f) {
+    B = 0.5f + z * (-1.f / 24.f + z * (1.f / 720.f + z * (-1.f / 40320.f)));
+    Dc = 1.f / 6.f + z * (-1.f / 120.f + z * (1.f / 5040.f + z * (-1.f / 362880.f)));
+  } else {
+    const float th = sqrtf(z), sh = sinf(0.5f * th);
+    B = 2.f * sh * sh / z;
+    Dc = (1.f - sinf(th) / th) / z;
+  }
+  float wv[3], wwv[3];
+  cross3(w, v, wv);
+  cross3(w, wv, wwv);
+#pragma unroll
+  for (int k = 0; k < 3; ++k) wb[k] = v[k] - B * wv[k] + Dc * wwv[k];
 }
 
 // Cotangent of the pivot o from one Gauss-Newton update, given the cotangent
@@ -1651,7 +1796,7 @@ __device__ __forceinline__ void rev_update_adjoint(const float d[6], const float
     db[3 + r] = xb_out.t[r];
   }
   rev_pivot_adjoint(d, xb_out.t, ob);
-  rev_exp_adjoint(d, Eb, db);
+  rev_exp_adjoint(d, E, Eb, db);
 }
 
 // Per-keypoint adjoint of one pass: adds this lane's part of the input
@@ -2024,14 +2169,10 @@ __global__ void __launch_bounds__(64) k_bwd_rev2d(DevBatch b, DevParams p, const
       for (int gs = 0; gs < p.n_gn && ok; ++gs) {
         const int ps = itr * p.n_gn + gs;
         if (q < 12) tape[12 * ps + q] = (float)(q < 9 ? x.R[q] : x.t[q - 9]);
-        double A[21], g[6], L[21], dinv[6], d[6];
+        double A[21], g[6];
         ok = gs == 0 ? rev_normal_eqs<true, double>(kp, n, q, I.K, ocd, p.z_min, band, xk, x, A, g, cl, false)
                      : rev_normal_eqs<false, double>(kp, n, q, I.K, ocd, p.z_min, band, xk, x, A, g, cl, true);
-        ok = ok && chol6_factor<double>(A, L, dinv);
-        if (ok) {
-          chol6_subst<double>(L, dinv, g, d);
-          apply_update<double>(d, ocd, x.R, x.t);
-        }
+        ok = ok && rev_step(A, g, ocd, x.R, x.t);
       }
       clb[itr * kRevGroup + q] = (uint8_t)cl;
     }
@@ -2124,7 +2265,7 @@ __global__ void __launch_bounds__(64) k_bwd_rev2d(DevBatch b, DevParams p, const
             Eb[3 * r + c] = I.Ra[r] * cR[c] + I.Ra[3 + r] * cR[3 + c] + I.Ra[6 + r] * cR[6 + c];
             RaT[3 * r + c] = I.Ra[3 * c + r];
           }
-        rev_exp_adjoint(phi, Eb, phib);
+        rev_exp_adjoint(phi, E, Eb, phib);
         const float wb[3] = {lo * phib[0], lo * phib[1], lo * phib[2]};
         matmul3(RaT, xf.R, Q);
         rev_log_adjoint(Q, wb, Qb);
@@ -2270,7 +2411,7 @@ __device__ __forceinline__ void rev3d_sums(const KpRec *__restrict__ kp, int n, 
     }
     const T r2 = e[0] * e[0] + e[1] * e[1] + e[2] * e[2];
     if (!use_cl && !(r2 <= T(k.kb2) * T(band))) cl |= 1u << rr;
-    const T sc = ((cl >> rr) & 1u) ? T(k.kb) * drsqrt(r2) : T(1);
+    const T sc = ((cl >> rr) & 1u) ? T(k.kb) * rev_rsq(r2) : T(1);
 #pragma unroll
     for (int r = 0; r < 3; ++r) {
       const T qq = sc * e[r] - d[r];
@@ -2429,8 +2570,8 @@ __global__ void __launch_bounds__(64) k_bwd_rev3d(DevBatch b, DevParams p, const
     const int n = live ? I.n_kp : 0;
     const int s = live ? rec->active[a] : 0;
     // ---------------------------------------------------------- forward
-    // In float64, as in the 2D-3D sweep (the polar factor by the float64
-    // Jacobi iteration); float32 tape and clamp bits for the sweep.
+    // In float64, as in the 2D-3D sweep (the polar factor by Newton steps
+    // from the last iteration's); float32 tape and clamp bits for the sweep.
     RevPoseT<double> x;
     {
       const PoseT<double> x0 = initial_pose<double>(frame_ref(I), I.seed, (uint64_t)s, p);
@@ -2447,7 +2588,7 @@ __global__ void __launch_bounds__(64) k_bwd_rev3d(DevBatch b, DevParams p, const
         uint32_t cl = 0u;
         rev3d_sums<double>(kp, n, q, I.abar, band, x, tt, M, qs, cl, false);
         clb[itr * kRevGroup + q] = (uint8_t)cl;
-        polar_so3<double>(M, x.R, 10);
+        rev_polar(M, x.R);
 #pragma unroll
         for (int r = 0; r < 3; ++r)
           x.t[r] = tt[r] + qs[r] * inv_n -
@@ -2540,7 +2681,7 @@ __global__ void __launch_bounds__(64) k_bwd_rev3d(DevBatch b, DevParams p, const
             Eb[3 * r + c] = I.Ra[r] * cR[c] + I.Ra[3 + r] * cR[3 + c] + I.Ra[6 + r] * cR[6 + c];
             RaT[3 * r + c] = I.Ra[3 * c + r];
           }
-        rev_exp_adjoint(phi, Eb, phib);
+        rev_exp_adjoint(phi, E, Eb, phib);
         const float wb[3] = {lo * phib[0], lo * phib[1], lo * phib[2]};
         matmul3(RaT, xf.R, Q);
         rev_log_adjoint(Q, wb, Qb);
