@@ -19,6 +19,11 @@ namespace purse {
 
 constexpr int kSmallN = 16;  // keypoint bound of the unrolled 2D-3D variant
 
+// Keypoints of the general 2D-3D loop whose targets stay in LDS: the 7.5 KB a
+// wavefront that 160 KB allows at the five wavefronts per SIMD of its registers
+// (four wavefronts with 20 keypoints, and three with 26, are slower).
+constexpr int kHeldKp = 15;
+
 constexpr int kSchedBlock = 1024;
 
 // Launch group of an instance: 0 for 3D-3D (an invalid kind goes there too,
@@ -138,10 +143,19 @@ __device__ __forceinline__ void sample_tile(int b, const InstRec *__restrict__ i
     return;
   }
   const FrameRef F = frame_ref(I);
-  const KpPlain kpl{kprec + I.kp_off};
   Pose x = initial_pose<float>(F, I.seed, (uint64_t)s, p);
   int n_fb = 0;
-  uint8_t m = run_trajectory<KIND, NMAX>(I, F, kpl, x, p, true, n_fb);
+  uint8_t m;
+  if constexpr (KIND == PURSE_KIND_2D3D && NMAX == 0) {
+    // this lane's column of its wave's kHeldKp x 64 targets
+    extern __shared__ float2 held_s[];
+    const KpHeld kpl{kprec + I.kp_off, held_s + (threadIdx.x >> 6) * (kHeldKp * 64) + (threadIdx.x & 63),
+                     min(I.n_kp, kHeldKp)};
+    m = run_trajectory<KIND, NMAX>(I, F, kpl, x, p, true, n_fb);
+  } else {
+    const KpPlain kpl{kprec + I.kp_off};
+    m = run_trajectory<KIND, NMAX>(I, F, kpl, x, p, true, n_fb);
+  }
   out[0] = make_float4(x.R[0], x.R[1], x.R[2], x.R[3]);
   out[1] = make_float4(x.R[4], x.R[5], x.R[6], x.R[7]);
   out[2] = make_float4(x.R[8], x.t[0], x.t[1], x.t[2]);
@@ -164,8 +178,9 @@ __device__ __forceinline__ void tile_queue(int32_t *counter, int total, F &&run)
   }
 }
 
+// (3D-3D: 128 registers, four wavefronts per SIMD)
 template <int KIND, int NMAX, bool QUEUE>
-__global__ void __launch_bounds__(256) k_sample(const InstRec *__restrict__ inst, const KpRec *__restrict__ kprec,
+__global__ void __launch_bounds__(256, KIND == PURSE_KIND_3D3D ? 4 : 1) k_sample(const InstRec *__restrict__ inst, const KpRec *__restrict__ kprec,
                                                 int32_t *__restrict__ sched, int n_inst, DevParams p,
                                                 float *__restrict__ poses, uint8_t *__restrict__ mask) {
   constexpr int grp = group_of<KIND, NMAX>();
@@ -317,6 +332,8 @@ hipError_t launch_sample(const DevBatch &b, const DevParams &p, const InstRec *i
     lds_block = 65536;
   const size_t lds = waves_per_simd > 0 ? (size_t)std::max(0, std::min(lds_cu / (wg_per_cu + 1) + 512, lds_block - 2048))
                                         : 0;
+  // the general 2D-3D loop's held targets
+  const size_t lds_held = std::max(lds, (size_t)tile * kHeldKp * sizeof(float2));
   const bool queue = (p.flags & PURSE_FLAG_WORK_QUEUE) != 0;
   auto grid_of = [&](int t) {
     const int64_t g = sample_grid(grid_samples, b.n_inst, t);
@@ -345,12 +362,12 @@ hipError_t launch_sample(const DevBatch &b, const DevParams &p, const InstRec *i
                        b.n_inst, p, poses, mask);
   }
   if (queue) {
-    hipLaunchKernelGGL((k_sample<PURSE_KIND_2D3D, 0, true>), grid, dim3(tile), lds, gs[1], inst, kp, sched, b.n_inst,
+    hipLaunchKernelGGL((k_sample<PURSE_KIND_2D3D, 0, true>), grid, dim3(tile), lds_held, gs[1], inst, kp, sched, b.n_inst,
                        p, poses, mask);
     hipLaunchKernelGGL((k_sample<PURSE_KIND_3D3D, 0, true>), grid, dim3(tile), lds, gs[2], inst, kp, sched, b.n_inst,
                        p, poses, mask);
   } else {
-    hipLaunchKernelGGL((k_sample<PURSE_KIND_2D3D, 0, false>), grid, dim3(tile), lds, gs[1], inst, kp, sched,
+    hipLaunchKernelGGL((k_sample<PURSE_KIND_2D3D, 0, false>), grid, dim3(tile), lds_held, gs[1], inst, kp, sched,
                        b.n_inst, p, poses, mask);
     hipLaunchKernelGGL((k_sample<PURSE_KIND_3D3D, 0, false>), grid, dim3(tile), lds, gs[2], inst, kp, sched,
                        b.n_inst, p, poses, mask);

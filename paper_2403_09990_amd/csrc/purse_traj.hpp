@@ -5,6 +5,9 @@
 // one input direction.
 #pragma once
 
+#include <cfloat>
+#include <type_traits>
+
 #include "purse_device.hpp"
 
 namespace purse {
@@ -37,6 +40,18 @@ struct KpT {
 struct KpPlain {
   static constexpr bool kPrefetch = true;
   const KpRec *__restrict__ kp;
+  __device__ __forceinline__ KpRec operator()(int i) const { return kp[i]; }
+};
+
+// The sampler's loader for the general 2D-3D loop: the same records, and a
+// column of LDS that holds the projection targets of the first `held`
+// keypoints between the Gauss-Newton steps of an iteration (q[i * 64] of
+// keypoint i; traj2d_held).
+struct KpHeld {
+  static constexpr bool kPrefetch = false;
+  const KpRec *__restrict__ kp;
+  float2 *q;
+  int held;
   __device__ __forceinline__ KpRec operator()(int i) const { return kp[i]; }
 };
 
@@ -215,6 +230,60 @@ __device__ __forceinline__ void traj3d(const KPL &kpl, int n, const float abar[3
   }
 }
 
+// The sampler's 3D-3D trajectory: traj3d's arithmetic and order with the polar
+// factor written without branches and the keypoint records loaded four at a
+// time (a lone wavefront otherwise waits for each record).  Every sum spells
+// out its fusing, so that the kernels that inline it round alike.
+__device__ __forceinline__ void traj3d_straight(const KpPlain &kpl, int n, const float abar[3], int n_iters, bool force64,
+                                                Pose &x) {
+  const float inv_n = 1.f / (float)n;
+  for (int it = 0; it < n_iters; ++it) {
+    float tt[3], M[9], qs[3];
+#pragma unroll
+    for (int r = 0; r < 3; ++r)
+      tt[r] = fmaf(x.R[3 * r + 2], abar[2], fmaf(x.R[3 * r + 1], abar[1], fmaf(x.R[3 * r], abar[0], x.t[r])));
+#pragma unroll
+    for (int k = 0; k < 9; ++k) M[k] = 0.f;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) qs[k] = 0.f;
+    const auto keypoint = [&](const KpRec &k) {
+      float d[3], e[3];
+#pragma unroll
+      for (int r = 0; r < 3; ++r) {
+        d[r] = tt[r] - k.c[r];
+        e[r] = fmaf(x.R[3 * r + 2], k.m[2], fmaf(x.R[3 * r + 1], k.m[1], x.R[3 * r] * k.m[0])) + d[r];
+      }
+      const float r2 = dot3_fma(e[0], e[0], e[1], e[1], e[2], e[2]);
+      const float s = (r2 <= k.kb2) ? 1.f : k.kb * drsqrt(r2);
+      const float q[3] = {fmaf(s, e[0], -d[0]), fmaf(s, e[1], -d[1]), fmaf(s, e[2], -d[2])};  // q_i - tt
+#pragma unroll
+      for (int r = 0; r < 3; ++r) {
+        M[3 * r] = fmaf(q[r], k.m[0], M[3 * r]);
+        M[3 * r + 1] = fmaf(q[r], k.m[1], M[3 * r + 1]);
+        M[3 * r + 2] = fmaf(q[r], k.m[2], M[3 * r + 2]);
+        qs[r] += q[r];
+      }
+    };
+    const KpRec *__restrict__ kp = kpl.kp;
+    const KpRec *const end = kp + n, *const end4 = kp + (n & ~3);
+    for (; kp != end4; kp += 4) {
+      const KpRec k0 = kp[0], k1 = kp[1], k2 = kp[2], k3 = kp[3];
+      keypoint(k0);
+      keypoint(k1);
+      keypoint(k2);
+      keypoint(k3);
+    }
+    for (; kp != end; ++kp) keypoint(*kp);
+    if (force64 || !polar_so3_straight(M, x.R)) polar_fp64(M, x.R);
+    float ra[3];
+#pragma unroll
+    for (int r = 0; r < 3; ++r)
+      ra[r] = fmaf(x.R[3 * r + 2], abar[2], fmaf(x.R[3 * r + 1], abar[1], x.R[3 * r] * abar[0]));
+#pragma unroll
+    for (int r = 0; r < 3; ++r) x.t[r] = fmaf(qs[r], inv_n, tt[r]) - ra[r];
+  }
+}
+
 // margin_k < 0: test r_i <= beta_i + tau; else r_i <= kappa beta_i + tau
 template <typename T, typename KPL>
 __device__ __forceinline__ bool feasible3d(const KPL &kpl, int n, const float abar[3], const PoseT<T> &x,
@@ -345,6 +414,109 @@ __device__ __forceinline__ bool gn_pass2d_unrolled(const KPL &kpl, int n, const 
   return true;
 }
 
+// The general loop of the sampler: gn_pass2d with the targets of the first
+// `held` keypoints kept in LDS, so that later steps neither project them at xk
+// again nor redo the ellipse scaling (29 of the 224 vector instructions of a
+// keypoint's two steps, and two of its five transcendentals).  Bounded by the
+// vector instruction rate: the depth test is one running minimum (a NaN depth
+// fails in the factorisation), the records are walked by a pointer and the
+// principal point sits in vector registers (an instruction reads one scalar
+// register), which takes the scalar instructions of a keypoint's step from 19 to
+// 10.  Arithmetic and order as in gn_pass2d, which the general trajectory
+// (prologue, tangents) keeps.  2 instances of 48 keypoints x 2^20 samples:
+// 21.1 -> 20.3 ms; one of 24 x 65536: 1.01 -> 0.82 ms (the LDS also spreads a
+// small launch evenly over the compute units).
+template <bool FIRST, bool HELD>
+__device__ __forceinline__ void gn_keypoint2d(const KpRec &k, const float K[4], const float cp[2], const float oc[3],
+                                              const Pose &xk, const Pose &x, float2 &q, float &z_lo, float A[21],
+                                              float g[6]) {
+  float P[3];
+#pragma unroll
+  for (int r = 0; r < 3; ++r)
+    P[r] = x.R[3 * r] * k.m[0] + x.R[3 * r + 1] * k.m[1] + x.R[3 * r + 2] * k.m[2] + x.t[r];
+  const float iz = drcp(P[2]);
+  const float u = fmaf(K[0], P[0] * iz, cp[0]), v = fmaf(K[1], P[1] * iz, cp[1]);
+  __asm__("v_min_f32 %0, %0, %1" : "+v"(z_lo) : "v"(P[2]));  // (fminf re-canonicalises z_lo each time)
+  float rt0, rt1;
+  if (FIRST) {
+    const float e0 = u - k.c[0], e1 = v - k.c[1];
+    const float et0 = k.w[0] * e0 + k.w[1] * e1, et1 = k.w[2] * e1;
+    const float r2 = et0 * et0 + et1 * et1, rs = drsqrt(r2);
+    const bool in = r2 <= k.kb2;
+    const float s1 = in ? 0.f : fmaf(k.kb, rs, -1.f);
+    rt0 = s1 * et0;
+    rt1 = s1 * et1;
+    if (HELD) {
+      const float s = in ? 1.f : k.kb * rs;
+      q = make_float2(fmaf(s, e0, k.c[0]), fmaf(s, e1, k.c[1]));
+    }
+  } else {
+    float q0, q1;
+    if (HELD) {
+      q0 = q.x;
+      q1 = q.y;
+    } else {
+      float Pk[3];
+#pragma unroll
+      for (int r = 0; r < 3; ++r)
+        Pk[r] = xk.R[3 * r] * k.m[0] + xk.R[3 * r + 1] * k.m[1] + xk.R[3 * r + 2] * k.m[2] + xk.t[r];
+      const float izk = drcp(Pk[2]);
+      const float e0 = fmaf(K[0], Pk[0] * izk, cp[0]) - k.c[0], e1 = fmaf(K[1], Pk[1] * izk, cp[1]) - k.c[1];
+      const float et0 = k.w[0] * e0 + k.w[1] * e1, et1 = k.w[2] * e1;
+      const float r2 = et0 * et0 + et1 * et1;
+      const float s = r2 <= k.kb2 ? 1.f : k.kb * drsqrt(r2);
+      q0 = fmaf(s, e0, k.c[0]);
+      q1 = fmaf(s, e1, k.c[1]);
+    }
+    const float r0 = q0 - u, r1 = q1 - v;
+    rt0 = k.w[0] * r0 + k.w[1] * r1;
+    rt1 = k.w[2] * r1;
+  }
+  const float pt[3] = {P[0] - oc[0], P[1] - oc[1], P[2] - oc[2]};
+  gn_accumulate<float>(P, pt, iz, K[0], K[1], k.w, rt0, rt1, A, g);
+}
+
+template <bool FIRST>
+__device__ __forceinline__ bool gn_pass2d_held(const KpHeld &kpl, int n, const float K[4], const float cp[2],
+                                               const float oc[3], float z_min, const Pose &xk, Pose &x) {
+  float A[21], g[6], z_lo = FLT_MAX;
+#pragma unroll
+  for (int k = 0; k < 21; ++k) A[k] = 0.f;
+#pragma unroll
+  for (int k = 0; k < 6; ++k) g[k] = 0.f;
+  const KpRec *__restrict__ kp = kpl.kp;
+  const KpRec *const mid = kp + kpl.held, *const end = kp + n;
+  float2 *q = kpl.q, none;
+  for (; kp != mid; ++kp, q += 64) {
+    if (FIRST) {
+      float2 t;
+      gn_keypoint2d<true, true>(*kp, K, cp, oc, xk, x, t, z_lo, A, g);
+      *q = t;
+    } else {
+      float2 t = *q;
+      gn_keypoint2d<false, true>(*kp, K, cp, oc, xk, x, t, z_lo, A, g);
+    }
+  }
+  for (; kp != end; ++kp) gn_keypoint2d<FIRST, false>(*kp, K, cp, oc, xk, x, none, z_lo, A, g);
+  float d[6];
+  if (!(z_lo > z_min && chol6_solve<float>(A, g, d))) return false;
+  apply_update<float>(d, oc, x.R, x.t);
+  return true;
+}
+
+__device__ __forceinline__ bool traj2d_held(const KpHeld &kpl, int n, const float K[4], const float oc[3], int n_iters,
+                                            int n_gn, float z_min, Pose &x) {
+  float cp[2] = {K[2], K[3]};
+  __asm__("" : "+v"(cp[0]), "+v"(cp[1]));
+  for (int it = 0; it < n_iters; ++it) {
+    const Pose xk = x;
+    if (!gn_pass2d_held<true>(kpl, n, K, cp, oc, z_min, xk, x)) return false;
+    for (int gs = 1; gs < n_gn; ++gs)
+      if (!gn_pass2d_held<false>(kpl, n, K, cp, oc, z_min, xk, x)) return false;
+  }
+  return true;
+}
+
 // NMAX > 0: at most NMAX keypoints, loops unrolled (gn_pass2d_unrolled).
 template <int NMAX, typename T, typename KPL>
 __device__ __forceinline__ bool traj2d(const KPL &kpl, int n, const float K[4], const T oc[3], int n_iters,
@@ -462,10 +634,17 @@ __device__ __forceinline__ uint8_t run_trajectory(const InstRec &I, const FR &F,
                                                   int &n_fb) {
   bool ok = true;
   if (KIND == PURSE_KIND_3D3D) {
-    traj3d(kpl, I.n_kp, I.abar, p.n_iters, (p.flags & PURSE_FLAG_FORCE_FP64_POLAR) != 0, x, n_fb);
+    const bool force64 = (p.flags & PURSE_FLAG_FORCE_FP64_POLAR) != 0;
+    if constexpr (std::is_same<KPL, KpPlain>::value)
+      traj3d_straight(kpl, I.n_kp, I.abar, p.n_iters, force64, x);
+    else
+      traj3d(kpl, I.n_kp, I.abar, p.n_iters, force64, x, n_fb);
   } else {
     T oc[3] = {T(F.oc[0]), T(F.oc[1]), T(F.oc[2])};
-    ok = traj2d<NMAX>(kpl, I.n_kp, I.K, oc, p.n_iters, p.n_gn, p.z_min, x);
+    if constexpr (std::is_same<KPL, KpHeld>::value)
+      ok = traj2d_held(kpl, I.n_kp, I.K, oc, p.n_iters, p.n_gn, p.z_min, x);
+    else
+      ok = traj2d<NMAX>(kpl, I.n_kp, I.K, oc, p.n_iters, p.n_gn, p.z_min, x);
     reorthonormalise(x.R);
   }
   if (!ok) return PURSE_MASK_FAILED;
