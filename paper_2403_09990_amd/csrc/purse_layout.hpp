@@ -10,10 +10,11 @@ namespace purse {
 
 // Per-keypoint record written by the prologue (48 bytes, read wave-uniformly
 // by the sampler).
-//   3D-3D: m = a_i - abar (centred model point), c = b_i, w unused.
-//   2D-3D: m = Z_i, c = (z_i.x, z_i.y, 0), w = (u00, u01, u11) with
+//   3D-3D: m = a_i - abar (centred model point), c = b_i, w = (lim, 0, 0).
+//   2D-3D: m = Z_i, c = (z_i.x, z_i.y, lim), w = (u00, u01, u11) with
 //          [[u00, u01], [0, u11]]^T [[u00, u01], [0, u11]] = Lambda_i.
-//   kb = kappa beta_i, kb2 = kb^2, bt = beta_i + tau_abs.
+//   kb = kappa beta_i, kb2 = kb^2, bt = beta_i + tau_abs, lim = the largest
+//   squared radius whose root is at most bt.
 struct KpRec {
   float m[3];
   float c[3];

@@ -88,6 +88,10 @@ __global__ void __launch_bounds__(kPrologueBlock) k_prologue(DevBatch b, DevPara
         k.kb = (float)((double)p.kappa * beta[i]);
         k.kb2 = k.kb * k.kb;
         k.bt = (float)((double)beta[i] + tau);
+        if (is2d)
+          k.c[2] = radius_limit(k.bt);  // r2_limit_2d
+        else
+          k.w[0] = radius_limit(k.bt);  // r2_limit_3d
         kprec[kp_off + i] = k;
       }
     }
