@@ -167,7 +167,7 @@ typedef struct purse_params {
   int32_t centre_gn;   /* cap on the Gauss-Newton steps of the 2D-3D centre fit, which
                           stops once the step is below 1e-13 (rotation, rad) and
                           1e-13 (1 + |t|_inf) (translation, m) */
-  int32_t tile;        /* samples per workgroup: 64, 128 or 256; 0 = library choice (256) */
+  int32_t tile;        /* samples per workgroup: 64, 128 or 256; 0 = library choice */
   int32_t flags;       /* PURSE_FLAG_* */
   int32_t waves_per_simd; /* purse_sample: cap on the trajectory kernels' resident wavefronts per SIMD
                              (1..8, by padding each workgroup's LDS within the per-workgroup limit; the

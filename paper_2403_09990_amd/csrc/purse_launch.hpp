@@ -13,10 +13,10 @@ void launch_prologue(const DevBatch &b, const DevParams &p, InstRec *inst, KpRec
 // Workgroups of one sampler launch (an upper bound on sum_j ceil(M_j / tile)).
 int64_t sample_grid(int64_t total_samples, int n_inst, int tile);
 
-// Builds the tile schedule (sched: sched_ints(n_inst) int32 per kind, then
-// one work-queue counter per kind) and runs both kinds' trajectories; tile:
-// samples per workgroup (64, 128 or 256); waves_per_simd: residency cap (0:
-// none).  The launch groups run on the stream and two auxiliary streams
+// Builds the tile schedule where one is needed (sched: sched_ints(n_inst) int32
+// per kind, then one work-queue counter per kind) and runs both kinds'
+// trajectories; tile: samples per workgroup (64, 128 or 256; 0: chosen);
+// waves_per_simd: residency cap (0: none).  The launch groups run on the stream and two auxiliary streams
 // unless PURSE_FLAG_SERIAL_GROUPS; returns an error (after launching the
 // work) if the auxiliary streams' join could not be recorded; launch errors
 // are left to hipGetLastError.

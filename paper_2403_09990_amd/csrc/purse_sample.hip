@@ -3,12 +3,15 @@
 // keypoint records (wave-uniform loads) and runs one code path; one launch
 // per kind keeps each kind's register allocation separate.
 //
-// Tiles of a ragged batch are dealt from a schedule built on the device after
-// the prologue: per kind, the instances in decreasing per-trajectory cost (the
-// keypoint count orders it within a kind), each contributing ceil(M_j / tile)
-// consecutive tiles.  The hardware dispatches workgroups in index order, so the
-// heaviest tiles start first and the tail of the launch is made of light ones
-// (longest-processing-time-first list scheduling).
+// Tiles of a ragged batch are dealt from a schedule: per kind, the instances in
+// decreasing per-trajectory cost (the keypoint count orders it within a kind),
+// each contributing ceil(M_j / tile) consecutive tiles.  The hardware dispatches
+// workgroups in index order, so the heaviest tiles start first and the tail of
+// the launch is made of light ones (longest-processing-time-first list
+// scheduling).  Up to 64 instances, every wavefront works its tile out from the
+// records itself (few_tile); larger batches, and the work queue, have the
+// schedule built on the device after the prologue (k_schedule).  A launch that
+// the chip holds at once anyway runs all kinds in one kernel (k_sample_few).
 #include <algorithm>
 #include <mutex>
 
@@ -49,64 +52,196 @@ constexpr int group_of() {
 
 constexpr int kMaxSorted = 8192;  // larger batches keep instance order
 
-// Builds both kinds' schedules in one workgroup: rank of instance j = number
-// of instances of the kind that come before it (larger keypoint count, or
-// equal count and lower index), then a prefix sum of tile counts in rank order.
+// Samples per tile of a launch group (a power of two), for workgroups of
+// `lanes`: one per lane, or one per lane group in the lane-group modes.
+__device__ __forceinline__ int tile_shift(int group, int lanes, int flags) {
+  return 31 - __clz(group == 2 ? lanes / group_lanes(flags) : lanes);
+}
+
+__device__ __forceinline__ uint32_t tiles_of(const InstRec &I, int group, int lanes, int flags) {
+  const int sh = tile_shift(group, lanes, flags);
+  return (uint32_t)((I.n_samples + (((int64_t)1 << sh) - 1)) >> sh);
+}
+
+// Cost class of an instance's trajectories, 0 the heaviest.
+__device__ __forceinline__ int cost_class(const InstRec &I, int flags) {
+  return (flags & PURSE_FLAG_INSTANCE_ORDER) ? 0 : PURSE_MAX_KP - min(max(I.n_kp, 0), PURSE_MAX_KP);
+}
+
+constexpr int kSchedKeys = kSchedGroups * (PURSE_MAX_KP + 1);  // (group, cost class)
+
+// Builds the groups' schedules in one workgroup.  A stable counting sort by
+// (group, cost class, index): totals per key, then each chunk of kSchedBlock
+// instances takes its places from the keys' bases, the counts of the
+// wavefronts before its own, and its rank among the equal keys of its
+// wavefront; then one prefix sum of tile counts over the whole order, from
+// which each group takes the differences to its own start.  (Ranking every
+// instance against every other, one group after the other, took 102 us for
+// 512 instances, between the prologue and the first trajectory.)
 __global__ void __launch_bounds__(kSchedBlock) k_schedule(const InstRec *__restrict__ inst, int n, int tile_lanes,
                                                           int flags, int32_t *__restrict__ sched) {
-  __shared__ int key[kMaxSorted];
-  __shared__ int part[kSchedBlock];
-  const int tid = threadIdx.x;
-  const bool sorted = n <= kMaxSorted && !(flags & PURSE_FLAG_INSTANCE_ORDER);
-  for (int kind = 0; kind < kSchedGroups; ++kind) {
-    // samples per tile: one per lane, or one per lane group in the lane-group modes
-    const int tile = kind == 2 ? tile_lanes / group_lanes(flags) : tile_lanes;
-    int32_t *order = sched + (size_t)kind * sched_ints(n);
-    int32_t *tstart = order + n;
-    if (sorted) {
-      for (int j = tid; j < n; j += kSchedBlock) key[j] = launch_group(inst[j], flags) == kind ? inst[j].n_kp : -1;
+  constexpr int kWaves = kSchedBlock / 64;
+  __shared__ uint32_t tl[kMaxSorted];            // tile counts in order
+  __shared__ uint32_t cnt[kWaves][kSchedKeys];   // a chunk's counts per wavefront, then places
+  __shared__ uint32_t base[kSchedKeys];          // next place of each key
+  __shared__ uint32_t part[kWaves];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const size_t stride = sched_ints(n);
+  // exclusive prefix sum of one value per thread
+  auto scan = [&](uint32_t v, uint32_t &total) {
+    uint32_t x = v;
+    for (int o = 1; o < 64; o <<= 1) {
+      const uint32_t y = (uint32_t)__shfl_up((int)x, o, 64);
+      if (lane >= o) x += y;
+    }
+    __syncthreads();  // (part is free)
+    if (lane == 63) part[wave] = x;
+    __syncthreads();
+    uint32_t before = 0, all = 0;
+    for (int w = 0; w < kWaves; ++w) {
+      const uint32_t q = part[w];
+      before += w < wave ? q : 0u;
+      all += q;
+    }
+    total = all;
+    return before + x - v;
+  };
+  if (n <= kMaxSorted) {
+    for (int k = tid; k < kSchedKeys; k += kSchedBlock) base[k] = 0u;
+    __syncthreads();
+    auto key_of = [&](const InstRec &I) {
+      return launch_group(I, flags) * (PURSE_MAX_KP + 1) + cost_class(I, flags);
+    };
+    for (int j = tid; j < n; j += kSchedBlock) atomicAdd(&base[key_of(inst[j])], 1u);
+    __syncthreads();
+    {
+      const uint32_t v = tid < kSchedKeys ? base[tid] : 0u;
+      uint32_t total;
+      const uint32_t x = scan(v, total);
+      if (tid < kSchedKeys) base[tid] = x;
       __syncthreads();
-      for (int j = tid; j < n; j += kSchedBlock) {
-        const int kj = key[j];
-        int r = 0;
-        for (int i = 0; i < n; ++i) {
-          const int ki = key[i];
-          r += (ki > kj) || (ki == kj && i < j);
-        }
-        order[r] = j;
+    }
+    uint32_t g0[kSchedGroups + 1];  // first place of each group
+    for (int g = 0; g < kSchedGroups; ++g) g0[g] = base[g * (PURSE_MAX_KP + 1)];
+    g0[kSchedGroups] = (uint32_t)n;
+    __syncthreads();
+    for (int j0 = 0; j0 < n; j0 += kSchedBlock) {
+      for (int k = tid; k < kWaves * kSchedKeys; k += kSchedBlock) (&cnt[0][0])[k] = 0u;
+      __syncthreads();
+      const int j = j0 + tid;
+      const bool in = j < n;
+      int grp = 0, key = 0;
+      uint32_t tiles = 0;
+      if (in) {
+        const InstRec &I = inst[j];
+        grp = launch_group(I, flags);
+        key = key_of(I);
+        tiles = tiles_of(I, grp, tile_lanes, flags);
       }
-    } else {
-      for (int j = tid; j < n; j += kSchedBlock) order[j] = j;
+      unsigned long long same = __ballot(in);
+#pragma unroll
+      for (int bit = 0; bit < 8; ++bit) {
+        const unsigned long long m = __ballot((key >> bit) & 1);
+        same &= ((key >> bit) & 1) ? m : ~m;
+      }
+      const uint32_t rank = (uint32_t)__popcll(same & ((1ull << lane) - 1ull));
+      if (in && rank == 0u) cnt[wave][key] = (uint32_t)__popcll(same);
+      __syncthreads();
+      if (tid < kSchedKeys) {
+        uint32_t at = base[tid];
+        for (int w = 0; w < kWaves; ++w) {
+          const uint32_t c = cnt[w][tid];
+          cnt[w][tid] = at;
+          at += c;
+        }
+        base[tid] = at;
+      }
+      __syncthreads();
+      if (in) {
+        const uint32_t r = cnt[wave][key] + rank;
+        tl[r] = tiles;
+        sched[grp * stride + (r - g0[grp])] = j;
+      }
+      __syncthreads();
     }
-    __threadfence_block();
-    __syncthreads();
-    // tiles per entry of the order, summed over contiguous chunks per thread
     const int per = (n + kSchedBlock - 1) / kSchedBlock;
-    const int b0 = tid * per, b1 = min(n, b0 + per);
-    int acc = 0;
-    for (int k = b0; k < b1; ++k) {
-      const InstRec &I = inst[order[k]];
-      acc += launch_group(I, flags) == kind ? (int)((I.n_samples + tile - 1) / tile) : 0;
-    }
-    part[tid] = acc;
+    const int b0 = min(n, tid * per), b1 = min(n, b0 + per);
+    uint32_t acc = 0, total;
+    for (int k = b0; k < b1; ++k) acc += tl[k];
+    uint32_t run = scan(acc, total);
     __syncthreads();
-    for (int off = 1; off < kSchedBlock; off <<= 1) {
-      const int v = tid >= off ? part[tid - off] : 0;
-      __syncthreads();
-      part[tid] += v;
-      __syncthreads();
-    }
-    int run = tid ? part[tid - 1] : 0;
     for (int k = b0; k < b1; ++k) {
-      tstart[k] = run;
-      const InstRec &I = inst[order[k]];
-      run += launch_group(I, flags) == kind ? (int)((I.n_samples + tile - 1) / tile) : 0;
+      const uint32_t t = tl[k];
+      tl[k] = run;
+      run += t;
     }
-    if (tid == kSchedBlock - 1) tstart[n] = part[kSchedBlock - 1];
     __syncthreads();
+    for (int g = 0; g < kSchedGroups; ++g) {
+      // places beyond the group's instances start at its end: no tile of theirs
+      int32_t *tstart = sched + g * stride + n;
+      const uint32_t first = g0[g] < (uint32_t)n ? tl[g0[g]] : total;
+      const uint32_t end = (g0[g + 1] < (uint32_t)n ? tl[g0[g + 1]] : total) - first;
+      const int m = (int)(g0[g + 1] - g0[g]);
+      for (int k = tid; k <= n; k += kSchedBlock) tstart[k] = (int32_t)(k < m ? tl[g0[g] + k] - first : end);
+    }
+  } else {
+    // instance order, one group after the other
+    const int per = (n + kSchedBlock - 1) / kSchedBlock;
+    const int b0 = min(n, tid * per), b1 = min(n, b0 + per);
+    for (int g = 0; g < kSchedGroups; ++g) {
+      int32_t *order = sched + g * stride, *tstart = order + n;
+      auto tiles = [&](int j) {
+        const InstRec &I = inst[j];
+        return launch_group(I, flags) == g ? tiles_of(I, g, tile_lanes, flags) : 0u;
+      };
+      uint32_t acc = 0, total;
+      for (int j = b0; j < b1; ++j) acc += tiles(j);
+      uint32_t run = scan(acc, total);
+      for (int j = b0; j < b1; ++j) {
+        order[j] = j;
+        tstart[j] = (int32_t)run;
+        run += tiles(j);
+      }
+      if (tid == 0) tstart[n] = (int32_t)total;
+    }
   }
   // the work-queue counters of the three groups
-  if (tid < kSchedGroups) sched[(size_t)kSchedGroups * sched_ints(n) + tid] = 0;
+  if (tid < kSchedGroups) sched[kSchedGroups * stride + tid] = 0;
+}
+
+// Tile b of launch group `group` (all of them for -1) of at most kFewInst
+// instances: its instance j and its place t among that instance's tiles; false
+// beyond the last tile.  Lane l holds instance l's tile count and cost, and
+// sums the counts of the instances before it; whole wavefronts call it.  (A
+// schedule built by a kernel of its own cost a launch, 10 us of the 0.2 ms of
+// the smallest calls; the sums are some 6 instructions per instance.)
+constexpr int kFewInst = 64;
+
+__device__ __forceinline__ bool few_tile(const InstRec *__restrict__ inst, int n, int lanes, int flags, int group,
+                                         uint32_t b, int &j, uint32_t &t) {
+  const int lane = threadIdx.x & 63;
+  int key = INT32_MAX;
+  uint32_t tiles = 0;
+  if (lane < n) {
+    const InstRec &I = inst[lane];
+    const int g = launch_group(I, flags);
+    if (group < 0 || g == group) {
+      tiles = tiles_of(I, g, lanes, flags);
+      // (a 2D-3D trajectory takes longer than any 3D-3D one)
+      key = cost_class(I, flags) + (g == 0 && !(flags & PURSE_FLAG_INSTANCE_ORDER) ? PURSE_MAX_KP + 1 : 0);
+    }
+  }
+  uint32_t start = 0;
+  for (int i = 0; i < n; ++i) {
+    const int ki = __builtin_amdgcn_readlane(key, i);
+    const uint32_t ti = (uint32_t)__builtin_amdgcn_readlane((int)tiles, i);
+    start += (ki < key || (ki == key && i < lane)) ? ti : 0u;
+  }
+  const unsigned long long hit = __ballot(b >= start && b - start < tiles);
+  if (hit == 0ull) return false;
+  j = __ffsll(hit) - 1;
+  t = b - (uint32_t)__builtin_amdgcn_readlane((int)start, j);
+  return true;
 }
 
 // The tile of schedule entry b: the entry k of the order with
@@ -123,15 +258,12 @@ __device__ __forceinline__ int tile_entry(const int32_t *__restrict__ tstart, in
   return lo;
 }
 
+// Sample s of instance j, one per lane.
 template <int KIND, int NMAX>
-__device__ __forceinline__ void sample_tile(int b, const InstRec *__restrict__ inst, const KpRec *__restrict__ kprec,
-                                            const int32_t *__restrict__ order, const int32_t *__restrict__ tstart,
-                                            int n_inst, const DevParams &p, float *__restrict__ poses,
-                                            uint8_t *__restrict__ mask) {
-  const int lo = tile_entry(tstart, n_inst, b);
-  const int j = order[lo];
+__device__ __forceinline__ void sample_at(int j, int64_t s, const InstRec *__restrict__ inst,
+                                          const KpRec *__restrict__ kprec, const DevParams &p,
+                                          float *__restrict__ poses, uint8_t *__restrict__ mask) {
   const InstRec &I = inst[j];
-  const int64_t s = (int64_t)(b - tstart[lo]) * blockDim.x + threadIdx.x;
   if (launch_group(I, p.flags) != group_of<KIND, NMAX>() || s >= I.n_samples) return;
   const int64_t g = I.sample_off + s;
   float4 *out = reinterpret_cast<float4 *>(poses + 12 * g);
@@ -162,6 +294,22 @@ __device__ __forceinline__ void sample_tile(int b, const InstRec *__restrict__ i
   mask[g] = m;
 }
 
+// This workgroup's tile of a launch group: instance j and the tile's place t
+// among its tiles, from the schedule or (none: at most kFewInst instances) the
+// records.
+__device__ __forceinline__ bool tile_of(const InstRec *__restrict__ inst, const int32_t *__restrict__ sched,
+                                        int n_inst, int flags, int grp, int &j, uint32_t &t) {
+  if (!sched) return few_tile(inst, n_inst, blockDim.x, flags, grp, blockIdx.x, j, t);
+  const int32_t *order = sched + (size_t)grp * sched_ints(n_inst);
+  const int32_t *tstart = order + n_inst;
+  const int b = blockIdx.x;
+  if (b >= tstart[n_inst]) return false;
+  const int lo = tile_entry(tstart, n_inst, b);
+  j = order[lo];
+  t = (uint32_t)(b - tstart[lo]);
+  return true;
+}
+
 // Work-queue mode: each workgroup takes the next tile of the group's
 // schedule from the counter k_schedule cleared, until none is left (every
 // workgroup reaches the end of the schedule and leaves).
@@ -184,14 +332,19 @@ __global__ void __launch_bounds__(256, KIND == PURSE_KIND_3D3D ? 4 : 1) k_sample
                                                 int32_t *__restrict__ sched, int n_inst, DevParams p,
                                                 float *__restrict__ poses, uint8_t *__restrict__ mask) {
   constexpr int grp = group_of<KIND, NMAX>();
-  const int32_t *order = sched + (size_t)grp * sched_ints(n_inst);
-  const int32_t *tstart = order + n_inst;
-  const int total = tstart[n_inst];
   if (QUEUE) {
-    tile_queue(sched + (size_t)kSchedGroups * sched_ints(n_inst) + grp, total,
-               [&](int b) { sample_tile<KIND, NMAX>(b, inst, kprec, order, tstart, n_inst, p, poses, mask); });
-  } else if ((int)blockIdx.x < total) {
-    sample_tile<KIND, NMAX>(blockIdx.x, inst, kprec, order, tstart, n_inst, p, poses, mask);
+    const int32_t *order = sched + (size_t)grp * sched_ints(n_inst);
+    const int32_t *tstart = order + n_inst;
+    tile_queue(sched + (size_t)kSchedGroups * sched_ints(n_inst) + grp, tstart[n_inst], [&](int b) {
+      const int lo = tile_entry(tstart, n_inst, b);
+      sample_at<KIND, NMAX>(order[lo], (int64_t)(b - tstart[lo]) * blockDim.x + threadIdx.x, inst, kprec, p, poses,
+                            mask);
+    });
+  } else {
+    int j;
+    uint32_t t;
+    if (!tile_of(inst, sched, n_inst, p.flags, grp, j, t)) return;
+    sample_at<KIND, NMAX>(j, (int64_t)t * blockDim.x + threadIdx.x, inst, kprec, p, poses, mask);
   }
 }
 
@@ -200,18 +353,15 @@ __global__ void __launch_bounds__(256, KIND == PURSE_KIND_3D3D ? 4 : 1) k_sample
 // trajectories, G lanes each; the instance's keypoint records are staged in
 // LDS first.
 template <int NMAX, int G>
-__device__ __forceinline__ void sample_tile_lanes(int b, KpRec *kp_s, const InstRec *__restrict__ inst,
-                                                  const KpRec *__restrict__ kprec, const int32_t *__restrict__ order,
-                                                  const int32_t *__restrict__ tstart, int n_inst, const DevParams &p,
-                                                  float *__restrict__ poses, uint8_t *__restrict__ mask) {
-  const int lo = tile_entry(tstart, n_inst, b);
-  const int j = order[lo];
+__device__ __forceinline__ void sample_lanes_at(int j, int64_t s0, KpRec *kp_s, const InstRec *__restrict__ inst,
+                                                const KpRec *__restrict__ kprec, const DevParams &p,
+                                                float *__restrict__ poses, uint8_t *__restrict__ mask) {
   const InstRec &I = inst[j];
   if (launch_group(I, p.flags) != 2) return;  // (whole workgroup)
   const bool valid = (I.status & 0xFF) == PURSE_INST_OK;
   if (valid && (int)threadIdx.x < I.n_kp) kp_s[threadIdx.x] = kprec[I.kp_off + threadIdx.x];
   __syncthreads();
-  const int64_t s = (int64_t)(b - tstart[lo]) * (blockDim.x / G) + (threadIdx.x / G);
+  const int64_t s = s0 + (threadIdx.x / G);
   const int q = threadIdx.x % G;
   if (s >= I.n_samples) return;  // the lanes of a group leave together
   const int64_t g = I.sample_off + s;
@@ -242,19 +392,50 @@ __global__ void __launch_bounds__(256, G == 4 ? 4 : 1) k_sample2d_lanes(const In
                                                         int32_t *__restrict__ sched, int n_inst, DevParams p,
                                                         float *__restrict__ poses, uint8_t *__restrict__ mask) {
   __shared__ KpRec kp_s[NMAX];
-  const int32_t *order = sched + (size_t)2 * sched_ints(n_inst);
-  const int32_t *tstart = order + n_inst;
-  const int total = tstart[n_inst];
   if (QUEUE) {
     // (the queue's barriers also keep a tile's keypoint records until every
     // lane is done with them)
-    tile_queue(sched + (size_t)kSchedGroups * sched_ints(n_inst) + 2, total, [&](int b) {
-      sample_tile_lanes<NMAX, G>(b, kp_s, inst, kprec, order, tstart, n_inst, p, poses, mask);
+    const int32_t *order = sched + (size_t)2 * sched_ints(n_inst);
+    const int32_t *tstart = order + n_inst;
+    tile_queue(sched + (size_t)kSchedGroups * sched_ints(n_inst) + 2, tstart[n_inst], [&](int b) {
+      const int lo = tile_entry(tstart, n_inst, b);
+      sample_lanes_at<NMAX, G>(order[lo], (int64_t)(b - tstart[lo]) * (blockDim.x / G), kp_s, inst, kprec, p, poses,
+                               mask);
     });
-  } else if ((int)blockIdx.x < total) {
-    sample_tile_lanes<NMAX, G>(blockIdx.x, kp_s, inst, kprec, order, tstart, n_inst, p, poses, mask);
+  } else {
+    int j;
+    uint32_t t;
+    if (!tile_of(inst, sched, n_inst, p.flags, 2, j, t)) return;
+    sample_lanes_at<NMAX, G>(j, (int64_t)t * (blockDim.x / G), kp_s, inst, kprec, p, poses, mask);
   }
 }
+
+// All launch groups of at most kFewInst instances in one launch, for batches
+// that the chip holds at once (few_waves): a launch per group, on streams of
+// their own with a fork and a join, costs 25 us that the groups of a large
+// batch win back by overlapping and a small batch does not.
+template <int G>
+__global__ void __launch_bounds__(256) k_sample_few(const InstRec *__restrict__ inst, const KpRec *__restrict__ kprec,
+                                                    int n_inst, DevParams p, float *__restrict__ poses,
+                                                    uint8_t *__restrict__ mask) {
+  __shared__ KpRec kp_s[G > 1 ? kSmallN : 1];
+  int j;
+  uint32_t t;
+  if (!few_tile(inst, n_inst, blockDim.x, p.flags, -1, blockIdx.x, j, t)) return;
+  const int64_t s = (int64_t)t * blockDim.x + threadIdx.x;
+  const int grp = launch_group(inst[j], p.flags);
+  if (grp == 0)
+    sample_at<PURSE_KIND_3D3D, 0>(j, s, inst, kprec, p, poses, mask);
+  else if (grp == 1)
+    sample_at<PURSE_KIND_2D3D, 0>(j, s, inst, kprec, p, poses, mask);
+  else if constexpr (G > 1)
+    sample_lanes_at<kSmallN, G>(j, (int64_t)t * (blockDim.x / G), kp_s, inst, kprec, p, poses, mask);
+  else
+    sample_at<PURSE_KIND_2D3D, kSmallN>(j, s, inst, kprec, p, poses, mask);
+}
+
+// Wavefronts that k_sample_few holds at once: three per SIMD at its registers.
+int64_t few_waves(int n_cu) { return (int64_t)n_cu * 4 * 3; }
 
 int64_t sample_grid(int64_t total_samples, int n_inst, int tile) {
   // sum_j ceil(M_j / tile) <= total / tile + n_inst
@@ -292,9 +473,53 @@ GroupAux *group_aux() {
 }  // namespace
 
 hipError_t launch_sample(const DevBatch &b, const DevParams &p, const InstRec *inst, const KpRec *kp,
-                         int32_t *sched, float *poses, uint8_t *mask, int tile, int64_t grid_samples,
+                         int32_t *sched, float *poses, uint8_t *mask, int asked_tile, int64_t grid_samples,
                          int waves_per_simd, hipStream_t stream) {
-  hipLaunchKernelGGL(k_schedule, dim3(1), dim3(kSchedBlock), 0, stream, inst, b.n_inst, tile, p.flags, sched);
+  const int tile = asked_tile ? asked_tile : 256;
+  const bool queue = (p.flags & PURSE_FLAG_WORK_QUEUE) != 0;
+  int dev = 0, n_cu = 256, lds_cu = 163840, lds_block = 65536;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+    n_cu = 256;
+  if (hipDeviceGetAttribute(&lds_cu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, dev) != hipSuccess ||
+      lds_cu <= 0)
+    lds_cu = 163840;
+  if (hipDeviceGetAttribute(&lds_block, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess ||
+      lds_block <= 0)
+    lds_block = 65536;
+  // LDS that keeps a compute unit from taking more than its share of a launch's
+  // workgroups: the dispatcher otherwise doubles up on some while others stay
+  // empty, one way or the other from call to call (262144 samples of 24
+  // keypoints, four wavefronts per SIMD: 0.77 or 0.89 ms)
+  auto even_lds = [&](int64_t wgs) {
+    const int64_t share = std::max<int64_t>(1, (wgs + n_cu - 1) / n_cu);
+    return (size_t)std::max<int64_t>(0, std::min<int64_t>(lds_cu / (share + 1) + 512, lds_block - 2048));
+  };
+  if (b.n_inst <= kFewInst && !queue) {
+    sched = nullptr;
+    const int lanes = group_lanes(p.flags);
+    const int64_t waves = sample_grid(grid_samples * lanes, b.n_inst, 64);
+    if (waves_per_simd == 0 && !(p.flags & PURSE_FLAG_SERIAL_GROUPS) && waves <= few_waves(n_cu)) {
+      // the smallest workgroups, unless the caller asked for a size, that
+      // still leave each its own compute unit: a wavefront runs up to 1.4
+      // times as fast there
+      const int wg = asked_tile ? asked_tile : (waves <= n_cu ? 64 : (waves <= 2 * n_cu ? 128 : 256));
+      // sum_j ceil(M_j / t) <= (sum_j M_j + n (t - 1)) / t, t = wg / lanes
+      const int t = wg / lanes;
+      const int64_t wgs = (grid_samples + (int64_t)b.n_inst * (t - 1)) / t;
+      const size_t held = std::max((size_t)wg * kHeldKp * sizeof(float2), even_lds(wgs));
+      const dim3 g((unsigned)wgs);
+      if (lanes == 4)
+        hipLaunchKernelGGL((k_sample_few<4>), g, dim3(wg), held, stream, inst, kp, b.n_inst, p, poses, mask);
+      else if (lanes == 2)
+        hipLaunchKernelGGL((k_sample_few<2>), g, dim3(wg), held, stream, inst, kp, b.n_inst, p, poses, mask);
+      else
+        hipLaunchKernelGGL((k_sample_few<1>), g, dim3(wg), held, stream, inst, kp, b.n_inst, p, poses, mask);
+      return hipSuccess;
+    }
+  } else {
+    hipLaunchKernelGGL(k_schedule, dim3(1), dim3(kSchedBlock), 0, stream, inst, b.n_inst, tile, p.flags, sched);
+  }
   // The three launch groups write disjoint samples and read only the
   // prologue's records and the schedules: they run concurrently on the
   // caller's stream and two auxiliary streams (a fork and a join by events,
@@ -320,21 +545,15 @@ hipError_t launch_sample(const DevBatch &b, const DevParams &p, const InstRec *i
   const int wg_waves = tile / 64;
   const int cap = waves_per_simd > 0 ? waves_per_simd : 8;
   const int wg_per_cu = std::max(1, (4 * cap + wg_waves - 1) / wg_waves);
-  int dev = 0, n_cu = 256, lds_cu = 163840, lds_block = 65536;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-    n_cu = 256;
-  if (hipDeviceGetAttribute(&lds_cu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, dev) != hipSuccess ||
-      lds_cu <= 0)
-    lds_cu = 163840;
-  if (hipDeviceGetAttribute(&lds_block, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess ||
-      lds_block <= 0)
-    lds_block = 65536;
-  const size_t lds = waves_per_simd > 0 ? (size_t)std::max(0, std::min(lds_cu / (wg_per_cu + 1) + 512, lds_block - 2048))
-                                        : 0;
+  size_t lds = waves_per_simd > 0 ? (size_t)std::max(0, std::min(lds_cu / (wg_per_cu + 1) + 512, lds_block - 2048)) : 0;
+  // (one instance is one launch group, whose workgroups may all be resident)
+  if (waves_per_simd == 0 && b.n_inst == 1 && !queue) {
+    const int t = tile / group_lanes(p.flags);
+    const int64_t wgs = (grid_samples + t - 1) / t;
+    if (wgs <= (int64_t)n_cu * 8) lds = even_lds(wgs);
+  }
   // the general 2D-3D loop's held targets
   const size_t lds_held = std::max(lds, (size_t)tile * kHeldKp * sizeof(float2));
-  const bool queue = (p.flags & PURSE_FLAG_WORK_QUEUE) != 0;
   auto grid_of = [&](int t) {
     const int64_t g = sample_grid(grid_samples, b.n_inst, t);
     return dim3((unsigned)(queue ? std::min<int64_t>(g, (int64_t)n_cu * wg_per_cu) : g));
