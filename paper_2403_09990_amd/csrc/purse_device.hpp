@@ -15,6 +15,17 @@ namespace purse {
 // ---------------------------------------------------------------------------
 // Philox4x64-10 (Salmon et al., SC'11): ten rounds of two 64x64->128-bit
 // multiplies, a word permutation and a key xor, Weyl key bump between rounds.
+// 64 x 64 -> 128 bits in four 32-bit multiply-adds with 64-bit addends (the
+// high and the low half formed by themselves take seven).
+__device__ __forceinline__ void mul64_wide(uint64_t a, uint64_t b, uint64_t &hi, uint64_t &lo) {
+  const uint32_t a0 = (uint32_t)a, a1 = (uint32_t)(a >> 32), b0 = (uint32_t)b, b1 = (uint32_t)(b >> 32);
+  const uint64_t p = (uint64_t)a0 * b0;
+  const uint64_t q = (uint64_t)a1 * b0 + (p >> 32);
+  const uint64_t r = (uint64_t)a0 * b1 + (uint32_t)q;
+  hi = (uint64_t)a1 * b1 + (q >> 32) + (r >> 32);
+  lo = (r << 32) | (uint32_t)p;
+}
+
 __device__ __forceinline__ void philox4x64_10(uint64_t c[4], uint64_t k0, uint64_t k1) {
 #pragma unroll
   for (int r = 0; r < 10; ++r) {
@@ -23,8 +34,9 @@ __device__ __forceinline__ void philox4x64_10(uint64_t c[4], uint64_t k0, uint64
       k1 += 0xBB67AE8584CAA73Bull;
     }
     const uint64_t m0 = 0xD2E7470EE14C6C93ull, m1 = 0xCA5A826395121157ull;
-    uint64_t hi0 = __umul64hi(m0, c[0]), lo0 = m0 * c[0];
-    uint64_t hi1 = __umul64hi(m1, c[2]), lo1 = m1 * c[2];
+    uint64_t hi0, lo0, hi1, lo1;
+    mul64_wide(m0, c[0], hi0, lo0);
+    mul64_wide(m1, c[2], hi1, lo1);
     uint64_t n0 = hi1 ^ c[1] ^ k0, n2 = hi0 ^ c[3] ^ k1;
     c[0] = n0;
     c[1] = lo1;
@@ -55,19 +67,27 @@ __device__ __forceinline__ float drcp(float x) { return __builtin_amdgcn_rcpf(x)
 __host__ __device__ inline double drcp(double x) { return 1.0 / x; }
 
 // sqrtf(x) and 1.f / x to the last bit from the hardware approximation and one
-// Newton step in fused arithmetic: equal to the correctly rounded functions for
-// every float of the stated ranges (compared over all of them), at 5 and 3
-// instructions instead of 17 and 11; outside the ranges the functions themselves.
-__device__ __forceinline__ float exact_sqrt(float x) {
+// Newton step in fused arithmetic: for |x| in [kShortMin, kShortMax] equal to the
+// correctly rounded functions (compared over all floats of the range), at 5
+// and 3 instructions instead of 17 and 11.  The exact_ forms take the functions
+// themselves outside the range.
+constexpr float kShortMin = 0x1p-100f, kShortMax = 0x1p100f;
+__device__ __forceinline__ float short_sqrt(float x) {
   const float y = __builtin_amdgcn_rsqf(x), s = x * y;
-  float r = fmaf(fmaf(-s, s, x), 0.5f * y, s);
-  if (__builtin_expect(!(x >= 0x1p-100f && x <= 0x1p126f), 0)) r = sqrtf(x);
+  return fmaf(fmaf(-s, s, x), 0.5f * y, s);
+}
+__device__ __forceinline__ float short_rcp(float x) {
+  const float y = __builtin_amdgcn_rcpf(x);
+  return fmaf(fmaf(-x, y, 1.f), y, y);
+}
+__device__ __forceinline__ float exact_sqrt(float x) {
+  float r = short_sqrt(x);
+  if (__builtin_expect(!(x >= kShortMin && x <= kShortMax), 0)) r = sqrtf(x);
   return r;
 }
 __device__ __forceinline__ float exact_rcp(float x) {
-  const float y = __builtin_amdgcn_rcpf(x);
-  float r = fmaf(fmaf(-x, y, 1.f), y, y);
-  if (__builtin_expect(!(fabsf(x) >= 0x1p-100f && fabsf(x) <= 0x1p100f), 0)) r = 1.f / x;
+  float r = short_rcp(x);
+  if (__builtin_expect(!(fabsf(x) >= kShortMin && fabsf(x) <= kShortMax), 0)) r = 1.f / x;
   return r;
 }
 
