@@ -160,7 +160,7 @@ __device__ __forceinline__ int find_active(const int *act, int n, int s) { retur
 
 }  // namespace
 
-__global__ void __launch_bounds__(kBwdBlock) k_bwd_megb(DevBatch b, DevParams p, const float *__restrict__ poses,
+__global__ void __launch_bounds__(kBwdBlock, 2) k_bwd_megb(DevBatch b, DevParams p, const float *__restrict__ poses,
                                                         const uint8_t *__restrict__ mask,
                                                         const int32_t *__restrict__ trace,
                                                         const double *__restrict__ g_radii,
@@ -169,15 +169,18 @@ __global__ void __launch_bounds__(kBwdBlock) k_bwd_megb(DevBatch b, DevParams p,
                                                         BwdRec *recs, float4 *ckpt_all, int ck) {
   __shared__ int act[kMaxActive];
   __shared__ int n_act_s, err_s, n_distinct_s;  // err_s: a BwdRec status (kBwdOk while the sweep may run)
-  __shared__ double cot[kMaxActive][12];
+  // (80 KB in all, so that two instances share a compute unit: the rotation
+  // cotangents are formed as they are written out)
+  __shared__ double cot_t[kMaxActive][3];      // translation cotangents of the active samples
+  __shared__ double cot_D[9];                  // the rotation radius' own term, of sample sD
   __shared__ float pact[kMaxActive][12];       // poses of the active samples
   __shared__ float4 qact[kMaxActive];          // their rotations as quaternions
   __shared__ uint8_t tslot[2 * kLdsTrace];     // trace as active-set slots
   __shared__ double jac[kBwdBlock][9];         // J_C of the steps of one chunk
   __shared__ double jadd[kBwdBlock][3];        // averaged-iterate terms of those steps, then rho terms
   __shared__ double gstep[kBwdBlock][3];       // g at each step of the chunk
-  __shared__ int cslot[kBwdBlock];             // active slot of each step of the chunk (rotation)
-  __shared__ int tslot_c[kBwdBlock];           // and of its translation winner
+  __shared__ int16_t cslot[kBwdBlock];         // active slot of each step of the chunk (rotation)
+  __shared__ int16_t tslot_c[kBwdBlock];       // and of its translation winner
   __shared__ double twt[kBwdBlock];            // translation weight of each step of the chunk
   __shared__ double tbar[3];                   // cotangent of t*
   __shared__ double rho[kMaxActive][3];        // tangent cotangents of active rotations
@@ -540,7 +543,8 @@ __global__ void __launch_bounds__(kBwdBlock) k_bwd_megb(DevBatch b, DevParams p,
       if (st != kBwdOk) err_s = st;
     }
   }
-  for (int k = tid; k < kMaxActive * 12; k += kBwdBlock) cot[k / 12][k % 12] = 0.0;
+  for (int k = tid; k < kMaxActive * 3; k += kBwdBlock) cot_t[k / 3][k % 3] = 0.0;
+  if (tid < 9) cot_D[tid] = 0.0;
   __syncthreads();
   const int n_act = n_act_s;
   // a radius sample outside the trace shifts the active set: stage the poses
@@ -585,11 +589,10 @@ __global__ void __launch_bounds__(kBwdBlock) k_bwd_megb(DevBatch b, DevParams p,
       D f = sqrt(f2);
       D x = f / (2.0 * sqrt(2.0));
       D kD = gD / (sqrt(2.0) * sqrt(fmax(1e-30, 1.0 - x * x)) * f);
-      const int pD = max(find_active(act, n_act, sD_s), 0);  // (inserted above)
       for (int k = 0; k < 9; ++k) {
         D v = kD * (Rstar[k] - RD[k]);
         G[k] += v;
-        cot[pD][k] -= v;
+        cot_D[k] -= v;
       }
     }
     // through R* = polar(S): S_bar = R* [b]x, b = (tr H I - H)^-1 v(R*^T G), H = sym(R*^T S)
@@ -633,7 +636,7 @@ __global__ void __launch_bounds__(kBwdBlock) k_bwd_megb(DevBatch b, DevParams p,
       const int pd = max(find_active(act, n_act, sd_s), 0);  // (inserted above)
       for (int r = 0; r < 3; ++r) {
         tb[r] += gd * dv[r] / dn;
-        cot[pd][9 + r] -= gd * dv[r] / dn;
+        cot_t[pd][r] -= gd * dv[r] / dn;
       }
     }
     for (int r = 0; r < 3; ++r) tbar[r] = tb[r];
@@ -734,14 +737,14 @@ __global__ void __launch_bounds__(kBwdBlock) k_bwd_megb(DevBatch b, DevParams p,
       // summing thread, selected by its slot)
       if (i <= i_hi) {
         for (int c = 0; c < 3; ++c) jadd[tid][c] = JR[c] * gstep[tid][0] + JR[3 + c] * gstep[tid][1] + JR[6 + c] * gstep[tid][2];
-        cslot[tid] = slot_of(2 * (i - 1));
+        cslot[tid] = (int16_t)slot_of(2 * (i - 1));
         D h = hsum;
         if (i > T - avg) {
           h = 0;
           for (int k = i; k <= T; ++k) h += 1.0 / (D)k;
         }
         twt[tid] = h / avg;
-        tslot_c[tid] = slot_of(2 * (i - 1) + 1);
+        tslot_c[tid] = (int16_t)slot_of(2 * (i - 1) + 1);
       } else {
         cslot[tid] = -1;
         tslot_c[tid] = -1;
@@ -769,7 +772,7 @@ __global__ void __launch_bounds__(kBwdBlock) k_bwd_megb(DevBatch b, DevParams p,
           rho[a][0] += v[0];
           rho[a][1] += v[1];
           rho[a][2] += v[2];
-          for (int r = 0; r < 3; ++r) cot[a][9 + r] += tbar[r] * v[3];
+          for (int r = 0; r < 3; ++r) cot_t[a][r] += tbar[r] * v[3];
         }
       }
       __syncthreads();
@@ -779,13 +782,17 @@ __global__ void __launch_bounds__(kBwdBlock) k_bwd_megb(DevBatch b, DevParams p,
       for (int k = 0; k < 3; ++k) rho[p0][k] += gvec[k];
     }
     __syncthreads();
-    // rho -> ambient cotangent R [rho]x / 2
-    for (int a = tid; a < n_act; a += kBwdBlock) {
+    // rho -> ambient cotangent R [rho]x / 2 (the active set is as large as the
+    // block, or smaller)
+    static_assert(kMaxActive <= kBwdBlock, "one active sample per thread");
+    const int pD = max(find_active(act, n_act, sD_s), 0);  // (inserted above)
+    if (tid < n_act) {
       D R[9], Wr[9], X[9];
-      load_act(a, R);
-      hat_d(rho[a], Wr);
+      load_act(tid, R);
+      hat_d(rho[tid], Wr);
       matmul3<D>(R, Wr, X);
-      for (int k = 0; k < 9; ++k) cot[a][k] += 0.5 * X[k];
+      for (int k = 0; k < 9; ++k) rec->cot[tid][k] = (tid == pD ? cot_D[k] : 0.0) + 0.5 * X[k];
+      for (int r = 0; r < 3; ++r) rec->cot[tid][9 + r] = cot_t[tid][r];
     }
   }
   __syncthreads();
@@ -798,7 +805,6 @@ __global__ void __launch_bounds__(kBwdBlock) k_bwd_megb(DevBatch b, DevParams p,
     rec->sd = sd_s;
   }
   const int n_out = err_s != kBwdOk ? 0 : n_act;
-  for (int k = tid; k < n_out * 12; k += kBwdBlock) rec->cot[k / 12][k % 12] = cot[k / 12][k % 12];
   for (int k = tid; k < n_out; k += kBwdBlock) rec->active[k] = act[k];
 }
 
@@ -923,6 +929,88 @@ __device__ void centre_fit_dual(const float *a, const float *cz, const float *L,
   for (int k = 0; k < 3; ++k) t[k] = Dual<double>(t0[k], 0.0);
   const ObsDual od{cz, L, i_d, c};
   gn_centre_2d<Dual<double>>(a, od, n, K, steps, z_min, R, t);
+}
+
+// The anchor's 3D-3D trajectory and its tangent along one direction (x, dx:
+// the centre's at first): the sampler's values, and per iteration the tangent
+// of the targets and of R = proj_SO3(M) in closed form, dR = R [y]x with
+// (tr(S) I - S) y = v(R^T dM), S = sym(R^T M), solved in float64.  (The
+// trajectory in dual numbers, Jacobi sweeps included, had half as many
+// instructions again; an instance with a remote anchor is the last workgroup
+// of k_bwd_frame.)
+__device__ void anchor_tangent_3d(const InstRec &I, const KpRec *__restrict__ kp, int i_d, const KpT<Dual<float>> &tk,
+                                  int n_iters, bool force64, Pose &x, Pose &dx) {
+  const int n = I.n_kp;
+  const float inv_n = 1.f / (float)n, band = ClampBand<Dual<float>>::v;
+  for (int it = 0; it < n_iters; ++it) {
+    float tt[3], dtt[3], M[9], dM[9], qs[3], dqs[3];
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+      tt[r] = x.t[r] + x.R[3 * r] * I.abar[0] + x.R[3 * r + 1] * I.abar[1] + x.R[3 * r + 2] * I.abar[2];
+      dtt[r] = dx.t[r] + dx.R[3 * r] * I.abar[0] + dx.R[3 * r + 1] * I.abar[1] + dx.R[3 * r + 2] * I.abar[2];
+      qs[r] = dqs[r] = 0.f;
+    }
+#pragma unroll
+    for (int k = 0; k < 9; ++k) M[k] = dM[k] = 0.f;
+    for (int i = 0; i < n; ++i) {
+      const KpRec k = kp[i];
+      const bool own = i == i_d;
+      const float dkb = own ? tk.kb.d : 0.f;
+      float d[3], dd[3], e[3], de[3];
+#pragma unroll
+      for (int r = 0; r < 3; ++r) {
+        d[r] = tt[r] - k.c[r];
+        dd[r] = dtt[r] - (own ? tk.c[r].d : 0.f);
+        e[r] = x.R[3 * r] * k.m[0] + x.R[3 * r + 1] * k.m[1] + x.R[3 * r + 2] * k.m[2] + d[r];
+        de[r] = dx.R[3 * r] * k.m[0] + dx.R[3 * r + 1] * k.m[1] + dx.R[3 * r + 2] * k.m[2] + dd[r];
+      }
+      const float r2 = e[0] * e[0] + e[1] * e[1] + e[2] * e[2], rs = drsqrt(r2);
+      const bool in = r2 <= k.kb2 * band;
+      const float s = in ? 1.f : k.kb * rs;
+      const float ds = in ? 0.f : rs * (dkb - s * rs * (e[0] * de[0] + e[1] * de[1] + e[2] * de[2]));
+#pragma unroll
+      for (int r = 0; r < 3; ++r) {
+        const float q = s * e[r] - d[r], dq = ds * e[r] + s * de[r] - dd[r];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+          M[3 * r + c] += q * k.m[c];
+          dM[3 * r + c] += dq * k.m[c];
+        }
+        qs[r] += q;
+        dqs[r] += dq;
+      }
+    }
+    if (force64 || !polar_so3_straight(M, x.R)) polar_fp64(M, x.R);
+    double R[9], Md[9], dMd[9], S[9], X[9], u[3], y[3], Yh[9], dR[9];
+#pragma unroll
+    for (int k = 0; k < 9; ++k) {
+      R[k] = x.R[k];
+      Md[k] = M[k];
+      dMd[k] = dM[k];
+    }
+    matmul_tn(R, Md, S);
+    matmul_tn(R, dMd, X);
+    vskew(X, u);
+    const double tr = S[0] + S[4] + S[8];
+    const double h00 = tr - S[0], h11 = tr - S[4], h22 = tr - S[8];
+    const double h01 = -0.5 * (S[1] + S[3]), h02 = -0.5 * (S[2] + S[6]), h12 = -0.5 * (S[5] + S[7]);
+    const double a00 = h11 * h22 - h12 * h12, a01 = h02 * h12 - h01 * h22, a02 = h01 * h12 - h02 * h11;
+    const double a11 = h00 * h22 - h02 * h02, a12 = h01 * h02 - h00 * h12, a22 = h00 * h11 - h01 * h01;
+    const double id = 1.0 / (h00 * a00 + h01 * a01 + h02 * a02);
+    y[0] = (a00 * u[0] + a01 * u[1] + a02 * u[2]) * id;
+    y[1] = (a01 * u[0] + a11 * u[1] + a12 * u[2]) * id;
+    y[2] = (a02 * u[0] + a12 * u[1] + a22 * u[2]) * id;
+    hat_d(y, Yh);
+    matmul3<double>(R, Yh, dR);
+#pragma unroll
+    for (int k = 0; k < 9; ++k) dx.R[k] = (float)dR[k];
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+      x.t[r] = tt[r] + qs[r] * inv_n - (x.R[3 * r] * I.abar[0] + x.R[3 * r + 1] * I.abar[1] + x.R[3 * r + 2] * I.abar[2]);
+      dx.t[r] =
+          dtt[r] + dqs[r] * inv_n - (dx.R[3 * r] * I.abar[0] + dx.R[3 * r + 1] * I.abar[1] + dx.R[3 * r + 2] * I.abar[2]);
+    }
+  }
 }
 
 // Tangents of the centre, pivot and anchor along every input direction of an
@@ -1137,16 +1225,28 @@ __global__ void __launch_bounds__(kMaxDirs) k_bwd_frame(DevBatch b, DevParams p,
     kpl.kp = kprec + I.kp_off;
     kpl.i_d = i_d;
     kp_tangent(I, kprec[I.kp_off + i_d], L + 4 * i_d, b.bounds[I.kp_off + i_d], p.kappa, c, kpl.tk);
-    PoseT<Dual<float>> x;
-    for (int k = 0; k < 9; ++k) x.R[k] = F.Rc[k];
-    for (int r = 0; r < 3; ++r) x.t[r] = F.tc[r];
-    int nfb = 0;
-    if (is2d)
+    if (is2d) {
+      PoseT<Dual<float>> x;
+      for (int k = 0; k < 9; ++k) x.R[k] = F.Rc[k];
+      for (int r = 0; r < 3; ++r) x.t[r] = F.tc[r];
+      int nfb = 0;
       run_trajectory<PURSE_KIND_2D3D>(I, F, kpl, x, p, false, nfb);
-    else
-      run_trajectory<PURSE_KIND_3D3D>(I, F, kpl, x, p, false, nfb);
-    for (int k = 0; k < 9; ++k) F.Ra[k] = Dual<float>(I.Ra[k], x.R[k].d);
-    for (int r = 0; r < 3; ++r) F.ta[r] = Dual<float>(I.ta[r], x.t[r].d);
+      for (int k = 0; k < 9; ++k) F.Ra[k] = Dual<float>(I.Ra[k], x.R[k].d);
+      for (int r = 0; r < 3; ++r) F.ta[r] = Dual<float>(I.ta[r], x.t[r].d);
+    } else {
+      Pose x, dx;
+      for (int k = 0; k < 9; ++k) {
+        x.R[k] = F.Rc[k].v;
+        dx.R[k] = F.Rc[k].d;
+      }
+      for (int r = 0; r < 3; ++r) {
+        x.t[r] = F.tc[r].v;
+        dx.t[r] = F.tc[r].d;
+      }
+      anchor_tangent_3d(I, kpl.kp, i_d, kpl.tk, p.n_iters, (p.flags & PURSE_FLAG_FORCE_FP64_POLAR) != 0, x, dx);
+      for (int k = 0; k < 9; ++k) F.Ra[k] = Dual<float>(I.Ra[k], dx.R[k]);
+      for (int r = 0; r < 3; ++r) F.ta[r] = Dual<float>(I.ta[r], dx.t[r]);
+    }
   }
   float *tan = tan_all + ((int64_t)j * max_dirs + d) * 27;
   for (int k = 0; k < 9; ++k) tan[k] = F.Rc[k].d;
