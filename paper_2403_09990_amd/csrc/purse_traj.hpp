@@ -747,8 +747,10 @@ __device__ __forceinline__ uint8_t run_trajectory(const InstRec &I, const FR &F,
 template <int G>
 __device__ __forceinline__ float lanes_sum(float x) {
   static_assert(G == 2 || G == 4, "groups within a quad");
-  x += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0xB1, 0xF, 0xF, false));  // quad_perm [1,0,3,2]
-  if (G == 4) x += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x4E, 0xF, 0xF, false));  // [2,3,0,1]
+  // (bound_ctrl lets the compiler fold each move into its add)
+  x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0xB1, 0xF, 0xF, true));  // quad_perm [1,0,3,2]
+  if (G == 4)
+    x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x4E, 0xF, 0xF, true));  // [2,3,0,1]
   return x;
 }
 
