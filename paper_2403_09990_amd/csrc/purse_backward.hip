@@ -24,6 +24,7 @@
 #include "purse_fit.hpp"
 #include "purse_geodesic.hpp"
 #include "purse_launch.hpp"
+#include "purse_near.hpp"
 #include "purse_traj.hpp"
 
 namespace purse {
@@ -63,26 +64,6 @@ __device__ __forceinline__ void hat_d(const D w[3], D W[9]) {
   W[6] = -w[1];
   W[7] = w[0];
   W[8] = 0;
-}
-
-// (1 - cos x) / x^2 and (x - sin x) / x^3 from z = x^2: their Taylor series for
-// |x| <= 1/2 (truncation below 1e-17), else by half angles.
-__device__ __forceinline__ void exp_coeffs_bd(D z, D &B, D &Dc, D &A) {
-  if (z <= 0.25) {
-    B = 0.5 + z * (-1.0 / 24 + z * (1.0 / 720 + z * (-1.0 / 40320 + z * (1.0 / 3628800 + z * (-1.0 / 479001600 +
-        z * (1.0 / 87178291200.0))))));
-    Dc = 1.0 / 6 + z * (-1.0 / 120 + z * (1.0 / 5040 + z * (-1.0 / 362880 + z * (1.0 / 39916800 +
-         z * (-1.0 / 6227020800.0 + z * (1.0 / 1307674368000.0))))));
-    A = 1.0 - z * Dc;
-  } else {
-    const D x = sqrt(z);
-    D s, c, sh, ch;
-    sincos(x, &s, &c);
-    sincos(0.5 * x, &sh, &ch);
-    A = s / x;
-    B = 2.0 * sh * sh / z;
-    Dc = (1.0 - A) / z;
-  }
 }
 
 // (1 - (x / 2) cot(x / 2)) / x^2 from z = x^2 (coefficients |B_2k| / (2k)!).
@@ -1374,52 +1355,6 @@ __global__ void __launch_bounds__(64) k_bwd_traj(DevBatch b, DevParams p, const 
 // value, addition being commutative), so each lane carries 1/G of the
 // keypoint work and a small batch of active samples fills G times more
 // wavefronts.  The arithmetic per keypoint is that of gn_pass2d.
-// (bound_ctrl lets the compiler fold a float's move into its add)
-template <int CTRL>
-__device__ __forceinline__ float dpp_of(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
-}
-template <int CTRL>
-__device__ __forceinline__ double dpp_of(double v) {
-  const long long b = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xF, 0xF, true);
-  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xF, 0xF, true);
-  return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
-}
-
-template <int G, typename T>
-__device__ __forceinline__ T group_sum(T x) {
-  static_assert(G == 2 || G == 4 || G == 8 || G == 16, "lane groups within a row of 16");
-  x += dpp_of<0xB1>(x);                // quad_perm [1,0,3,2]
-  if (G >= 4) x += dpp_of<0x4E>(x);    // [2,3,0,1]
-  if (G >= 8) x += dpp_of<0x141>(x);   // half mirror
-  if (G >= 16) x += dpp_of<0x140>(x);  // row mirror
-  return x;
-}
-
-// The sums of N values over a group of 16, a step of nine values at a time: a
-// lone wavefront otherwise waits in each value's chain of four dependent steps
-// (one instance of 12 keypoints, 100 iterations: 1.36 -> 1.23 ms; by the
-// float64 4x4x4 matrix instruction against ones, 1.62).
-template <int CTRL, int N, typename T>
-__device__ __forceinline__ void group_step(T *x) {
-  T y[N];
-#pragma unroll
-  for (int k = 0; k < N; ++k) y[k] = dpp_of<CTRL>(x[k]);
-#pragma unroll
-  for (int k = 0; k < N; ++k) x[k] += y[k];
-  __builtin_amdgcn_sched_barrier(0);
-}
-template <int N, typename T>
-__device__ __forceinline__ void group_sums(T *x) {
-  constexpr int M = N < 9 ? N : 9;
-  group_step<0xB1, M>(x);
-  group_step<0x4E, M>(x);
-  group_step<0x141, M>(x);
-  group_step<0x140, M>(x);
-  if constexpr (N > M) group_sums<N - M>(x + M);
-}
-
 template <int G>
 __device__ __forceinline__ Dual<float> group_sum(Dual<float> x) {
   return Dual<float>(group_sum<G>(x.v), group_sum<G>(x.d));
@@ -1635,83 +1570,6 @@ __host__ __device__ constexpr size_t rev_lds(int passes, int iters) {
          (size_t)kRevSamples * kRevGroup * (size_t)(iters > 0 ? iters : 1);
 }
 
-// Reciprocal and reciprocal square root of the sweeps' recomputation: in
-// float64 the hardware approximation (2^-26 or better) and two Newton steps, a
-// few units in the last place and a third of the instructions of the
-// correctly rounded forms (arguments are depths, squared radii and pivots, far
-// from the ends of the range).
-__device__ __forceinline__ float rev_rcp(float x) { return drcp(x); }
-__device__ __forceinline__ float rev_rsq(float x) { return drsqrt(x); }
-__device__ __forceinline__ double rev_rcp(double x) {
-  double r = __builtin_amdgcn_rcp(x);
-  r = fma(fma(-x, r, 1.0), r, r);
-  return fma(fma(-x, r, 1.0), r, r);
-}
-__device__ __forceinline__ double rev_rsq(double x) {
-  double r = __builtin_amdgcn_rsq(x);
-  r = fma(0.5 * fma(-x * r, r, 1.0), r, r);
-  return fma(0.5 * fma(-x * r, r, 1.0), r, r);
-}
-
-// Exp of so(3) in float64: the Taylor series of its coefficients for angles up
-// to 1/2 (no square root or trigonometric call), else the general form.
-__device__ __forceinline__ void rev_exp_so3(const double w[3], double E[9]) {
-  const double z = w[0] * w[0] + w[1] * w[1] + w[2] * w[2];
-  if (z <= 0.25) {
-    double B, Dc, A;
-    exp_coeffs_bd(z, B, Dc, A);
-    const double C = 1.0 - z * B;
-    const double b0 = B * w[0], b1 = B * w[1], a0 = A * w[0], a1 = A * w[1], a2 = A * w[2];
-    E[0] = C + b0 * w[0];
-    E[4] = C + b1 * w[1];
-    E[8] = C + B * w[2] * w[2];
-    E[1] = b0 * w[1] - a2;
-    E[3] = b0 * w[1] + a2;
-    E[2] = b0 * w[2] + a1;
-    E[6] = b0 * w[2] - a1;
-    E[5] = b1 * w[2] - a0;
-    E[7] = b1 * w[2] + a0;
-  } else {
-    exp_so3<double>(w, E);
-  }
-}
-
-// The Gauss-Newton solve and update of the recomputation, in float64: false
-// (and the pose as it was) when a pivot is not positive.
-__device__ __forceinline__ bool rev_step(const double A[21], const double g[6], const double o[3], double R[9],
-                                         double t[3]) {
-  double L[21], dinv[6], d[6];
-  bool ok = true;
-#pragma unroll
-  for (int j = 0; j < 6; ++j) {
-    double v = A[tri(j, j)];
-#pragma unroll
-    for (int k = 0; k < j; ++k) v -= L[tri(j, k)] * L[tri(j, k)];
-    ok = ok && v > 0.0;
-    dinv[j] = rev_rsq(v);
-#pragma unroll
-    for (int i = j + 1; i < 6; ++i) {
-      double x = A[tri(i, j)];
-#pragma unroll
-      for (int k = 0; k < j; ++k) x -= L[tri(i, k)] * L[tri(j, k)];
-      L[tri(i, j)] = x * dinv[j];
-    }
-  }
-  if (!ok) return false;
-  chol6_subst<double>(L, dinv, g, d);  // (it reads no diagonal entry of L)
-  double E[9], Rn[9], arm[3], e[3];
-  rev_exp_so3(d, E);
-  matmul3(E, R, Rn);
-#pragma unroll
-  for (int r = 0; r < 3; ++r) arm[r] = t[r] - o[r];
-  matvec3(E, arm, e);
-#pragma unroll
-  for (int r = 0; r < 3; ++r) t[r] = e[r] + o[r] + d[3 + r];
-#pragma unroll
-  for (int k = 0; k < 9; ++k) R[k] = Rn[k];
-  return true;
-}
-
 // R <- proj_SO3(M) in float64 from the previous iteration's rotation in R, by
 // Newton steps of max tr(R^T M) (polar_newton's): near the maximum their
 // error squares, so a last step below 1e-8 leaves rounding.  When they leave
@@ -1734,11 +1592,11 @@ __device__ __forceinline__ void rev_polar(const double M[9], double R[9]) {
     const double det = h00 * a00 + h01 * a01 + h02 * a02;
     // positive definite (leading minors), and not nearly singular
     if (!(h00 > 0.0 && a22 > 0.0 && det > 1e-9 * tr * tr * tr)) break;
-    const double id = rev_rcp(det);
+    const double id = near_rcp(det);
     const double w[3] = {(a00 * g[0] + a01 * g[1] + a02 * g[2]) * id, (a01 * g[0] + a11 * g[1] + a12 * g[2]) * id,
                          (a02 * g[0] + a12 * g[1] + a22 * g[2]) * id};
     double E[9], Xn[9];
-    rev_exp_so3(w, E);
+    near_exp_so3(w, E);
     matmul3(X, E, Xn);
 #pragma unroll
     for (int k = 0; k < 9; ++k) X[k] = Xn[k];
@@ -1776,7 +1634,7 @@ __device__ __forceinline__ void rev_project2d(const T R[9], const T t[3], const 
 #pragma unroll
   for (int r = 0; r < 3; ++r)
     P[r] = R[3 * r] * T(k.m[0]) + R[3 * r + 1] * T(k.m[1]) + R[3 * r + 2] * T(k.m[2]) + t[r];
-  iz = rev_rcp(P[2]);
+  iz = near_rcp(P[2]);
   u = T(K[0]) * (P[0] * iz) + T(K[2]);
   v = T(K[1]) * (P[1] * iz) + T(K[3]);
 }
@@ -1819,7 +1677,7 @@ __device__ __forceinline__ bool rev_normal_eqs(const KpRec *__restrict__ kp, int
       const T et0 = w[0] * e0 + w[1] * e1, et1 = w[2] * e1;
       const T r2 = et0 * et0 + et1 * et1;
       if (!use_cl && !(r2 <= T(k.kb2) * T(band))) cl |= 1u << rr;
-      const T s = ((cl >> rr) & 1u) ? T(k.kb) * rev_rsq(r2) : T(1);
+      const T s = ((cl >> rr) & 1u) ? T(k.kb) * near_rsq(r2) : T(1);
       rt0 = (s - T(1)) * et0;
       rt1 = (s - T(1)) * et1;
     } else {
@@ -1829,7 +1687,7 @@ __device__ __forceinline__ bool rev_normal_eqs(const KpRec *__restrict__ kp, int
       const T et0 = w[0] * e0 + w[1] * e1, et1 = w[2] * e1;
       const T r2 = et0 * et0 + et1 * et1;
       if (!use_cl && !(r2 <= T(k.kb2) * T(band))) cl |= 1u << rr;
-      const T s = ((cl >> rr) & 1u) ? T(k.kb) * rev_rsq(r2) : T(1);
+      const T s = ((cl >> rr) & 1u) ? T(k.kb) * near_rsq(r2) : T(1);
       const T r0 = T(k.c[0]) + s * e0 - u, r1 = T(k.c[1]) + s * e1 - v;
       rt0 = w[0] * r0 + w[1] * r1;
       rt1 = w[2] * r1;
@@ -2299,10 +2157,10 @@ __global__ void __launch_bounds__(64) k_bwd_rev2d(DevBatch b, DevParams p, const
       for (int gs = 0; gs < p.n_gn && ok; ++gs) {
         const int ps = itr * p.n_gn + gs;
         if (q < 12) tape[12 * ps + q] = rev_entry(x, q);
-        double A[21], g[6];
+        double A[21], g[6], d[6];
         ok = gs == 0 ? rev_normal_eqs<true, double>(kp, n, q, I.K, ocd, p.z_min, band, xk, x, A, g, cl, false)
                      : rev_normal_eqs<false, double>(kp, n, q, I.K, ocd, p.z_min, band, xk, x, A, g, cl, true);
-        ok = ok && rev_step(A, g, ocd, x.R, x.t);
+        ok = ok && near_step(A, g, ocd, x.R, x.t, d);
       }
       clb[itr * kRevGroup + q] = (uint8_t)cl;
     }
@@ -2541,7 +2399,7 @@ __device__ __forceinline__ void rev3d_sums(const KpRec *__restrict__ kp, int n, 
     }
     const T r2 = e[0] * e[0] + e[1] * e[1] + e[2] * e[2];
     if (!use_cl && !(r2 <= T(k.kb2) * T(band))) cl |= 1u << rr;
-    const T sc = ((cl >> rr) & 1u) ? T(k.kb) * rev_rsq(r2) : T(1);
+    const T sc = ((cl >> rr) & 1u) ? T(k.kb) * near_rsq(r2) : T(1);
 #pragma unroll
     for (int r = 0; r < 3; ++r) {
       const T qq = sc * e[r] - d[r];

@@ -1,10 +1,10 @@
 // Per-instance prologue: validation, keypoint records, centre fit (float64),
-// pivot and feasible anchor.  Two wavefronts per instance: validation and the
-// keypoint records take one keypoint per lane of wavefront 0; the 2D-3D
-// centre fit is a float64 Gauss-Newton iteration from two starts, one start
-// per wavefront (formed by lane 0, iterated with one keypoint per lane), so
-// the two run on different SIMDs at once; the rest (Arun's fit, the pivot,
-// the anchor) is serial in lane 0 of wavefront 0.
+// pivot and feasible anchor.  Two wavefronts per instance: validation, the
+// keypoint records and the anchor test take one keypoint per lane of wavefront
+// 0; the 2D-3D centre fit is a float64 Gauss-Newton iteration from two starts,
+// one per wavefront, so the two run on different SIMDs at once; the rest (the
+// polar factor of Arun's fit, the pivot, a remote anchor's trajectory) is serial
+// in lane 0 of wavefront 0.
 #include "purse_bwd_check.hpp"
 #include "purse_fit.hpp"
 #include "purse_launch.hpp"
@@ -20,6 +20,7 @@ __global__ void __launch_bounds__(kPrologueBlock) k_prologue(DevBatch b, DevPara
   const int tid = threadIdx.x;
   __shared__ double w_s[3 * PURSE_MAX_KP];  // whitening factors of the keypoints
   __shared__ double fit_R[2][9], fit_t[2][3], fit_cost[2];
+  __shared__ double dlt_buf[PURSE_MAX_KP][7];
   __shared__ int fit_good[2], stage;         // stage: 0 invalid, 1 valid 3D-3D, 2 valid 2D-3D
   __shared__ int fp_n;                       // keypoints the data fingerprint covers
   __shared__ int64_t fp_ko;
@@ -131,48 +132,41 @@ __global__ void __launch_bounds__(kPrologueBlock) k_prologue(DevBatch b, DevPara
   }
   if (st == 2) {
     // Gauss-Newton from the DLT (wavefront 0) and from the weak-perspective
-    // fit (wavefront 1): lane 0 forms the start, the whole wavefront iterates
+    // fit (wavefront 1)
     const int f = tid >> 6;
     const int n = b.n_kp[j];
     const int64_t ko = b.kp_off[j];
     const float *a = b.model_pts + 3 * ko, *c = b.centres + 3 * ko;
     const float K[4] = {b.intrinsics[4 * j], b.intrinsics[4 * j + 1], b.intrinsics[4 * j + 2], b.intrinsics[4 * j + 3]};
     const ObsCached obs{c, w_s};
-    if ((tid & 63) == 0) {
-      double R[9], t[3];
-      const bool ok = f == 0 ? dlt_2d(a, c, n, K, R, t) : affine_2d(a, c, n, K, R, t);
-      fit_good[f] = ok;
-      for (int k = 0; k < 9; ++k) fit_R[f][k] = R[k];
-      for (int k = 0; k < 3; ++k) fit_t[f][k] = t[k];
-    }
-    __syncthreads();
-    bool ok = fit_good[f] != 0;
     double R[9], t[3];
-    for (int k = 0; k < 9; ++k) R[k] = fit_R[f][k];
-    for (int k = 0; k < 3; ++k) t[k] = fit_t[f][k];
-    __syncthreads();
+    bool ok = f == 0 ? dlt_2d_wave(a, c, n, K, dlt_buf, R, t) : affine_2d_wave(a, c, n, K, R, t);
     if (ok) ok = gn_centre_2d_wave(a, obs, n, K, p.centre_gn, (double)p.z_min, R, t);
+    const double cost = ok ? cost_2d_wave(a, obs, n, K, R, t) : 0.0;
     if ((tid & 63) == 0) {
       fit_good[f] = ok;
       if (ok) {
         for (int k = 0; k < 9; ++k) fit_R[f][k] = R[k];
         for (int k = 0; k < 3; ++k) fit_t[f][k] = t[k];
-        fit_cost[f] = cost_2d_obs(a, obs, n, K, R, t);
+        fit_cost[f] = cost;
       }
     }
   }
   __syncthreads();
-  if (tid != 0) return;
+  if (tid >= 64) return;
   if (st == 0) {
-    inst[j] = I;
-    inst_status[j] = I.status;
+    if (tid == 0) {
+      inst[j] = I;
+      inst_status[j] = I.status;
+    }
     return;
   }
-  const int n = I.n_kp;
+  const int n = b.n_kp[j];
   const bool is2d = st == 2;
-  const float *a = b.model_pts + 3 * I.kp_off;
-  const float *c = b.centres + 3 * I.kp_off;
-  KpRec *kp = kprec + I.kp_off;
+  const int64_t kp_off = b.kp_off[j];
+  const float *a = b.model_pts + 3 * kp_off;
+  const float *c = b.centres + 3 * kp_off;
+  KpRec *kp = kprec + kp_off;
   // ---- centre fit: the successful fit with the lower cost (ties: the DLT one)
   double Rd[9], td[3];
   bool fit_ok = true;
@@ -183,14 +177,23 @@ __global__ void __launch_bounds__(kPrologueBlock) k_prologue(DevBatch b, DevPara
     for (int k = 0; k < 9; ++k) Rd[k] = fit_ok ? fit_R[f][k] : (k % 4 == 0 ? 1.0 : 0.0);
     for (int k = 0; k < 3; ++k) td[k] = fit_ok ? fit_t[f][k] : 0.0;
   } else {
-    kabsch_centre(a, c, n, Rd, td);
+    if (tid == 0) {
+      kabsch_centre(a, c, n, Rd, td);
+      for (int k = 0; k < 9; ++k) fit_R[0][k] = Rd[k];
+      for (int k = 0; k < 3; ++k) fit_t[0][k] = td[k];
+    }
+    wave_lds_fence();
+    for (int k = 0; k < 9; ++k) Rd[k] = fit_R[0][k];
+    for (int k = 0; k < 3; ++k) td[k] = fit_t[0][k];
   }
   for (int k = 0; k < 9; ++k) I.Rc[k] = (float)Rd[k];
   for (int r = 0; r < 3; ++r) I.tc[r] = (float)td[r];
   if (!fit_ok) {
-    I.status = PURSE_INST_FIT_FAILED;
-    inst[j] = I;
-    inst_status[j] = I.status;
+    if (tid == 0) {
+      I.status = PURSE_INST_FIT_FAILED;
+      inst[j] = I;
+      inst_status[j] = I.status;
+    }
     return;
   }
   double oc[3];
@@ -202,8 +205,16 @@ __global__ void __launch_bounds__(kPrologueBlock) k_prologue(DevBatch b, DevPara
   for (int k = 0; k < 9; ++k) xc.R[k] = I.Rc[k];
   for (int r = 0; r < 3; ++r) xc.t[r] = I.tc[r];
   const KpPlain kpl{kp};
-  bool inside = is2d ? feasible<PURSE_KIND_2D3D>(I, kpl, xc, p, p.kappa)
-                     : feasible<PURSE_KIND_3D3D>(I, kpl, xc, p, p.kappa);
+  bool inside = true;  // keypoint `tid` (its record is this lane's own store)
+  if (tid < n) {
+    const float abar[3] = {(float)ab[0], (float)ab[1], (float)ab[2]};
+    const float K[4] = {is2d ? b.intrinsics[4 * j] : 0.f, is2d ? b.intrinsics[4 * j + 1] : 0.f,
+                        is2d ? b.intrinsics[4 * j + 2] : 0.f, is2d ? b.intrinsics[4 * j + 3] : 0.f};
+    inside = is2d ? feasible2d(KpPlain{kp + tid}, 1, K, xc, p.z_min, p.kappa)
+                  : feasible3d(KpPlain{kp + tid}, 1, abar, xc, p.kappa);
+  }
+  inside = __ballot(!inside) == 0ull;
+  if (tid != 0) return;
   if (inside) {
     I.has_anchor = 1;
     for (int k = 0; k < 9; ++k) I.Ra[k] = xc.R[k];
