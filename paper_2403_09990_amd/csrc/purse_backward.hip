@@ -1563,12 +1563,15 @@ constexpr int kRevPerLane = (PURSE_MAX_KP + kRevGroup - 1) / kRevGroup;
 constexpr int kRevSamples = 64 / kRevGroup;  // active samples per wavefront
 constexpr size_t kRevLds = 65536;              // LDS of a reverse-sweep workgroup at most
 
-// LDS of a reverse-sweep workgroup: per sample, a float32 pose per pass (the
-// tape) and a byte of clamp bits per lane and iteration.
-__host__ __device__ constexpr size_t rev_lds(int passes, int iters) {
-  return sizeof(float) * 12 * kRevSamples * (size_t)(passes > 0 ? passes : 1) +
+// LDS of a reverse-sweep workgroup: per sample, a row of `row` floats per pass
+// (the tape) and a byte of clamp bits per lane and iteration.
+__host__ __device__ constexpr size_t rev_lds(int passes, int iters, int row) {
+  return sizeof(float) * row * kRevSamples * (size_t)(passes > 0 ? passes : 1) +
          (size_t)kRevSamples * kRevGroup * (size_t)(iters > 0 ? iters : 1);
 }
+constexpr int kRevPoseRow = 12;                // a pass's input pose
+constexpr int kRevSolveRow = kRevPoseRow + 24; // and its factor: 15 entries, 6 reciprocal pivots
+constexpr int kRevPolarRow = kRevPoseRow + 12; // (3D-3D) and its M
 
 // R <- proj_SO3(M) in float64 from the previous iteration's rotation in R, by
 // Newton steps of max tr(R^T M) (polar_newton's): near the maximum their
@@ -1639,15 +1642,17 @@ __device__ __forceinline__ void rev_project2d(const T R[9], const T t[3], const 
   v = T(K[1]) * (P[1] * iz) + T(K[3]);
 }
 
-// Entry q of a pose as its 12 floats (selects: an array index by lane would put
-// the pose into scratch memory).
-__device__ __forceinline__ float rev_entry(const RevPoseT<double> &x, int q) {
-  double v = x.R[0];
+// N floats to the tape, by one lane of the group.
+template <int N>
+__device__ __forceinline__ void rev_put(float *row, const double *v) {
+  static_assert(N % 4 == 0, "whole float4s");
 #pragma unroll
-  for (int k = 1; k < 9; ++k) v = q == k ? x.R[k] : v;
-#pragma unroll
-  for (int r = 0; r < 3; ++r) v = q == 9 + r ? x.t[r] : v;
-  return (float)v;
+  for (int k = 0; k < N; k += 4)
+    reinterpret_cast<float4 *>(row)[k / 4] = make_float4((float)v[k], (float)v[k + 1], (float)v[k + 2], (float)v[k + 3]);
+}
+__device__ __forceinline__ void rev_put_pose(float *row, const RevPoseT<double> &x) {
+  const double v[12] = {x.R[0], x.R[1], x.R[2], x.R[3], x.R[4], x.R[5], x.R[6], x.R[7], x.R[8], x.t[0], x.t[1], x.t[2]};
+  rev_put<12>(row, v);
 }
 
 // Group-summed normal equations of one pass at x (targets from xk for the
@@ -1655,7 +1660,7 @@ __device__ __forceinline__ float rev_entry(const RevPoseT<double> &x, int q) {
 // z_min.  Projection decisions: bit rr of cl is lane q's keypoint
 // q + kRevGroup rr; taken from cl when use_cl, else decided here and
 // recorded in cl.
-template <bool FIRST, typename T>
+template <bool FIRST, typename T, bool MATRIX = true>
 __device__ __forceinline__ bool rev_normal_eqs(const KpRec *__restrict__ kp, int n, int q, const float K[4],
                                                const T oc[3], float z_min, float band, const RevPoseT<T> &xk,
                                                const RevPoseT<T> &x, T A[21], T g[6], uint32_t &cl, bool use_cl) {
@@ -1696,7 +1701,7 @@ __device__ __forceinline__ bool rev_normal_eqs(const KpRec *__restrict__ kp, int
     gn_accumulate<T>(P, pt, iz, T(K[0]), T(K[1]), w, rt0, rt1, A, g);
   }
   static_assert(kRevGroup == 16, "group_sums");
-  group_sums<21>(A);
+  if constexpr (MATRIX) group_sums<21>(A);  // (else A is not formed)
   group_sums<6>(g);
   return group_and<kRevGroup>(ok);
 }
@@ -1966,15 +1971,27 @@ __device__ __forceinline__ void rev_keypoints(const KpRec *__restrict__ kp, int 
 
 // One pass of the reverse sweep: the normal equations at x recomputed, the
 // update's and the solve's adjoints, the keypoints' adjoints; xb holds the
-// cotangent of the pass's output on entry and of its input on return.
-template <bool FIRST>
+// cotangent of the pass's output on entry and of its input on return.  (SOLVE:
+// the factor is read from the tape, and only the right side formed at x: the
+// step has to be the one of the residuals that the adjoints below see.)
+template <bool FIRST, bool SOLVE>
 __device__ __forceinline__ void rev_pass(const KpRec *__restrict__ kp, int n, int q, const float K[4],
-                                         const float oc[3], float z_min, uint32_t clbits, const RevPose &xk,
+                                         const float oc[3], float z_min, uint32_t clbits, const float *solve,
+                                         const RevPose &xk,
                                          const RevPose &x, RevPose &xb, RevPose &xkb, float ob_u[3],
                                          float kb[kRevPerLane][6]) {
   float A[21], g[6], L[21], dinv[6], d[6];
-  rev_normal_eqs<FIRST, float>(kp, n, q, K, oc, z_min, 1.f, xk, x, A, g, clbits, true);
-  chol6_factor<float>(A, L, dinv);
+  rev_normal_eqs<FIRST, float, !SOLVE>(kp, n, q, K, oc, z_min, 1.f, xk, x, A, g, clbits, true);
+  if constexpr (SOLVE) {
+#pragma unroll
+    for (int i = 1, m = 0; i < 6; ++i)
+#pragma unroll
+      for (int c = 0; c < i; ++c, ++m) L[tri(i, c)] = solve[m];
+#pragma unroll
+    for (int m = 0; m < 6; ++m) dinv[m] = solve[15 + m];
+  } else {
+    chol6_factor<float>(A, L, dinv);
+  }
   chol6_subst<float>(L, dinv, g, d);
   RevPose xin;
   float db[6];
@@ -2110,7 +2127,14 @@ __device__ __forceinline__ bool rev_feasible(const KpRec *__restrict__ kp, int n
 }
 
 // One wavefront per kRevSamples active samples; dynamic LDS: the tape,
-// kRevSamples x n_iters x n_gn poses of 12 floats.
+// kRevSamples x n_iters x n_gn rows.  SOLVE: the rows keep each pass's factor
+// too, so that the sweep does not sum and factor the normal matrix again, at 144
+// bytes a row: for calls of so few samples that a compute unit holds one
+// wavefront anyway (one instance of 12 keypoints, 100 iterations: 1.22 -> 1.13 ms).
+// (With the step on the tape as well the sweep was another 0.1 ms shorter and up
+// to eight times as far off: it then differentiates a step that is not the one
+// of the rounded pose.)
+template <bool SOLVE>
 __global__ void __launch_bounds__(64) k_bwd_rev2d(DevBatch b, DevParams p, const InstRec *__restrict__ inst,
                                                   const KpRec *__restrict__ kprec, const BwdRec *recs,
                                                   const int64_t *__restrict__ item_off,
@@ -2119,8 +2143,9 @@ __global__ void __launch_bounds__(64) k_bwd_rev2d(DevBatch b, DevParams p, const
   const int64_t total = item_off[b.n_inst];
   const int lane = threadIdx.x, grp = lane / kRevGroup, q = lane % kRevGroup;
   const int passes = p.n_iters * p.n_gn;
-  float *tape = tape_all + (int64_t)grp * passes * 12;
-  uint8_t *clb = reinterpret_cast<uint8_t *>(tape_all + (int64_t)kRevSamples * (passes > 0 ? passes : 1) * 12) +
+  constexpr int kRow = SOLVE ? kRevSolveRow : kRevPoseRow;
+  float *tape = tape_all + (int64_t)grp * passes * kRow;
+  uint8_t *clb = reinterpret_cast<uint8_t *>(tape_all + (int64_t)kRevSamples * (passes > 0 ? passes : 1) * kRow) +
                  (int64_t)grp * (p.n_iters > 0 ? p.n_iters : 1) * kRevGroup;
   const float band = ClampBand<Dual<float>>::v;
   for (int64_t wv = blockIdx.x; wv * kRevSamples < total; wv += gridDim.x) {
@@ -2156,11 +2181,25 @@ __global__ void __launch_bounds__(64) k_bwd_rev2d(DevBatch b, DevParams p, const
       uint32_t cl = 0u;
       for (int gs = 0; gs < p.n_gn && ok; ++gs) {
         const int ps = itr * p.n_gn + gs;
-        if (q < 12) tape[12 * ps + q] = rev_entry(x, q);
-        double A[21], g[6], d[6];
+        float *row = tape + kRow * ps;
+        if (q == 0) rev_put_pose(row, x);
+        double A[21], g[6], L[21], dinv[6], d[6];
         ok = gs == 0 ? rev_normal_eqs<true, double>(kp, n, q, I.K, ocd, p.z_min, band, xk, x, A, g, cl, false)
                      : rev_normal_eqs<false, double>(kp, n, q, I.K, ocd, p.z_min, band, xk, x, A, g, cl, true);
-        ok = ok && near_step(A, g, ocd, x.R, x.t, d);
+        ok = ok && near_solve(A, g, L, dinv, d);
+        if (!ok) break;
+        near_update(d, ocd, x.R, x.t);
+        if (SOLVE && q == 0) {
+          double v[24];
+          v[21] = v[22] = v[23] = 0.0;
+#pragma unroll
+          for (int i = 1, m = 0; i < 6; ++i)
+#pragma unroll
+            for (int c = 0; c < i; ++c, ++m) v[m] = L[tri(i, c)];
+#pragma unroll
+          for (int m = 0; m < 6; ++m) v[15 + m] = dinv[m];
+          rev_put<24>(row + kRevPoseRow, v);
+        }
       }
       clb[itr * kRevGroup + q] = (uint8_t)cl;
     }
@@ -2273,7 +2312,7 @@ __global__ void __launch_bounds__(64) k_bwd_rev2d(DevBatch b, DevParams p, const
       rev_reorthonormalise(xe.R, xb.R);
       for (int itr = p.n_iters - 1; itr >= 0; --itr) {
         RevPose xk, xkb;
-        const float *tk = tape + 12 * (itr * p.n_gn);
+        const float *tk = tape + kRow * (itr * p.n_gn);
         const uint32_t clbi = clb[itr * kRevGroup + q];
 #pragma unroll
         for (int m = 0; m < 9; ++m) {
@@ -2286,15 +2325,15 @@ __global__ void __launch_bounds__(64) k_bwd_rev2d(DevBatch b, DevParams p, const
           xkb.t[m] = 0.f;
         }
         for (int gs = p.n_gn - 1; gs >= 1; --gs) {
-          const float *tx = tape + 12 * (itr * p.n_gn + gs);
+          const float *tx = tape + kRow * (itr * p.n_gn + gs);
           RevPose xin;
 #pragma unroll
           for (int m = 0; m < 9; ++m) xin.R[m] = tx[m];
 #pragma unroll
           for (int m = 0; m < 3; ++m) xin.t[m] = tx[9 + m];
-          rev_pass<false>(kp, n, q, I.K, oc, p.z_min, clbi, xk, xin, xb, xkb, ob_u, kb);
+          rev_pass<false, SOLVE>(kp, n, q, I.K, oc, p.z_min, clbi, tx + kRevPoseRow, xk, xin, xb, xkb, ob_u, kb);
         }
-        rev_pass<true>(kp, n, q, I.K, oc, p.z_min, clbi, xk, xk, xb, xkb, ob_u, kb);
+        rev_pass<true, SOLVE>(kp, n, q, I.K, oc, p.z_min, clbi, tk + kRevPoseRow, xk, xk, xb, xkb, ob_u, kb);
       }
       // the start: even s rotate the centre by E about the pivot, odd s shift it
       if ((s & 1) == 0) {
@@ -2447,11 +2486,21 @@ __device__ __forceinline__ void rev_polar_adjoint(const float M[9], const float 
 // iteration's output (whose rotation is Rn) on entry and of its input x on
 // return; the keypoints' cotangents (c_bar in kb[.][0..2], kappa beta in
 // kb[.][3]) accumulate per lane.
+template <bool KEEP>
 __device__ __forceinline__ void rev3d_iter(const KpRec *__restrict__ kp, int n, int q, const float abar[3],
-                                           uint32_t clbits, const RevPose &x, const float Rn[9], RevPose &xb,
-                                           float kb[kRevPerLane][6]) {
-  float tt[3], M[9], qs[3];
-  rev3d_sums<float>(kp, n, q, abar, 1.f, x, tt, M, qs, clbits, true);
+                                           uint32_t clbits, const RevPose &x, const float *Mt, const float Rn[9],
+                                           RevPose &xb, float kb[kRevPerLane][6]) {
+  float tt[3], M[9];
+  if constexpr (KEEP) {
+#pragma unroll
+    for (int k = 0; k < 9; ++k) M[k] = Mt[k];
+#pragma unroll
+    for (int r = 0; r < 3; ++r)
+      tt[r] = x.t[r] + x.R[3 * r] * abar[0] + x.R[3 * r + 1] * abar[1] + x.R[3 * r + 2] * abar[2];
+  } else {
+    float qs[3];
+    rev3d_sums<float>(kp, n, q, abar, 1.f, x, tt, M, qs, clbits, true);
+  }
   const float inv_n = 1.f / (float)n;
   float qsb[3], Rpb[9], Mb[9];
 #pragma unroll
@@ -2533,7 +2582,9 @@ __device__ __forceinline__ bool rev3d_feasible(const KpRec *__restrict__ kp, int
 }
 
 // One wavefront per kRevSamples active samples of 3D-3D instances; dynamic
-// LDS: the tape, kRevSamples x n_iters poses of 12 floats.
+// LDS: the tape, kRevSamples x n_iters rows of a pose and (KEEP: while they fit) its
+// M, which the sweep otherwise sums again.
+template <bool KEEP>
 __global__ void __launch_bounds__(64) k_bwd_rev3d(DevBatch b, DevParams p, const InstRec *__restrict__ inst,
                                                   const KpRec *__restrict__ kprec, const BwdRec *recs,
                                                   const int64_t *__restrict__ item_off,
@@ -2543,8 +2594,9 @@ __global__ void __launch_bounds__(64) k_bwd_rev3d(DevBatch b, DevParams p, const
   const int lane = threadIdx.x, grp = lane / kRevGroup, q = lane % kRevGroup;
   const int iters = p.n_iters;
   const int it_alloc = iters > 0 ? iters : 1;
-  float *tape = tape_all + (int64_t)grp * it_alloc * 12;
-  uint8_t *clb = reinterpret_cast<uint8_t *>(tape_all + (int64_t)kRevSamples * it_alloc * 12) +
+  constexpr int kRow = KEEP ? kRevPolarRow : kRevPoseRow;
+  float *tape = tape_all + (int64_t)grp * it_alloc * kRow;
+  uint8_t *clb = reinterpret_cast<uint8_t *>(tape_all + (int64_t)kRevSamples * it_alloc * kRow) +
                  (int64_t)grp * it_alloc * kRevGroup;
   const float band = ClampBand<Dual<float>>::v;
   for (int64_t wv = blockIdx.x; wv * kRevSamples < total; wv += gridDim.x) {
@@ -2571,11 +2623,16 @@ __global__ void __launch_bounds__(64) k_bwd_rev3d(DevBatch b, DevParams p, const
     if (live) {
       const double inv_n = 1.0 / (double)n;
       for (int itr = 0; itr < iters; ++itr) {
-        if (q < 12) tape[12 * itr + q] = rev_entry(x, q);
+        float *row = tape + kRow * itr;
+        if (q == 0) rev_put_pose(row, x);
         double tt[3], M[9], qs[3];
         uint32_t cl = 0u;
         rev3d_sums<double>(kp, n, q, I.abar, band, x, tt, M, qs, cl, false);
         clb[itr * kRevGroup + q] = (uint8_t)cl;
+        if (KEEP && q == 0) {
+          const double v[12] = {M[0], M[1], M[2], M[3], M[4], M[5], M[6], M[7], M[8], 0.0, 0.0, 0.0};
+          rev_put<12>(row + kRevPoseRow, v);
+        }
         rev_polar(M, x.R);
 #pragma unroll
         for (int r = 0; r < 3; ++r)
@@ -2688,15 +2745,15 @@ __global__ void __launch_bounds__(64) k_bwd_rev3d(DevBatch b, DevParams p, const
       for (int itr = iters - 1; itr >= 0; --itr) {
         RevPose xin;
         float Rn[9];
-        const float *tx = tape + 12 * itr;
+        const float *tx = tape + kRow * itr;
 #pragma unroll
         for (int m = 0; m < 9; ++m) {
           xin.R[m] = tx[m];
-          Rn[m] = itr + 1 < iters ? tx[12 + m] : xf.R[m];
+          Rn[m] = itr + 1 < iters ? tx[kRow + m] : xf.R[m];
         }
 #pragma unroll
         for (int m = 0; m < 3; ++m) xin.t[m] = tx[9 + m];
-        rev3d_iter(kp, n, q, I.abar, clb[itr * kRevGroup + q], xin, Rn, xb, kb);
+        rev3d_iter<KEEP>(kp, n, q, I.abar, clb[itr * kRevGroup + q], xin, tx + kRevPoseRow, Rn, xb, kb);
       }
       // the start: even s rotate the centre by E about the pivot, odd s shift it
       if ((s & 1) == 0) {
@@ -2891,13 +2948,26 @@ hipError_t launch_backward(const DevBatch &b, const DevParams &p, const float *p
   // 2D-3D: one reverse sweep per active sample while the tape fits in LDS,
   // else (or when asked) one forward-mode re-run per input direction
   const int passes = p.n_iters * p.n_gn;
-  const size_t lds2 = rev_lds(passes, p.n_iters);
+  const size_t lds2 = rev_lds(passes, p.n_iters, kRevPoseRow);
   const bool reverse = lds2 <= kRevLds && !(p.flags & PURSE_FLAG_FORWARD_TANGENTS);
   if (reverse) {
     hipLaunchKernelGGL(k_bwd_items_rev, dim3(1), dim3(1024), 0, stream, b, inst, recs, (int)PURSE_KIND_2D3D, items);
-    const size_t lds = lds2;
-    hipLaunchKernelGGL(k_bwd_rev2d, dim3(kItemGrid), dim3(64), lds, stream, b, p, inst, kp, recs, items, tan,
-                       contrib, max_dirs);
+    // with the factors on the tape while the active sets, at most kMaxActive
+    // samples each, fill no more than one wavefront per compute unit and the
+    // rows fit its LDS
+    int dev = 0, n_cu = 256, lds_block = 65536;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+      n_cu = 256;
+    if (hipDeviceGetAttribute(&lds_block, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess)
+      lds_block = 65536;
+    const size_t lds_solve = rev_lds(passes, p.n_iters, kRevSolveRow);
+    if ((int64_t)n * (kMaxActive / kRevSamples) <= n_cu && lds_solve <= (size_t)lds_block)
+      hipLaunchKernelGGL(k_bwd_rev2d<true>, dim3(n_cu), dim3(64), lds_solve, stream, b, p, inst, kp, recs, items,
+                         tan, contrib, max_dirs);
+    else
+      hipLaunchKernelGGL(k_bwd_rev2d<false>, dim3(kItemGrid), dim3(64), lds2, stream, b, p, inst, kp, recs, items,
+                         tan, contrib, max_dirs);
   } else {
     hipLaunchKernelGGL(k_bwd_items, dim3(1), dim3(1024), 0, stream, b, inst, recs, (int)PURSE_KIND_2D3D, kTrajGroup,
                        items);
@@ -2905,14 +2975,18 @@ hipError_t launch_backward(const DevBatch &b, const DevParams &p, const float *p
                        items, tan, contrib, max_dirs);
   }
   // 3D-3D likewise, with one tape pose per iteration
-  const size_t lds3 = rev_lds(p.n_iters, p.n_iters);
-  const bool reverse3 = lds3 <= kRevLds && !(p.flags & PURSE_FLAG_FORWARD_TANGENTS);
+  const size_t lds3 = rev_lds(p.n_iters, p.n_iters, kRevPolarRow);
+  const size_t lds3p = rev_lds(p.n_iters, p.n_iters, kRevPoseRow);
+  const bool reverse3 = lds3p <= kRevLds && !(p.flags & PURSE_FLAG_FORWARD_TANGENTS);
   if (reverse3) {
     hipLaunchKernelGGL(k_bwd_items_rev, dim3(1), dim3(1024), 0, s3, b, inst, recs, (int)PURSE_KIND_3D3D,
                        items + (n + 1));
-    const size_t lds = lds3;
-    hipLaunchKernelGGL(k_bwd_rev3d, dim3(kItemGrid), dim3(64), lds, s3, b, p, inst, kp, recs, items + (n + 1),
-                       tan, contrib, max_dirs);
+    if (lds3 <= kRevLds)
+      hipLaunchKernelGGL(k_bwd_rev3d<true>, dim3(kItemGrid), dim3(64), lds3, s3, b, p, inst, kp, recs,
+                         items + (n + 1), tan, contrib, max_dirs);
+    else
+      hipLaunchKernelGGL(k_bwd_rev3d<false>, dim3(kItemGrid), dim3(64), lds3p, s3, b, p, inst, kp, recs,
+                         items + (n + 1), tan, contrib, max_dirs);
   } else {
     hipLaunchKernelGGL(k_bwd_items, dim3(1), dim3(1024), 0, s3, b, inst, recs, (int)PURSE_KIND_3D3D, 1,
                        items + (n + 1));

@@ -288,8 +288,9 @@ __device__ bool gn_centre_2d_wave(const float *Z, const OBS &obs, int n, const f
       gn_accumulate<double>(P, pt, iz, Kd[0], Kd[1], wi, rt0, rt1, A, g);
     }
     wave_sums<27>(A, n);
-    double d[6];
-    if (!near_step(A, g, o, R, t, d)) return false;
+    double L[21], dinv[6], d[6];
+    if (!near_solve(A, g, L, dinv, d)) return false;
+    near_update(d, o, R, t);
     double dw = 0.0, dv = 0.0, tm = 0.0;
     for (int k = 0; k < 3; ++k) {
       dw = fmax(dw, fabs(d[k]));

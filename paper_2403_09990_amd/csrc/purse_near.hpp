@@ -135,11 +135,10 @@ __device__ __forceinline__ void near_exp_so3(const double w[3], double E[9]) {
   }
 }
 
-// The Gauss-Newton solve (step d) and update about o in float64: false (and the
-// pose as it was) when a pivot is not positive.
-__device__ __forceinline__ bool near_step(const double A[21], const double g[6], const double o[3], double R[9],
-                                          double t[3], double d[6]) {
-  double L[21], dinv[6];
+// The Gauss-Newton solve A d = g in float64: the factor's off-diagonal entries L
+// and reciprocal diagonal dinv; false when a pivot is not positive.
+__device__ __forceinline__ bool near_solve(const double A[21], const double g[6], double L[21], double dinv[6],
+                                           double d[6]) {
   bool ok = true;
 #pragma unroll
   for (int j = 0; j < 6; ++j) {
@@ -158,6 +157,11 @@ __device__ __forceinline__ bool near_step(const double A[21], const double g[6],
   }
   if (!ok) return false;
   chol6_subst<double>(L, dinv, g, d);  // (it reads no diagonal entry of L)
+  return true;
+}
+
+// The left update about o by the step d.
+__device__ __forceinline__ void near_update(const double d[6], const double o[3], double R[9], double t[3]) {
   double E[9], Rn[9], arm[3], e[3];
   near_exp_so3(d, E);
   matmul3(E, R, Rn);
@@ -168,7 +172,6 @@ __device__ __forceinline__ bool near_step(const double A[21], const double g[6],
   for (int r = 0; r < 3; ++r) t[r] = e[r] + o[r] + d[3 + r];
 #pragma unroll
   for (int k = 0; k < 9; ++k) R[k] = Rn[k];
-  return true;
 }
 
 // R = proj_SO3(M) in float64 for det M > 0 by Newton's iteration for the
