@@ -43,7 +43,7 @@ static_assert(sizeof(InstRec) == 192, "InstRec layout");
 struct MegbRec {
   int32_t first;          // first feasible instance-local index (INT32_MAX if none)
   int32_t n_rescan[2];    // diagnostics: rescans per chain
-  int32_t n_global[2];    // diagnostics: full-scan stages per chain (low 16 bits), global shells rebuilt (high 16)
+  int32_t n_global[2];    // diagnostics: full-scan stages per chain (low 16 bits), undominated gathers (high 16)
   int32_t n_piped;        // diagnostics: rotation steps taken in pipelined segments
   unsigned long long n_feasible;
   unsigned long long max_rot;    // float64 bit pattern of max ||R* - R_s||_F^2
@@ -81,7 +81,7 @@ constexpr int kShellDiv = 8;
 // Slots of an instance's undominated samples: [off / kShellDiv, off / kShellDiv
 // + M / kShellDiv) in each chain's array (disjoint between instances, since
 // floor(a) + floor(b) <= floor(a + b)).
-__host__ __device__ inline int64_t gshell_stride(int64_t total_samples, int64_t max_samples) {
+__host__ __device__ inline int64_t undominated_stride(int64_t total_samples, int64_t max_samples) {
   return max_samples >= kBigInstance ? total_samples / kShellDiv + 1 : 0;
 }
 
@@ -173,7 +173,7 @@ inline WsLayout ws_layout(int64_t n_inst, int64_t total_kp, int64_t total_sample
   const bool big = max_samples >= kBigInstance;
   L.early = o;  // [n_inst][2] first-phase scratch
   o += big ? align_up(sizeof(EarlyScratch) * 2 * (size_t)n_inst) : 0;
-  const size_t gs = (size_t)gshell_stride(total_samples, max_samples);
+  const size_t gs = (size_t)undominated_stride(total_samples, max_samples);
   L.gid = o;  // [2][stride] ids of the undominated samples
   o += align_up(sizeof(int32_t) * 2 * gs);
   L.gpt = o;  // [2][stride] their points (quaternion or translation)

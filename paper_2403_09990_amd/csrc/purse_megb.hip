@@ -2279,7 +2279,7 @@ void launch_megb(const DevBatch &b, const DevParams &p, const float *poses, cons
   const int cap = wide ? chain_cap<kChainWide>() : chain_cap<kChainNarrow>();
   const size_t lds = (size_t)cap * (sizeof(float4) + sizeof(int));
   const int no_prune = (p.flags & PURSE_FLAG_NO_PRUNING) ? 1 : 0;
-  const int64_t gstride = gshell_stride(total_samples, max_samples);
+  const int64_t gstride = undominated_stride(total_samples, max_samples);
   const int n_early = early_steps(max_samples, wide);
   if (early_phase_applies(max_samples, p.megb_iters, p.megb_avg, no_prune, n_early)) {
     const dim3 eg((unsigned)kEarlyWG, 2u, (unsigned)n);
