@@ -1,7 +1,8 @@
 // Backward of purse_sample + purse_megb with every discrete decision held as
 // taken (argmax trace, feasibility and bisection outcomes, clamp sides).
 //
-// 1. k_bwd_megb (one workgroup per instance): the rotation iterates are the
+// 1. k_bwd_megb (one workgroup per instance; large instances search their
+//    radius samples in k_bwd_radius between its halves): the rotation iterates are the
 //    forward's own float32 ones: every ckpt_every-th is a checkpoint that
 //    purse_megb left (or, for a trace it did not produce, that a replay of the
 //    descent from the trace writes); the cotangents of (D_hat, d_hat, R*, t*) are swept back through the
@@ -18,6 +19,7 @@
 //    with its cotangent.
 // 4. k_bwd_reduce: per direction, the sum over active samples in a fixed
 //    order, scattered into the gradient arrays.
+#include <algorithm>
 #include <mutex>
 
 #include "purse_bwd_check.hpp"
@@ -141,13 +143,79 @@ __device__ __forceinline__ int find_active(const int *act, int n, int s) { retur
 
 }  // namespace
 
+// Parts of k_bwd_megb: the whole in one launch, or its two halves around
+// k_bwd_radius.
+constexpr int kBwdWhole = 0, kBwdHead = 1, kBwdTail = 2;
+
+// What the halves hand over, in the cotangents' place (the tail reads it
+// before it writes those): the centre, the averaged sum and each
+// k_bwd_radius workgroup's argmax of the two distances.
+constexpr int kRadiusGroups = kBwdBlock;  // workgroups per instance at most: one partial per thread of the tail
+// The search reads every pose of the instance once.  One workgroup keeps 48 KB
+// in flight, 27 GB/s of them, so 2^20 samples take it 1.9 ms; spread over up to
+// 256 workgroups (in a launch of its own between the halves of k_bwd_megb) it
+// runs at the memory's rate.  Backward of one instance, one workgroup against
+// spread: 4,096 samples 0.724 / 0.746 ms (two launches and a second staging),
+// 32,768 0.732 / 0.716, 65,536 1.107 / 1.064, 2^20 1.836 / 0.616.
+constexpr int64_t kRadiusSplit = 1 << 15;  // samples of the largest instance from which the search is spread
+constexpr int64_t kRadiusGrid = 1 << 15;   // workgroups of the search in all (those past an instance's end leave at once)
+constexpr int kRadiusPer = 4;              // samples per thread and round, their loads issued together
+struct BwdHand {
+  double Rstar[9], tstar[3], Ssum[9];
+  double v[2][kRadiusGroups];
+  int32_t id[2][kRadiusGroups];
+};
+static_assert(sizeof(BwdHand) <= sizeof(BwdRec::cot), "the hand-over fits the cotangents' place");
+
+// The feasible samples farthest from (Rs, ts) among rounds of kRadiusPer *
+// kBwdBlock samples from s0, stride apart.
+__device__ __forceinline__ void radius_scan(const float *__restrict__ poses, const uint8_t *__restrict__ mask,
+                                            int64_t off, unsigned M, unsigned s0, unsigned stride, const D Rs[9], const D ts[3],
+                                            D &br, int &ir, D &bt, int &it) {
+  constexpr unsigned U = kRadiusPer;
+  const unsigned tid = threadIdx.x;
+  for (unsigned r0 = s0; r0 < M; r0 += stride) {  // (no wrap: M < 2^31)
+    float4 q[U][3];
+    uint8_t m4[U];
+#pragma unroll
+    for (unsigned u = 0; u < U; ++u) {
+      const unsigned s = min(r0 + u * kBwdBlock + tid, M - 1);
+      const float4 *P = reinterpret_cast<const float4 *>(poses + 12 * (off + s));
+      q[u][0] = P[0];
+      q[u][1] = P[1];
+      q[u][2] = P[2];
+      m4[u] = mask[off + s];
+    }
+#pragma unroll
+    for (unsigned u = 0; u < U; ++u) {
+      const unsigned s = r0 + u * kBwdBlock + tid;
+      if (s >= M || !(m4[u] & PURSE_MASK_FEASIBLE)) continue;
+      const float P[12] = {q[u][0].x, q[u][0].y, q[u][0].z, q[u][0].w, q[u][1].x, q[u][1].y,
+                           q[u][1].z, q[u][1].w, q[u][2].x, q[u][2].y, q[u][2].z, q[u][2].w};
+      D fr = 0, ft = 0;
+      for (int k = 0; k < 9; ++k) {
+        D d = Rs[k] - (D)P[k];
+        fr += d * d;
+      }
+      for (int k = 0; k < 3; ++k) {
+        D d = ts[k] - (D)P[9 + k];
+        ft += d * d;
+      }
+      // increasing s per thread: a strictly larger value replaces the best
+      radius_take(fr, (int)s, br, ir);
+      radius_take(ft, (int)s, bt, it);
+    }
+  }
+}
+
+template <int PART>
 __global__ void __launch_bounds__(kBwdBlock, 2) k_bwd_megb(DevBatch b, DevParams p, const float *__restrict__ poses,
                                                         const uint8_t *__restrict__ mask,
                                                         const int32_t *__restrict__ trace,
                                                         const double *__restrict__ g_radii,
                                                         const float *__restrict__ g_centre,
                                                         const InstRec *__restrict__ inst, MegbRec *megb,
-                                                        BwdRec *recs, float4 *ckpt_all, int ck) {
+                                                        BwdRec *recs, float4 *ckpt_all, int ck, int n_radius) {
   __shared__ int act[kMaxActive];
   __shared__ int n_act_s, err_s, n_distinct_s;  // err_s: a BwdRec status (kBwdOk while the sweep may run)
   // (80 KB in all, so that two instances share a compute unit: the rotation
@@ -180,142 +248,163 @@ __global__ void __launch_bounds__(kBwdBlock, 2) k_bwd_megb(DevBatch b, DevParams
   sample_range(b.sample_off, j, b.total_samples, b.max_samples, off, M64);
   const int M = (int)M64;
   BwdRec *rec = recs + j;
-  // ---- the prologue's records must belong to this batch and its data (else
-  // they would index keypoints of another batch): the instance record's
-  // ranges and key, and the fingerprint of the inputs, recomputed here
-  if (tid == 0) {
-    s0_s = INT32_MAX;
-    err_s = inst_record_ok(inst[j], inst_view(b, j)) ? kBwdOk : kBwdStale;
-  }
-  __syncthreads();
-  if (wave == 0 && err_s == kBwdOk) {
-    const int n = b.n_kp[j];
-    const int64_t ko = b.kp_off[j];
-    unsigned long long h = 0ull;
-    if (lane < n) {
-      const int64_t k = ko + lane;
-      uint32_t w[11];
-      kp_words(b.kind[j], b.model_pts + 3 * k, b.centres + 3 * k, b.shapes + 4 * k, b.bounds[k], w);
-      h = kp_data_term(lane, w);
-    }
-    for (int o = 32; o >= 1; o >>= 1) h += __shfl_xor(h, o, 64);
-    if (lane == 0) {
-      const InstRec &I = inst[j];
-      h += I.kind == PURSE_KIND_2D3D ? intrinsics_term(I.K) : 0ull;
-      if (h != I.data_fp) err_s = kBwdStale;
-    }
-  }
-  __syncthreads();
-  if (err_s != kBwdOk) {
-    if (tid == 0) {
-      rec->n_act = 0;
-      rec->n_distinct = 0;
-      rec->status = err_s;
-    }
-    return;
-  }
-  // ---- first feasible sample: rounds of 8 masks per thread (loads issued
-  // together), stopping at the first round that holds one
-  for (int r0 = 0; r0 < M; r0 += 8 * kBwdBlock) {
-    uint8_t m8[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) m8[u] = mask[off + min(r0 + u * kBwdBlock + tid, M - 1)];
-    int first = INT32_MAX;
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int s = r0 + u * kBwdBlock + tid;
-      if (s < M && (m8[u] & PURSE_MASK_FEASIBLE)) first = min(first, s);
-    }
-    for (int o = 32; o >= 1; o >>= 1) first = min(first, __shfl_xor(first, o, 64));
-    if (lane == 0 && first != INT32_MAX) atomicMin(&s0_s, first);
-    __syncthreads();
-    const bool found = s0_s != INT32_MAX;
-    __syncthreads();  // every wave has read s0_s before any wave's next round may write it
-    if (found) break;
-  }
-  const int s0 = s0_s;
-  if (s0 == INT32_MAX) {
-    if (tid == 0) {
-      rec->n_act = 0;
-      rec->n_distinct = 0;
-      rec->status = kBwdEmpty;
-    }
-    return;
-  }
-  // ---- active set: the sorted distinct samples of the trace and the first
-  // sample, extracted by repeated block minima (the set has tens of members)
   const int32_t *tr = trace + (int64_t)j * T * 2;
-  {
-    int bad = 0;
-    for (int k = tid; k < 2 * T; k += kBwdBlock) {
-      int v = tr[k];
-      if (v < 0 || v >= M || !(mask[off + v] & PURSE_MASK_FEASIBLE)) bad = 1;
+  int s0;
+  if constexpr (PART != kBwdTail) {
+    // ---- the prologue's records must belong to this batch and its data (else
+    // they would index keypoints of another batch): the instance record's
+    // ranges and key, and the fingerprint of the inputs, recomputed here
+    if (tid == 0) {
+      s0_s = INT32_MAX;
+      err_s = inst_record_ok(inst[j], inst_view(b, j)) ? kBwdOk : kBwdStale;
     }
-    bad = __syncthreads_or(bad);
-    if (bad) {
+    __syncthreads();
+    if (wave == 0 && err_s == kBwdOk) {
+      const int n = b.n_kp[j];
+      const int64_t ko = b.kp_off[j];
+      unsigned long long h = 0ull;
+      if (lane < n) {
+        const int64_t k = ko + lane;
+        uint32_t w[11];
+        kp_words(b.kind[j], b.model_pts + 3 * k, b.centres + 3 * k, b.shapes + 4 * k, b.bounds[k], w);
+        h = kp_data_term(lane, w);
+      }
+      for (int o = 32; o >= 1; o >>= 1) h += __shfl_xor(h, o, 64);
+      if (lane == 0) {
+        const InstRec &I = inst[j];
+        h += I.kind == PURSE_KIND_2D3D ? intrinsics_term(I.K) : 0ull;
+        if (h != I.data_fp) err_s = kBwdStale;
+      }
+    }
+    __syncthreads();
+    if (err_s != kBwdOk) {
       if (tid == 0) {
         rec->n_act = 0;
         rec->n_distinct = 0;
-        rec->status = kBwdBadTrace;
+        rec->status = err_s;
       }
       return;
     }
-  }
-  // ---- the rotation checkpoints purse_megb left are used when their
-  // signature (steps, winners, the bits of the start's and the winners'
-  // rotations) matches this descent (else it is replayed below)
-  {
-    unsigned long long h = 0ull;
-    for (int i = tid; i <= T; i += kBwdBlock) {
-      const int id = i == 0 ? s0 : tr[2 * (i - 1)];  // (checked above: samples of the instance)
-      uint32_t R[9];
-      const float *P = poses + 12 * (off + id);
-      for (int k = 0; k < 9; ++k) R[k] = __float_as_uint(P[k]);
-      h += step_sig_term(i, id, R);
-    }
-    for (int o = 32; o >= 1; o >>= 1) h += __shfl_xor(h, o, 64);
-    if (lane == 0) red_h[wave] = h;
-    __syncthreads();
-    if (tid == 0) {
-      unsigned long long t = 0ull;
-      for (int w = 0; w < kBwdWaves; ++w) t += red_h[w];
-      const MegbRec &mr = megb[j];
-      stored_s = !(p.flags & PURSE_FLAG_REPLAY_DESCENT) && mr.ck_T == T && mr.ck_every == ck && mr.ck_hash == t;
-      if (!stored_s) {
-        // the replay below rewrites the checkpoints: they then belong to this trace
-        megb[j].ck_hash = t;
-        megb[j].ck_T = 0;  // (set to T once written)
-        megb[j].ck_every = ck;
+    // ---- first feasible sample: rounds of 8 masks per thread (loads issued
+    // together), stopping at the first round that holds one
+    for (int r0 = 0; r0 < M; r0 += 8 * kBwdBlock) {
+      uint8_t m8[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) m8[u] = mask[off + min(r0 + u * kBwdBlock + tid, M - 1)];
+      int first = INT32_MAX;
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int s = r0 + u * kBwdBlock + tid;
+        if (s < M && (m8[u] & PURSE_MASK_FEASIBLE)) first = min(first, s);
       }
-      n_act_s = 0;
-      n_distinct_s = 0;
+      for (int o = 32; o >= 1; o >>= 1) first = min(first, __shfl_xor(first, o, 64));
+      if (lane == 0 && first != INT32_MAX) atomicMin(&s0_s, first);
+      __syncthreads();
+      const bool found = s0_s != INT32_MAX;
+      __syncthreads();  // every wave has read s0_s before any wave's next round may write it
+      if (found) break;
     }
-  }
-  __syncthreads();
-  int last = -1;
-  while (true) {
-    int mn = INT32_MAX;
-    for (int k = tid; k <= 2 * T; k += kBwdBlock) {
-      int v = k < 2 * T ? tr[k] : s0;
-      if (v > last && v < mn) mn = v;
+    s0 = s0_s;
+    if (s0 == INT32_MAX) {
+      if (tid == 0) {
+        rec->n_act = 0;
+        rec->n_distinct = 0;
+        rec->status = kBwdEmpty;
+      }
+      return;
     }
-    for (int o = 32; o >= 1; o >>= 1) mn = min(mn, __shfl_xor(mn, o, 64));
-    if (lane == 0) red_i[wave] = mn;
+    // ---- active set: the sorted distinct samples of the trace and the first
+    // sample, extracted by repeated block minima (the set has tens of members)
+    {
+      int bad = 0;
+      for (int k = tid; k < 2 * T; k += kBwdBlock) {
+        int v = tr[k];
+        if (v < 0 || v >= M || !(mask[off + v] & PURSE_MASK_FEASIBLE)) bad = 1;
+      }
+      bad = __syncthreads_or(bad);
+      if (bad) {
+        if (tid == 0) {
+          rec->n_act = 0;
+          rec->n_distinct = 0;
+          rec->status = kBwdBadTrace;
+        }
+        return;
+      }
+    }
+    // ---- the rotation checkpoints purse_megb left are used when their
+    // signature (steps, winners, the bits of the start's and the winners'
+    // rotations) matches this descent (else it is replayed below)
+    {
+      unsigned long long h = 0ull;
+      for (int i = tid; i <= T; i += kBwdBlock) {
+        const int id = i == 0 ? s0 : tr[2 * (i - 1)];  // (checked above: samples of the instance)
+        uint32_t R[9];
+        const float *P = poses + 12 * (off + id);
+        for (int k = 0; k < 9; ++k) R[k] = __float_as_uint(P[k]);
+        h += step_sig_term(i, id, R);
+      }
+      for (int o = 32; o >= 1; o >>= 1) h += __shfl_xor(h, o, 64);
+      if (lane == 0) red_h[wave] = h;
+      __syncthreads();
+      if (tid == 0) {
+        unsigned long long t = 0ull;
+        for (int w = 0; w < kBwdWaves; ++w) t += red_h[w];
+        const MegbRec &mr = megb[j];
+        stored_s = !(p.flags & PURSE_FLAG_REPLAY_DESCENT) && mr.ck_T == T && mr.ck_every == ck && mr.ck_hash == t;
+        if (!stored_s) {
+          // the replay below rewrites the checkpoints: they then belong to this trace
+          megb[j].ck_hash = t;
+          megb[j].ck_T = 0;  // (set to T once written)
+          megb[j].ck_every = ck;
+        }
+        n_act_s = 0;
+        n_distinct_s = 0;
+      }
+    }
     __syncthreads();
-    mn = INT32_MAX;
-    for (int w = 0; w < kBwdWaves; ++w) mn = min(mn, red_i[w]);
+    int last = -1;
+    while (true) {
+      int mn = INT32_MAX;
+      for (int k = tid; k <= 2 * T; k += kBwdBlock) {
+        int v = k < 2 * T ? tr[k] : s0;
+        if (v > last && v < mn) mn = v;
+      }
+      for (int o = 32; o >= 1; o >>= 1) mn = min(mn, __shfl_xor(mn, o, 64));
+      if (lane == 0) red_i[wave] = mn;
+      __syncthreads();
+      mn = INT32_MAX;
+      for (int w = 0; w < kBwdWaves; ++w) mn = min(mn, red_i[w]);
+      __syncthreads();
+      if (mn == INT32_MAX) break;
+      if (tid == 0) {
+        ++n_distinct_s;
+        if (n_act_s < kMaxActive)
+          act[n_act_s++] = mn;
+        else
+          err_s = kBwdOverflow;
+      }
+      last = mn;
+    }
     __syncthreads();
-    if (mn == INT32_MAX) break;
+  } else {
+    // the head's record of this call
+    if (rec->status != kBwdOk) return;
+    s0 = rec->s0;
+    const int n0 = min(max(rec->n_act, 0), kMaxActive);
+    for (int k = tid; k < n0; k += kBwdBlock) act[k] = rec->active[k];
+    const BwdHand &H = *reinterpret_cast<const BwdHand *>(rec->cot);
+    if (tid < 9) {
+      Rstar[tid] = H.Rstar[tid];
+      Ssum[tid] = H.Ssum[tid];
+    }
+    if (tid < 3) tstar[tid] = H.tstar[tid];
     if (tid == 0) {
-      ++n_distinct_s;
-      if (n_act_s < kMaxActive)
-        act[n_act_s++] = mn;
-      else
-        err_s = kBwdOverflow;
+      n_act_s = n0;
+      n_distinct_s = rec->n_distinct;
+      err_s = kBwdOk;
     }
-    last = mn;
+    __syncthreads();
   }
-  __syncthreads();
   // ---- stage the active samples' poses and the trace (as slots) in LDS: the
   // serial sweeps below then read nothing from global memory per step
   // (every active id is a sample of the instance: the trace was checked and
@@ -340,7 +429,8 @@ __global__ void __launch_bounds__(kBwdBlock, 2) k_bwd_megb(DevBatch b, DevParams
     for (int a = tid; a < n_act_now && !miss && !stop; a += kBwdBlock) qact[a] = quat_from_rot(pact[a]);
     __syncthreads();
   };
-  stage_active(n_act_s);
+  // (the tail stages once, below, when the radius samples are known)
+  if constexpr (PART != kBwdTail) stage_active(n_act_s);
   auto slot_of = [&](int k) {
     if (lds_trace) return (int)tslot[k];
     const int sl = find_active(act, n_act_s, tr[k]);
@@ -349,145 +439,141 @@ __global__ void __launch_bounds__(kBwdBlock, 2) k_bwd_megb(DevBatch b, DevParams
   auto load_act = [&](int a, D R[9]) {
     for (int q = 0; q < 9; ++q) R[q] = (D)pact[a][q];
   };
-  // ---- the rotation iterates.  The chain repeats the forward's float32
-  // quaternion steps, so the backward linearises at the iterates the forward
-  // computed; C_0, C_ck, C_2ck, ... are the checkpoints.  With the forward's
-  // checkpoints only the last avg iterates are recomputed (from the one at or
-  // before step T - avg); otherwise wavefront 0 replays the whole descent
-  // (every lane runs the same steps, 1/i and the winners' quaternions from
-  // per-lane tables of the next 64 steps) and writes the checkpoints.
   float4 *ckq = ckpt_all + (int64_t)j * ckpt_count(T, ck);
-  const bool stored = stored_s != 0;
-  if (wave == 0 && err_s == kBwdOk) {
-    D S[9];
-    for (int k = 0; k < 9; ++k) S[k] = 0;
-    if (stored) {
-      const int q0 = (T - avg) / ck;
-      float4 C = ckq[q0];
-      for (int i = q0 * ck + 1; i <= T; ++i) {
-        C = geodesic_step(C, qact[slot_of(2 * (i - 1))], i, 0);
-        if (i > T - avg) {
-          D Cm[9];
-          rot_of_quat_d(C, Cm);
-          for (int k = 0; k < 9; ++k) S[k] += Cm[k];
+  if constexpr (PART != kBwdTail) {
+    // ---- the rotation iterates.  The chain repeats the forward's float32
+    // quaternion steps, so the backward linearises at the iterates the forward
+    // computed; C_0, C_ck, C_2ck, ... are the checkpoints.  With the forward's
+    // checkpoints only the last avg iterates are recomputed (from the one at or
+    // before step T - avg); otherwise wavefront 0 replays the whole descent
+    // (every lane runs the same steps, 1/i and the winners' quaternions from
+    // per-lane tables of the next 64 steps) and writes the checkpoints.
+    const bool stored = stored_s != 0;
+    if (wave == 0 && err_s == kBwdOk) {
+      D S[9];
+      for (int k = 0; k < 9; ++k) S[k] = 0;
+      if (stored) {
+        const int q0 = (T - avg) / ck;
+        float4 C = ckq[q0];
+        for (int i = q0 * ck + 1; i <= T; ++i) {
+          C = geodesic_step(C, qact[slot_of(2 * (i - 1))], i, 0);
+          if (i > T - avg) {
+            D Cm[9];
+            rot_of_quat_d(C, Cm);
+            for (int k = 0; k < 9; ++k) S[k] += Cm[k];
+          }
+        }
+      } else {
+        float4 C = qact[max(find_active(act, n_act_s, s0), 0)];  // (s0 is in the set)
+        int ib = 1, kc = 0, q = 0;
+        float inv_tab = 1.f / (float)(ib + lane);
+        float4 B_tab = qact[slot_of(2 * min(ib - 1 + lane, T - 1))];
+        for (int i = 1; i <= T; ++i) {
+          if (i - ib == 64) {
+            ib = i;
+            inv_tab = 1.f / (float)(ib + lane);
+            B_tab = qact[slot_of(2 * min(ib - 1 + lane, T - 1))];
+          }
+          const int l = i - ib;
+          const float inv = readlane_f(inv_tab, l);
+          const float4 B = make_float4(readlane_f(B_tab.x, l), readlane_f(B_tab.y, l), readlane_f(B_tab.z, l),
+                                       readlane_f(B_tab.w, l));
+          if (kc == 0) {  // (i - 1) % ck == 0
+            if (lane == 0) ckq[q] = C;
+            ++q;
+            kc = ck;
+          }
+          --kc;
+          C = geodesic_step_inv(C, B, inv, i, 0);
+          if (i > T - avg) {
+            D Cm[9];
+            rot_of_quat_d(C, Cm);
+            for (int k = 0; k < 9; ++k) S[k] += Cm[k];
+          }
         }
       }
-    } else {
-      float4 C = qact[max(find_active(act, n_act_s, s0), 0)];  // (s0 is in the set)
-      int ib = 1, kc = 0, q = 0;
-      float inv_tab = 1.f / (float)(ib + lane);
-      float4 B_tab = qact[slot_of(2 * min(ib - 1 + lane, T - 1))];
-      for (int i = 1; i <= T; ++i) {
-        if (i - ib == 64) {
-          ib = i;
-          inv_tab = 1.f / (float)(ib + lane);
-          B_tab = qact[slot_of(2 * min(ib - 1 + lane, T - 1))];
+      if (lane == 0) {
+        D Rs[9];
+        polar_so3<D>(S, Rs, 12);
+        for (int k = 0; k < 9; ++k) {
+          Rstar[k] = Rs[k];
+          Ssum[k] = S[k];
         }
-        const int l = i - ib;
-        const float inv = readlane_f(inv_tab, l);
-        const float4 B = make_float4(readlane_f(B_tab.x, l), readlane_f(B_tab.y, l), readlane_f(B_tab.z, l),
-                                     readlane_f(B_tab.w, l));
-        if (kc == 0) {  // (i - 1) % ck == 0
-          if (lane == 0) ckq[q] = C;
-          ++q;
-          kc = ck;
-        }
-        --kc;
-        C = geodesic_step_inv(C, B, inv, i, 0);
-        if (i > T - avg) {
-          D Cm[9];
-          rot_of_quat_d(C, Cm);
-          for (int k = 0; k < 9; ++k) S[k] += Cm[k];
-        }
+        if (!stored) megb[j].ck_T = T;
       }
     }
-    if (lane == 0) {
-      D Rs[9];
-      polar_so3<D>(S, Rs, 12);
-      for (int k = 0; k < 9; ++k) {
-        Rstar[k] = Rs[k];
-        Ssum[k] = S[k];
+    // ---- t* = (1/avg) sum_{i > T - avg} c_i, where c_i (c_i = c_{i-1} + (t_{s_i}
+    // - c_{i-1}) / i, c_1 = t_{s_1}) is the mean of the first i winners: winner
+    // k carries (1/avg) sum_{i >= max(k, T - avg + 1)} 1/i.  All threads, in
+    // float64, summed in a fixed order.
+    if (err_s == kBwdOk) {
+      D hs = 0;
+      for (int k = T - avg + 1; k <= T; ++k) hs += 1.0 / (D)k;
+      D ta[3] = {0.0, 0.0, 0.0};
+      for (int k = 1 + tid; k <= T; k += kBwdBlock) {
+        D w = hs;
+        if (k > T - avg) {
+          w = 0;
+          for (int m = k; m <= T; ++m) w += 1.0 / (D)m;
+        }
+        const float *P = pact[slot_of(2 * (k - 1) + 1)];
+        for (int r = 0; r < 3; ++r) ta[r] += w * (D)P[9 + r];
       }
-      if (!stored) megb[j].ck_T = T;
+      for (int o = 1; o < 64; o <<= 1)
+        for (int r = 0; r < 3; ++r) ta[r] += __shfl_xor(ta[r], o, 64);
+      if (lane == 0)
+        for (int r = 0; r < 3; ++r) gstep[wave][r] = ta[r];
     }
+    __syncthreads();
+    if (tid == 0 && err_s == kBwdOk) {
+      for (int r = 0; r < 3; ++r) {
+        D t = 0;
+        for (int w = 0; w < kBwdWaves; ++w) t += gstep[w][r];
+        tstar[r] = t / avg;
+      }
+      // a non-finite centre has no radius samples
+      bool fin = true;
+      for (int k = 0; k < 9; ++k) fin = fin && isfinite(Rstar[k]);
+      for (int k = 0; k < 3; ++k) fin = fin && isfinite(tstar[k]);
+      if (!fin) err_s = kBwdNonFinite;
+    }
+    __syncthreads();
   }
-  // ---- t* = (1/avg) sum_{i > T - avg} c_i, where c_i (c_i = c_{i-1} + (t_{s_i}
-  // - c_{i-1}) / i, c_1 = t_{s_1}) is the mean of the first i winners: winner
-  // k carries (1/avg) sum_{i >= max(k, T - avg + 1)} 1/i.  All threads, in
-  // float64, summed in a fixed order.
-  if (err_s == kBwdOk) {
-    D hs = 0;
-    for (int k = T - avg + 1; k <= T; ++k) hs += 1.0 / (D)k;
-    D ta[3] = {0.0, 0.0, 0.0};
-    for (int k = 1 + tid; k <= T; k += kBwdBlock) {
-      D w = hs;
-      if (k > T - avg) {
-        w = 0;
-        for (int m = k; m <= T; ++m) w += 1.0 / (D)m;
-      }
-      const float *P = pact[slot_of(2 * (k - 1) + 1)];
-      for (int r = 0; r < 3; ++r) ta[r] += w * (D)P[9 + r];
+  if constexpr (PART == kBwdHead) {
+    const int n_out = err_s != kBwdOk ? 0 : n_act_s;
+    if (tid == 0) {
+      rec->n_act = n_out;
+      rec->n_distinct = n_distinct_s;
+      rec->status = err_s;
+      rec->s0 = s0;
+      rec->sD = INT32_MAX;
+      rec->sd = INT32_MAX;
     }
-    for (int o = 1; o < 64; o <<= 1)
-      for (int r = 0; r < 3; ++r) ta[r] += __shfl_xor(ta[r], o, 64);
-    if (lane == 0)
-      for (int r = 0; r < 3; ++r) gstep[wave][r] = ta[r];
-  }
-  __syncthreads();
-  if (tid == 0 && err_s == kBwdOk) {
-    for (int r = 0; r < 3; ++r) {
-      D t = 0;
-      for (int w = 0; w < kBwdWaves; ++w) t += gstep[w][r];
-      tstar[r] = t / avg;
+    for (int k = tid; k < n_out; k += kBwdBlock) rec->active[k] = act[k];
+    BwdHand &H = *reinterpret_cast<BwdHand *>(rec->cot);
+    if (tid < 9) {
+      H.Rstar[tid] = Rstar[tid];
+      H.Ssum[tid] = Ssum[tid];
     }
-    // a non-finite centre has no radius samples
-    bool fin = true;
-    for (int k = 0; k < 9; ++k) fin = fin && isfinite(Rstar[k]);
-    for (int k = 0; k < 3; ++k) fin = fin && isfinite(tstar[k]);
-    if (!fin) err_s = kBwdNonFinite;
+    if (tid < 3) H.tstar[tid] = tstar[tid];
+    return;
   }
-  __syncthreads();
   // ---- samples realising the radii about (R*, t*)
   D br = -1, bt = -1;
   int ir = INT32_MAX, it = INT32_MAX;
-  {
-    // 4 samples per thread and round, their loads issued together
-    constexpr int U = 4;
+  if constexpr (PART == kBwdTail) {
+    const BwdHand &H = *reinterpret_cast<const BwdHand *>(rec->cot);
+    if (tid < n_radius) {
+      br = H.v[0][tid];
+      ir = H.id[0][tid];
+      bt = H.v[1][tid];
+      it = H.id[1][tid];
+    }
+  } else {
     D Rs[9], ts[3];
     for (int k = 0; k < 9; ++k) Rs[k] = Rstar[k];
     for (int k = 0; k < 3; ++k) ts[k] = tstar[k];
-    for (int r0 = 0; r0 < M; r0 += U * kBwdBlock) {
-      float4 q[U][3];
-      uint8_t m4[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int s = min(r0 + u * kBwdBlock + tid, M - 1);
-        const float4 *P = reinterpret_cast<const float4 *>(poses + 12 * (off + s));
-        q[u][0] = P[0];
-        q[u][1] = P[1];
-        q[u][2] = P[2];
-        m4[u] = mask[off + s];
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int s = r0 + u * kBwdBlock + tid;
-        if (s >= M || !(m4[u] & PURSE_MASK_FEASIBLE)) continue;
-        const float P[12] = {q[u][0].x, q[u][0].y, q[u][0].z, q[u][0].w, q[u][1].x, q[u][1].y,
-                             q[u][1].z, q[u][1].w, q[u][2].x, q[u][2].y, q[u][2].z, q[u][2].w};
-        D fr = 0, ft = 0;
-        for (int k = 0; k < 9; ++k) {
-          D d = Rs[k] - (D)P[k];
-          fr += d * d;
-        }
-        for (int k = 0; k < 3; ++k) {
-          D d = ts[k] - (D)P[9 + k];
-          ft += d * d;
-        }
-        // increasing s per thread: a strictly larger value replaces the best
-        radius_take(fr, s, br, ir);
-        radius_take(ft, s, bt, it);
-      }
-    }
+    radius_scan(poses, mask, off, M, 0, kRadiusPer * kBwdBlock, Rs, ts, br, ir, bt, it);
   }
   for (int o = 32; o >= 1; o >>= 1) radius_merge(__shfl_xor(br, o, 64), __shfl_xor(ir, o, 64), br, ir);
   if (lane == 0) {
@@ -787,6 +873,43 @@ __global__ void __launch_bounds__(kBwdBlock, 2) k_bwd_megb(DevBatch b, DevParams
   }
   const int n_out = err_s != kBwdOk ? 0 : n_act;
   for (int k = tid; k < n_out; k += kBwdBlock) rec->active[k] = act[k];
+}
+
+// The radius samples' search of the instances k_bwd_megb<kBwdHead> left a
+// centre for: workgroup y of an instance takes every gridDim.y-th round.
+__global__ void __launch_bounds__(kBwdBlock) k_bwd_radius(DevBatch b, const float *__restrict__ poses,
+                                                          const uint8_t *__restrict__ mask, BwdRec *recs) {
+  __shared__ double red_v[2][kBwdWaves];
+  __shared__ int red_i[2][kBwdWaves];
+  const int j = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (recs[j].status != kBwdOk) return;
+  int64_t off, M64;
+  sample_range(b.sample_off, j, b.total_samples, b.max_samples, off, M64);
+  BwdHand &H = *reinterpret_cast<BwdHand *>(recs[j].cot);
+  D Rs[9], ts[3];
+  for (int k = 0; k < 9; ++k) Rs[k] = H.Rstar[k];
+  for (int k = 0; k < 3; ++k) ts[k] = H.tstar[k];
+  constexpr unsigned round = kRadiusPer * kBwdBlock;
+  D v[2] = {-1, -1};
+  int id[2] = {INT32_MAX, INT32_MAX};
+  radius_scan(poses, mask, off, (unsigned)M64, blockIdx.y * round, gridDim.y * round, Rs, ts, v[0], id[0], v[1],
+              id[1]);
+#pragma unroll
+  for (int c = 0; c < 2; ++c) {
+    for (int o = 32; o >= 1; o >>= 1) radius_merge(__shfl_xor(v[c], o, 64), __shfl_xor(id[c], o, 64), v[c], id[c]);
+    if (lane == 0) {
+      red_v[c][wave] = v[c];
+      red_i[c][wave] = id[c];
+    }
+  }
+  __syncthreads();
+  if (tid < 2) {
+    D best = red_v[tid][0];
+    int s = red_i[tid][0];
+    for (int w = 1; w < kBwdWaves; ++w) radius_merge(red_v[tid][w], red_i[tid][w], best, s);
+    H.v[tid][blockIdx.y] = best;
+    H.id[tid][blockIdx.y] = s;
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -2905,6 +3028,25 @@ Aux *aux_stream() {
   return &a;
 }
 
+void launch_bwd_megb(const DevBatch &b, const DevParams &p, const float *poses, const uint8_t *mask,
+                     const int32_t *trace, const double *g_radii, const float *g_centre, const InstRec *inst,
+                     MegbRec *megb, BwdRec *recs, float4 *ckpt, int ck, hipStream_t stream) {
+  const dim3 g(b.n_inst), t(kBwdBlock);
+  if (b.max_samples < kRadiusSplit) {
+    hipLaunchKernelGGL(k_bwd_megb<kBwdWhole>, g, t, 0, stream, b, p, poses, mask, trace, g_radii, g_centre, inst, megb,
+                       recs, ckpt, ck, 0);
+    return;
+  }
+  constexpr int64_t round = kRadiusPer * kBwdBlock;
+  const int64_t cap = std::clamp<int64_t>(kRadiusGrid / b.n_inst, 1, kRadiusGroups);
+  const int nr = (int)std::min<int64_t>(cap, (b.max_samples + round - 1) / round);
+  hipLaunchKernelGGL(k_bwd_megb<kBwdHead>, g, t, 0, stream, b, p, poses, mask, trace, g_radii, g_centre, inst, megb,
+                     recs, ckpt, ck, nr);
+  hipLaunchKernelGGL(k_bwd_radius, dim3(b.n_inst, nr), t, 0, stream, b, poses, mask, recs);
+  hipLaunchKernelGGL(k_bwd_megb<kBwdTail>, g, t, 0, stream, b, p, poses, mask, trace, g_radii, g_centre, inst, megb,
+                     recs, ckpt, ck, nr);
+}
+
 }  // namespace
 
 hipError_t launch_backward(const DevBatch &b, const DevParams &p, const float *poses, const uint8_t *mask,
@@ -2924,13 +3066,11 @@ hipError_t launch_backward(const DevBatch &b, const DevParams &p, const float *p
     if (a && hipEventRecord(a->fork, stream) == hipSuccess && hipStreamWaitEvent(a->s, a->fork, 0) == hipSuccess) {
       hipLaunchKernelGGL(k_bwd_frame, dim3(n), dim3(kMaxDirs), 0, a->s, b, p, inst, kp, tan, max_dirs);
       hipError_t e = hipEventRecord(a->join, a->s);
-      hipLaunchKernelGGL(k_bwd_megb, dim3(n), dim3(kBwdBlock), 0, stream, b, p, poses, mask, trace, g_radii,
-                         g_centre, inst, megb, recs, ckpt, ck);
+      launch_bwd_megb(b, p, poses, mask, trace, g_radii, g_centre, inst, megb, recs, ckpt, ck, stream);
       if (e == hipSuccess) e = hipStreamWaitEvent(stream, a->join, 0);
       if (e != hipSuccess) return e;  // no join: nothing that reads the frame tangents is launched
     } else {
-      hipLaunchKernelGGL(k_bwd_megb, dim3(n), dim3(kBwdBlock), 0, stream, b, p, poses, mask, trace, g_radii,
-                         g_centre, inst, megb, recs, ckpt, ck);
+      launch_bwd_megb(b, p, poses, mask, trace, g_radii, g_centre, inst, megb, recs, ckpt, ck, stream);
       hipLaunchKernelGGL(k_bwd_frame, dim3(n), dim3(kMaxDirs), 0, stream, b, p, inst, kp, tan, max_dirs);
     }
   }
