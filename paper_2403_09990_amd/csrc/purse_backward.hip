@@ -1366,33 +1366,24 @@ __global__ void __launch_bounds__(kMaxDirs) k_bwd_frame(DevBatch b, DevParams p,
   }
   for (int k = 0; k < 9; ++k) F.Ra[k] = F.Rc[k];
   for (int r = 0; r < 3; ++r) F.ta[r] = F.tc[r];
-  if ((I.status & PURSE_INST_ANCHOR_ITERATED) && I.has_anchor) {
+  // (k_bwd_anchor2d replaces the anchor's tangents of 2D-3D instances)
+  if (!is2d && (I.status & PURSE_INST_ANCHOR_ITERATED) && I.has_anchor) {
     KpDual kpl;
     kpl.kp = kprec + I.kp_off;
     kpl.i_d = i_d;
     kp_tangent(I, kprec[I.kp_off + i_d], L + 4 * i_d, b.bounds[I.kp_off + i_d], p.kappa, c, kpl.tk);
-    if (is2d) {
-      PoseT<Dual<float>> x;
-      for (int k = 0; k < 9; ++k) x.R[k] = F.Rc[k];
-      for (int r = 0; r < 3; ++r) x.t[r] = F.tc[r];
-      int nfb = 0;
-      run_trajectory<PURSE_KIND_2D3D>(I, F, kpl, x, p, false, nfb);
-      for (int k = 0; k < 9; ++k) F.Ra[k] = Dual<float>(I.Ra[k], x.R[k].d);
-      for (int r = 0; r < 3; ++r) F.ta[r] = Dual<float>(I.ta[r], x.t[r].d);
-    } else {
-      Pose x, dx;
-      for (int k = 0; k < 9; ++k) {
-        x.R[k] = F.Rc[k].v;
-        dx.R[k] = F.Rc[k].d;
-      }
-      for (int r = 0; r < 3; ++r) {
-        x.t[r] = F.tc[r].v;
-        dx.t[r] = F.tc[r].d;
-      }
-      anchor_tangent_3d(I, kpl.kp, i_d, kpl.tk, p.n_iters, (p.flags & PURSE_FLAG_FORCE_FP64_POLAR) != 0, x, dx);
-      for (int k = 0; k < 9; ++k) F.Ra[k] = Dual<float>(I.Ra[k], dx.R[k]);
-      for (int r = 0; r < 3; ++r) F.ta[r] = Dual<float>(I.ta[r], dx.t[r]);
+    Pose x, dx;
+    for (int k = 0; k < 9; ++k) {
+      x.R[k] = F.Rc[k].v;
+      dx.R[k] = F.Rc[k].d;
     }
+    for (int r = 0; r < 3; ++r) {
+      x.t[r] = F.tc[r].v;
+      dx.t[r] = F.tc[r].d;
+    }
+    anchor_tangent_3d(I, kpl.kp, i_d, kpl.tk, p.n_iters, (p.flags & PURSE_FLAG_FORCE_FP64_POLAR) != 0, x, dx);
+    for (int k = 0; k < 9; ++k) F.Ra[k] = Dual<float>(I.Ra[k], dx.R[k]);
+    for (int r = 0; r < 3; ++r) F.ta[r] = Dual<float>(I.ta[r], dx.t[r]);
   }
   float *tan = tan_all + ((int64_t)j * max_dirs + d) * 27;
   for (int k = 0; k < 9; ++k) tan[k] = F.Rc[k].d;
@@ -1646,6 +1637,42 @@ __device__ __forceinline__ uint8_t run_trajectory_group(const InstRec &I, const 
     for (int r = 0; r < 3; ++r) x.t[r] = ta[r] + lo * (x.t[r] - ta[r]);
   }
   return PURSE_MASK_FEASIBLE | PURSE_MASK_PULLED_IN;
+}
+
+// Tangents of a remote 2D-3D anchor, after k_bwd_frame: the trajectory from the
+// centre in dual numbers, G lanes per direction, 64 / G directions per
+// workgroup.  (An instance with such an anchor is rare and its chain long: one
+// lane per direction inside k_bwd_frame took a 512-instance batch that holds
+// one of 42 keypoints from 1.5 to 4.3 ms; spread, to 2.3 ms.)
+template <int G>
+__global__ void __launch_bounds__(64) k_bwd_anchor2d(DevBatch b, DevParams p, const InstRec *__restrict__ inst,
+                                                     const KpRec *__restrict__ kprec, float *tan_all, int max_dirs) {
+  const int j = blockIdx.x;
+  const int st = inst[j].status;
+  if (!(st & PURSE_INST_ANCHOR_ITERATED) || (st & 0xFF) != PURSE_INST_OK || inst[j].kind != PURSE_KIND_2D3D) return;
+  const InstRec I = inst[j];
+  const int dpk = dirs_per_kp(PURSE_KIND_2D3D);
+  const int d = blockIdx.y * (64 / G) + threadIdx.x / G, q = threadIdx.x % G;
+  // (see k_bwd_frame; whole lane groups leave past the last direction)
+  if (!inst_record_ok(I, inst_view(b, j)) || !I.has_anchor || d >= I.n_kp * dpk) return;
+  const int i_d = d / dpk, c = d % dpk;
+  float *tan = tan_all + ((int64_t)j * max_dirs + d) * 27;
+  FrameT<DF> F;
+  PoseT<DF> x;
+  for (int k = 0; k < 9; ++k) F.Rc[k] = F.Ra[k] = x.R[k] = DF(I.Rc[k], tan[k]);
+  for (int r = 0; r < 3; ++r) {
+    F.tc[r] = F.ta[r] = x.t[r] = DF(I.tc[r], tan[9 + r]);
+    F.oc[r] = DF(I.oc[r], tan[12 + r]);
+  }
+  KpDual kpl;
+  kpl.kp = kprec + I.kp_off;
+  kpl.i_d = i_d;
+  kp_tangent(I, kprec[I.kp_off + i_d], b.shapes + 4 * (I.kp_off + i_d), b.bounds[I.kp_off + i_d], p.kappa, c, kpl.tk);
+  run_trajectory_group<G>(I, F, kpl, q, x, p);
+  if (q == 0) {
+    for (int k = 0; k < 9; ++k) tan[15 + k] = x.R[k].d;
+    for (int r = 0; r < 3; ++r) tan[24 + r] = x.t[r].d;
+  }
 }
 
 // k_bwd_traj for 2D-3D instances with G lanes per direction: work item
@@ -3099,7 +3126,8 @@ hipError_t launch_backward(const DevBatch &b, const DevParams &p, const float *p
   const int n = b.n_inst;
   const int ck = ckpt_spacing(p.ckpt_every);
   const int max_dirs = 6 * b.max_kp;
-  // k_bwd_frame on the device's auxiliary stream, concurrently with
+  const dim3 ga(n, (max_dirs + 64 / kTrajGroup - 1) / (64 / kTrajGroup));
+  // k_bwd_frame (and the remote anchors' tangents) on the device's auxiliary stream, concurrently with
   // k_bwd_megb (a fork and a join by events, which graph capture records as
   // edges); on the caller's stream when there is none
   {
@@ -3107,6 +3135,7 @@ hipError_t launch_backward(const DevBatch &b, const DevParams &p, const float *p
     Aux *a = aux_stream();
     if (a && hipEventRecord(a->fork, stream) == hipSuccess && hipStreamWaitEvent(a->s, a->fork, 0) == hipSuccess) {
       hipLaunchKernelGGL(k_bwd_frame, dim3(n), dim3(kMaxDirs), 0, a->s, b, p, inst, kp, tan, max_dirs);
+      hipLaunchKernelGGL(k_bwd_anchor2d<kTrajGroup>, ga, dim3(64), 0, a->s, b, p, inst, kp, tan, max_dirs);
       hipError_t e = hipEventRecord(a->join, a->s);
       launch_bwd_megb(b, p, poses, mask, trace, g_radii, g_centre, inst, megb, recs, ckpt, ck, stream);
       if (e == hipSuccess) e = hipStreamWaitEvent(stream, a->join, 0);
@@ -3114,6 +3143,7 @@ hipError_t launch_backward(const DevBatch &b, const DevParams &p, const float *p
     } else {
       launch_bwd_megb(b, p, poses, mask, trace, g_radii, g_centre, inst, megb, recs, ckpt, ck, stream);
       hipLaunchKernelGGL(k_bwd_frame, dim3(n), dim3(kMaxDirs), 0, stream, b, p, inst, kp, tan, max_dirs);
+      hipLaunchKernelGGL(k_bwd_anchor2d<kTrajGroup>, ga, dim3(64), 0, stream, b, p, inst, kp, tan, max_dirs);
     }
   }
   // the tangent kernels walk lists of the (instance, active sample,
