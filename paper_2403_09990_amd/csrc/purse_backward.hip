@@ -14,6 +14,7 @@
 // 2. k_bwd_frame: per input direction, the tangent of the centre fit, pivot
 //    and anchor (of a converged fit by implicit differentiation of its normal
 //    equations; else the fit re-run in float64 dual numbers from its start).
+//    A remote 2D-3D anchor's tangents are k_bwd_anchor2d's.
 // 3. k_bwd_traj: per (active sample, input direction), the trajectory re-run
 //    in float32 dual numbers gives the tangent of the sample's pose, dotted
 //    with its cotangent.
