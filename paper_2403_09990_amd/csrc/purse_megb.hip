@@ -246,14 +246,14 @@ struct Domination {
 // of its value relatively (and unit quaternions are so to 2e-7), and xw, xs
 // within 4e-7, against 1e-5 here.
 struct DomBall {
-  float chk;    // a centre is inside while |C - C_ref|^2 <= chk
+  float chk;    // a centre is outside from |C - C_ref|^2 > chk on
   float four;   // (2 rho)^2
   float xin;    // samples nearer than this are dominated whatever their direction
   float eta;
 };
 __device__ __forceinline__ DomBall dom_ball(const Domination &S, float rho) {
   DomBall b;
-  if (S.n == 0) return DomBall{FLT_MAX, FLT_MAX, -1.f, FLT_MAX};
+  if (S.n == 0) return DomBall{INFINITY, FLT_MAX, -1.f, FLT_MAX};
   const float rw = __builtin_amdgcn_sqrtf(S.xmax);
   b.chk = rho * rho * (1.f - 1e-5f);
   b.four = 4.f * rho * rho * (1.f + 4e-5f);
@@ -942,7 +942,7 @@ __device__ __forceinline__ void chain_run(const ChainShared &S, const int64_t *_
     const bool global = (no_prune || stalled || early) && n_feas > cap;
     if (use_dm && !in_dm(C0)) use_dm = false;
     float4 Cref = C0;
-    DomBall ball = DomBall{FLT_MAX, FLT_MAX, -1.f, FLT_MAX};
+    DomBall ball = DomBall{INFINITY, FLT_MAX, -1.f, FLT_MAX};
     float rref = 0.f;
     if (!global) {
       // -------------------------------------------------------------- rescan
@@ -1123,7 +1123,7 @@ __device__ __forceinline__ void chain_run(const ChainShared &S, const int64_t *_
           }
           if (lane == 63) {
             sh_n = at;
-            if (at > (unsigned)cap) st_mode = 1;
+            if (at > (unsigned)cap || at == 0u) st_mode = 1;  // (no entry: no distance is a number)
           }
         }
         __syncthreads();
@@ -1222,7 +1222,7 @@ __device__ __forceinline__ void chain_run(const ChainShared &S, const int64_t *_
           }
         par ^= 1;
         if (CHAIN == 0 && tid == 0 && (i - 1) % ck == 0) ckq[(i - 1) / ck] = C;
-        C = geodesic_step(C, D[bi], i, chain);
+        if (bi < M) C = geodesic_step(C, D[bi], i, chain);  // (no winner: no key is a number)
         if (tid == 0) tr[2 * (i - 1)] = bi;
         if (i > T - avg && wave == 0) accumulate_iterate(C, chain, acc);
         ++i;
@@ -1287,16 +1287,18 @@ __device__ __forceinline__ void chain_run(const ChainShared &S, const int64_t *_
       // square root is within the slack).  Rotation: |C + C_ref|^2 = 4 -
       // |C - C_ref|^2 for unit quaternions (C stays near C_ref within a stage;
       // the form only feeds bounds).
-      auto drift = [&](float4 Cc, bool &inside) {  // inside: C is in the ball the shell holds for
+      // inside: C is in the ball the shell holds for (a centre that is no number,
+      // after a sample that is none, counts as inside: every stage takes a step)
+      auto drift = [&](float4 Cc, bool &inside) {
         float dC2;
         if (CHAIN == 0) {
           const float e0 = Cc.x - Cref.x, e1 = Cc.y - Cref.y, e2 = Cc.z - Cref.z, e3 = Cc.w - Cref.w;
           const float xc = fmaf(e3, e3, fmaf(e2, e2, fmaf(e1, e1, e0 * e0)));
-          inside = xc <= ball.chk;
+          inside = !(xc > ball.chk);
           dC2 = (2.f * xc) * (4.f - xc);
         } else {
           dC2 = sqdist(Cc, Cref, chain);
-          inside = dC2 <= ball.chk;
+          inside = !(dC2 > ball.chk);
         }
         return __builtin_amdgcn_sqrtf(dC2);
       };
@@ -2042,6 +2044,10 @@ __global__ void __launch_bounds__(kBlock) k_megb_exact(const int64_t *__restrict
     double r2hat;
     int ihat;
     block_max(dmax, imax, r2hat, ihat);
+    if (ihat == INT32_MAX) {  // no distance is a number: the descent's centre is kept
+      if (tid == 0) fail_s = 1;
+      break;
+    }
     const double rhat = sqrt(fmax(r2hat, 0.0));
     for (int k = tid; k < kExactBins; k += kBlock) hist[k] = 0;
     __syncthreads();
@@ -2052,7 +2058,7 @@ __global__ void __launch_bounds__(kBlock) k_megb_exact(const int64_t *__restrict
       if (!feasible_pt(D[s], chain)) continue;
       double x[4];
       exact_point(D, s, chain, ref, x);
-      const int bin = min(kExactBins - 1, (int)(sqrt(exact_d2(x, ref)) / binw));
+      const int bin = max(0, min(kExactBins - 1, (int)(sqrt(exact_d2(x, ref)) / binw)));
       atomicAdd(&hist[bin], 1);
     }
     __syncthreads();
