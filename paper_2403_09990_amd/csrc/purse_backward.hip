@@ -1763,7 +1763,6 @@ __host__ __device__ constexpr size_t rev_lds(int passes, int iters, int row) {
          (size_t)kRevSamples * kRevGroup * (size_t)(iters > 0 ? iters : 1);
 }
 constexpr int kRevPoseRow = 12;                // a pass's input pose
-constexpr int kRevSolveRow = kRevPoseRow + 24; // and its factor: 15 entries, 6 reciprocal pivots
 constexpr int kRevPolarRow = kRevPoseRow + 12; // (3D-3D) and its M
 
 // R <- proj_SO3(M) in float64 from the previous iteration's rotation in R, by
@@ -1853,7 +1852,7 @@ __device__ __forceinline__ void rev_put_pose(float *row, const RevPoseT<double> 
 // z_min.  Projection decisions: bit rr of cl is lane q's keypoint
 // q + kRevGroup rr; taken from cl when use_cl, else decided here and
 // recorded in cl.
-template <bool FIRST, typename T, bool MATRIX = true>
+template <bool FIRST, typename T>
 __device__ __forceinline__ bool rev_normal_eqs(const KpRec *__restrict__ kp, int n, int q, const float K[4],
                                                const T oc[3], float z_min, float band, const RevPoseT<T> &xk,
                                                const RevPoseT<T> &x, T A[21], T g[6], uint32_t &cl, bool use_cl) {
@@ -1894,7 +1893,7 @@ __device__ __forceinline__ bool rev_normal_eqs(const KpRec *__restrict__ kp, int
     gn_accumulate<T>(P, pt, iz, T(K[0]), T(K[1]), w, rt0, rt1, A, g);
   }
   static_assert(kRevGroup == 16, "group_sums");
-  if constexpr (MATRIX) group_sums<21>(A);  // (else A is not formed)
+  group_sums<21>(A);
   group_sums<6>(g);
   return group_and<kRevGroup>(ok);
 }
@@ -2164,27 +2163,15 @@ __device__ __forceinline__ void rev_keypoints(const KpRec *__restrict__ kp, int 
 
 // One pass of the reverse sweep: the normal equations at x recomputed, the
 // update's and the solve's adjoints, the keypoints' adjoints; xb holds the
-// cotangent of the pass's output on entry and of its input on return.  (SOLVE:
-// the factor is read from the tape, and only the right side formed at x: the
-// step has to be the one of the residuals that the adjoints below see.)
-template <bool FIRST, bool SOLVE>
+// cotangent of the pass's output on entry and of its input on return.
+template <bool FIRST>
 __device__ __forceinline__ void rev_pass(const KpRec *__restrict__ kp, int n, int q, const float K[4],
-                                         const float oc[3], float z_min, uint32_t clbits, const float *solve,
-                                         const RevPose &xk,
+                                         const float oc[3], float z_min, uint32_t clbits, const RevPose &xk,
                                          const RevPose &x, RevPose &xb, RevPose &xkb, float ob_u[3],
                                          float kb[kRevPerLane][6]) {
   float A[21], g[6], L[21], dinv[6], d[6];
-  rev_normal_eqs<FIRST, float, !SOLVE>(kp, n, q, K, oc, z_min, 1.f, xk, x, A, g, clbits, true);
-  if constexpr (SOLVE) {
-#pragma unroll
-    for (int i = 1, m = 0; i < 6; ++i)
-#pragma unroll
-      for (int c = 0; c < i; ++c, ++m) L[tri(i, c)] = solve[m];
-#pragma unroll
-    for (int m = 0; m < 6; ++m) dinv[m] = solve[15 + m];
-  } else {
-    chol6_factor<float>(A, L, dinv);
-  }
+  rev_normal_eqs<FIRST, float>(kp, n, q, K, oc, z_min, 1.f, xk, x, A, g, clbits, true);
+  chol6_factor<float>(A, L, dinv);
   chol6_subst<float>(L, dinv, g, d);
   RevPose xin;
   float db[6];
@@ -2320,14 +2307,14 @@ __device__ __forceinline__ bool rev_feasible(const KpRec *__restrict__ kp, int n
 }
 
 // One wavefront per kRevSamples active samples; dynamic LDS: the tape,
-// kRevSamples x n_iters x n_gn rows.  SOLVE: the rows keep each pass's factor
-// too, so that the sweep does not sum and factor the normal matrix again, at 144
-// bytes a row: for calls of so few samples that a compute unit holds one
-// wavefront anyway (one instance of 12 keypoints, 100 iterations: 1.22 -> 1.13 ms).
-// (With the step on the tape as well the sweep was another 0.1 ms shorter and up
-// to eight times as far off: it then differentiates a step that is not the one
-// of the rounded pose.)
-template <bool SOLVE>
+// kRevSamples x n_iters x n_gn poses.  (The passes' factors on the tape, which
+// the float64 recomputation has anyway, made one instance of 12 keypoints and
+// 100 iterations 1.22 -> 1.13 ms, but their rows leave a compute unit one
+// wavefront, so a batch cannot keep them, and the factor of the unrounded pose
+// has other last bits: an instance's gradients then depend on its batch.  With
+// the step on the tape as well the sweep was another 0.1 ms shorter and up to
+// eight times as far off: it then differentiates a step that is not the one of
+// the rounded pose.)
 __global__ void __launch_bounds__(64) k_bwd_rev2d(DevBatch b, DevParams p, const InstRec *__restrict__ inst,
                                                   const KpRec *__restrict__ kprec, const BwdRec *recs,
                                                   const int64_t *__restrict__ item_off,
@@ -2336,7 +2323,7 @@ __global__ void __launch_bounds__(64) k_bwd_rev2d(DevBatch b, DevParams p, const
   const int64_t total = item_off[b.n_inst];
   const int lane = threadIdx.x, grp = lane / kRevGroup, q = lane % kRevGroup;
   const int passes = p.n_iters * p.n_gn;
-  constexpr int kRow = SOLVE ? kRevSolveRow : kRevPoseRow;
+  constexpr int kRow = kRevPoseRow;
   float *tape = tape_all + (int64_t)grp * passes * kRow;
   uint8_t *clb = reinterpret_cast<uint8_t *>(tape_all + (int64_t)kRevSamples * (passes > 0 ? passes : 1) * kRow) +
                  (int64_t)grp * (p.n_iters > 0 ? p.n_iters : 1) * kRevGroup;
@@ -2374,25 +2361,13 @@ __global__ void __launch_bounds__(64) k_bwd_rev2d(DevBatch b, DevParams p, const
       uint32_t cl = 0u;
       for (int gs = 0; gs < p.n_gn && ok; ++gs) {
         const int ps = itr * p.n_gn + gs;
-        float *row = tape + kRow * ps;
-        if (q == 0) rev_put_pose(row, x);
+        if (q == 0) rev_put_pose(tape + kRow * ps, x);
         double A[21], g[6], L[21], dinv[6], d[6];
         ok = gs == 0 ? rev_normal_eqs<true, double>(kp, n, q, I.K, ocd, p.z_min, band, xk, x, A, g, cl, false)
                      : rev_normal_eqs<false, double>(kp, n, q, I.K, ocd, p.z_min, band, xk, x, A, g, cl, true);
         ok = ok && near_solve(A, g, L, dinv, d);
         if (!ok) break;
         near_update(d, ocd, x.R, x.t);
-        if (SOLVE && q == 0) {
-          double v[24];
-          v[21] = v[22] = v[23] = 0.0;
-#pragma unroll
-          for (int i = 1, m = 0; i < 6; ++i)
-#pragma unroll
-            for (int c = 0; c < i; ++c, ++m) v[m] = L[tri(i, c)];
-#pragma unroll
-          for (int m = 0; m < 6; ++m) v[15 + m] = dinv[m];
-          rev_put<24>(row + kRevPoseRow, v);
-        }
       }
       clb[itr * kRevGroup + q] = (uint8_t)cl;
     }
@@ -2524,9 +2499,9 @@ __global__ void __launch_bounds__(64) k_bwd_rev2d(DevBatch b, DevParams p, const
           for (int m = 0; m < 9; ++m) xin.R[m] = tx[m];
 #pragma unroll
           for (int m = 0; m < 3; ++m) xin.t[m] = tx[9 + m];
-          rev_pass<false, SOLVE>(kp, n, q, I.K, oc, p.z_min, clbi, tx + kRevPoseRow, xk, xin, xb, xkb, ob_u, kb);
+          rev_pass<false>(kp, n, q, I.K, oc, p.z_min, clbi, xk, xin, xb, xkb, ob_u, kb);
         }
-        rev_pass<true, SOLVE>(kp, n, q, I.K, oc, p.z_min, clbi, tk + kRevPoseRow, xk, xk, xb, xkb, ob_u, kb);
+        rev_pass<true>(kp, n, q, I.K, oc, p.z_min, clbi, xk, xk, xb, xkb, ob_u, kb);
       }
       // the start: even s rotate the centre by E about the pivot, odd s shift it
       if ((s & 1) == 0) {
@@ -3165,22 +3140,10 @@ hipError_t launch_backward(const DevBatch &b, const DevParams &p, const float *p
   const bool reverse = lds2 <= kRevLds && !(p.flags & PURSE_FLAG_FORWARD_TANGENTS);
   if (reverse) {
     hipLaunchKernelGGL(k_bwd_items_rev, dim3(1), dim3(1024), 0, stream, b, inst, recs, (int)PURSE_KIND_2D3D, items);
-    // with the factors on the tape while the active sets, at most kMaxActive
-    // samples each, fill no more than one wavefront per compute unit and the
-    // rows fit its LDS
-    int dev = 0, n_cu = 256, lds_block = 65536;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-      n_cu = 256;
-    if (hipDeviceGetAttribute(&lds_block, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess)
-      lds_block = 65536;
-    const size_t lds_solve = rev_lds(passes, p.n_iters, kRevSolveRow);
-    if ((int64_t)n * (kMaxActive / kRevSamples) <= n_cu && lds_solve <= (size_t)lds_block)
-      hipLaunchKernelGGL(k_bwd_rev2d<true>, dim3(n_cu), dim3(64), lds_solve, stream, b, p, inst, kp, recs, items,
-                         tan, contrib, max_dirs);
-    else
-      hipLaunchKernelGGL(k_bwd_rev2d<false>, dim3(kItemGrid), dim3(64), lds2, stream, b, p, inst, kp, recs, items,
-                         tan, contrib, max_dirs);
+    // (no more wavefronts than full active sets take)
+    const int grid = (int)std::min<int64_t>(kItemGrid, (int64_t)n * (kMaxActive / kRevSamples));
+    hipLaunchKernelGGL(k_bwd_rev2d, dim3(grid), dim3(64), lds2, stream, b, p, inst, kp, recs, items, tan, contrib,
+                       max_dirs);
   } else {
     hipLaunchKernelGGL(k_bwd_items, dim3(1), dim3(1024), 0, stream, b, inst, recs, (int)PURSE_KIND_2D3D, kTrajGroup,
                        items);
