@@ -1755,6 +1755,12 @@ constexpr int kRevGroup = 16;
 constexpr int kRevPerLane = (PURSE_MAX_KP + kRevGroup - 1) / kRevGroup;
 constexpr int kRevSamples = 64 / kRevGroup;  // active samples per wavefront
 constexpr size_t kRevLds = 65536;              // LDS of a reverse-sweep workgroup at most
+// ... and with M in the 3D-3D rows: four wavefronts, one per SIMD, still share
+// a compute unit (91 iterations).  512 instances, without M / with it: 2.19 /
+// 2.11 ms at 91 iterations, 2.04 / 2.20 at 92, 3.09 / 3.89 at 146; one instance
+// gains 3-7 % on either side of the line, but the rule must not know the batch (the
+// same gradients in each).
+constexpr size_t kRevKeepLds = 40960;
 
 // LDS of a reverse-sweep workgroup: per sample, a row of `row` floats per pass
 // (the tape) and a byte of clamp bits per lane and iteration.
@@ -3157,7 +3163,7 @@ hipError_t launch_backward(const DevBatch &b, const DevParams &p, const float *p
   if (reverse3) {
     hipLaunchKernelGGL(k_bwd_items_rev, dim3(1), dim3(1024), 0, s3, b, inst, recs, (int)PURSE_KIND_3D3D,
                        items + (n + 1));
-    if (lds3 <= kRevLds)
+    if (lds3 <= kRevKeepLds)
       hipLaunchKernelGGL(k_bwd_rev3d<true>, dim3(kItemGrid), dim3(64), lds3, s3, b, p, inst, kp, recs,
                          items + (n + 1), tan, contrib, max_dirs);
     else
