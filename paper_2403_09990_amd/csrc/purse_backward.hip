@@ -1160,6 +1160,17 @@ __device__ void anchor_tangent_3d(const InstRec &I, const KpRec *__restrict__ kp
   }
 }
 
+// How far a centre fit is from the record's float32 centre; within kCentreOff
+// it is that one.
+constexpr double kCentreOff = 1e-6;
+__device__ __forceinline__ double centre_off(const InstRec &I, const double R[9], const double t[3]) {
+  double off = 0.0, tm = 0.0;
+  for (int k = 0; k < 9; ++k) off = fmax(off, fabs(R[k] - (double)I.Rc[k]));
+  for (int k = 0; k < 3; ++k) tm = fmax(tm, fabs(t[k]));
+  for (int k = 0; k < 3; ++k) off = fmax(off, fabs(t[k] - (double)I.tc[k]) / (1.0 + tm));
+  return off;
+}
+
 // Tangents of the centre, pivot and anchor along every input direction of an
 // instance.  (It reads nothing k_bwd_megb writes, so the two run
 // concurrently.)  The centre is a stationary point, so its tangent is that of
@@ -1190,6 +1201,7 @@ __global__ void __launch_bounds__(kMaxDirs) k_bwd_frame(DevBatch b, DevParams p,
   __shared__ double R_s[9], t_s[3], ab_s[3];  // centre, model centroid
   __shared__ double L_s[21], dinv_s[6];       // 2D-3D: Cholesky factor of -dg/dx; 3D-3D: (tr(S) I - S)^-1
   __shared__ double st_R[2][9], st_t[2][3], st_cost[2];
+  __shared__ double st_off[2], dlt_buf[PURSE_MAX_KP][7];
   __shared__ int st_ok[2], rerun_s;
   if (d < 64) {
     const bool mine = d < n;
@@ -1211,11 +1223,7 @@ __global__ void __launch_bounds__(kMaxDirs) k_bwd_frame(DevBatch b, DevParams p,
       const ObsCached obs{cz, w_s};
       ok = gn_centre_2d_wave(a, obs, n, I.K, p.centre_gn, (double)p.z_min, R, t);
       // the forward had converged: its centre is this one to float32 rounding
-      double off = 0.0, tm = 0.0;
-      for (int k = 0; k < 9; ++k) off = fmax(off, fabs(R[k] - (double)I.Rc[k]));
-      for (int k = 0; k < 3; ++k) tm = fmax(tm, fabs(t[k]));
-      for (int k = 0; k < 3; ++k) off = fmax(off, fabs(t[k] - (double)I.tc[k]) / (1.0 + tm));
-      ok = ok && off <= 1e-6;
+      ok = ok && centre_off(I, R, t) <= kCentreOff;
       double P[3], pt[3], zz[2], w[3];
       obs(i, zz, w);
       double o[3];
@@ -1294,20 +1302,24 @@ __global__ void __launch_bounds__(kMaxDirs) k_bwd_frame(DevBatch b, DevParams p,
   __syncthreads();
   const bool rerun = rerun_s != 0;
   if (rerun) {
-    // the forward's choice between the two starts: wavefront 0 fits from the
-    // DLT start, wavefront 1 from the weak-perspective start
-    if (d == 0 || d == 64) {
+    // the forward's two starts and fits, by its own functions: wavefront 0 from
+    // the DLT start, wavefront 1 from the weak-perspective start
+    if (d < 128) {
       const int f = d >> 6;
       const ObsCached obs{cz, w_s};
       double R[9], t[3], R0[9], t0[3];
-      bool ok = f == 0 ? dlt_2d(a, cz, n, I.K, R, t) : affine_2d(a, cz, n, I.K, R, t);
+      bool ok = f == 0 ? dlt_2d_wave(a, cz, n, I.K, dlt_buf, R, t) : affine_2d_wave(a, cz, n, I.K, R, t);
       for (int k = 0; k < 9; ++k) R0[k] = R[k];
       for (int k = 0; k < 3; ++k) t0[k] = t[k];
-      if (ok) ok = gn_centre_2d<double>(a, obs, n, I.K, p.centre_gn, (double)p.z_min, R, t);
-      st_ok[f] = ok;
-      for (int k = 0; k < 9; ++k) st_R[f][k] = R0[k];  // the start, not the fit
-      for (int k = 0; k < 3; ++k) st_t[f][k] = t0[k];
-      st_cost[f] = ok ? cost_2d_obs(a, obs, n, I.K, R, t) : 0.0;
+      if (ok) ok = gn_centre_2d_wave(a, obs, n, I.K, p.centre_gn, (double)p.z_min, R, t);
+      const double cost = ok ? cost_2d_wave(a, obs, n, I.K, R, t) : 0.0;
+      if ((d & 63) == 0) {
+        st_ok[f] = ok;
+        for (int k = 0; k < 9; ++k) st_R[f][k] = R0[k];  // the start, not the fit
+        for (int k = 0; k < 3; ++k) st_t[f][k] = t0[k];
+        st_cost[f] = cost;
+        st_off[f] = ok ? centre_off(I, R, t) : INFINITY;
+      }
     }
     __syncthreads();
   }
@@ -1315,9 +1327,11 @@ __global__ void __launch_bounds__(kMaxDirs) k_bwd_frame(DevBatch b, DevParams p,
   const int i_d = d / dpk, c = d % dpk;
   Dual<double> Rd[9], td[3];
   if (rerun) {
-    // from the start whose fit the forward kept (lower cost; ties: the DLT one)
+    // from the start whose fit the forward kept: lower cost (ties: the DLT one),
+    // unless only the other's fit ends at the record's centre (equal costs)
     const bool ok1 = st_ok[0] != 0, ok2 = st_ok[1] != 0;
-    const int f = (ok2 && (!ok1 || st_cost[1] < st_cost[0])) ? 1 : 0;
+    int f = (ok2 && (!ok1 || st_cost[1] < st_cost[0])) ? 1 : 0;
+    if (st_off[f] > kCentreOff && st_off[1 - f] <= kCentreOff) f = 1 - f;
     centre_fit_dual(a, cz, L, n, I.K, p.centre_gn, (double)p.z_min, st_R[f], st_t[f], i_d, c, Rd, td);
   } else {
     double dR[9], dt[3];
