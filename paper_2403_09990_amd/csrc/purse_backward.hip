@@ -1603,11 +1603,11 @@ __device__ __forceinline__ bool feasible2d_group(const KpDual &kpl, int n, int q
   return group_and<G>(ok);
 }
 
-// run_trajectory (2D-3D) on a lane group: iterations, feasibility test,
-// bisection pull-in towards the anchor.
+// The iterations of run_trajectory (2D-3D) on a lane group; false when a step
+// failed.
 template <int G, typename FR>
-__device__ __forceinline__ uint8_t run_trajectory_group(const InstRec &I, const FR &F, const KpDual &kpl, int q,
-                                                        PoseT<DF> &x, const DevParams &p) {
+__device__ __forceinline__ bool iterate_group(const InstRec &I, const FR &F, const KpDual &kpl, int q, PoseT<DF> &x,
+                                              const DevParams &p) {
   const float band = ClampBand<DF>::v;
   const DF oc[3] = {DF(F.oc[0]), DF(F.oc[1]), DF(F.oc[2])};
   bool ok = true;
@@ -1617,7 +1617,15 @@ __device__ __forceinline__ uint8_t run_trajectory_group(const InstRec &I, const 
     for (int gs = 1; gs < p.n_gn && ok; ++gs) ok = gn_pass2d_group<false, G>(kpl, I.n_kp, q, I.K, oc, p.z_min, band, xk, x);
   }
   reorthonormalise(x.R);
-  if (!ok) return PURSE_MASK_FAILED;
+  return ok;
+}
+
+// The whole of it: iterations, feasibility test, bisection pull-in towards the
+// anchor.
+template <int G, typename FR>
+__device__ __forceinline__ uint8_t run_trajectory_group(const InstRec &I, const FR &F, const KpDual &kpl, int q,
+                                                        PoseT<DF> &x, const DevParams &p) {
+  if (!iterate_group<G>(I, F, kpl, q, x, p)) return PURSE_MASK_FAILED;
   if (feasible2d_group<G>(kpl, I.n_kp, q, I.K, x, p.z_min)) return PURSE_MASK_FEASIBLE;
   if (!I.has_anchor) return 0;
   DF Ra[9], ta[3], RtR[9], RaT[9], w[3];
@@ -1655,8 +1663,8 @@ __device__ __forceinline__ uint8_t run_trajectory_group(const InstRec &I, const 
 }
 
 // Tangents of a remote 2D-3D anchor, after k_bwd_frame: the trajectory from the
-// centre in dual numbers, G lanes per direction, 64 / G directions per
-// workgroup.  (An instance with such an anchor is rare and its chain long: one
+// centre in dual numbers (without the pull-in, as the anchor's own), G lanes per
+// direction, 64 / G directions per workgroup.  (An instance with such an anchor is rare and its chain long: one
 // lane per direction inside k_bwd_frame took a 512-instance batch that holds
 // one of 42 keypoints from 1.5 to 4.3 ms; spread, to 2.3 ms.)
 template <int G>
@@ -1683,7 +1691,7 @@ __global__ void __launch_bounds__(64) k_bwd_anchor2d(DevBatch b, DevParams p, co
   kpl.kp = kprec + I.kp_off;
   kpl.i_d = i_d;
   kp_tangent(I, kprec[I.kp_off + i_d], b.shapes + 4 * (I.kp_off + i_d), b.bounds[I.kp_off + i_d], p.kappa, c, kpl.tk);
-  run_trajectory_group<G>(I, F, kpl, q, x, p);
+  iterate_group<G>(I, F, kpl, q, x, p);
   if (q == 0) {
     for (int k = 0; k < 9; ++k) tan[15 + k] = x.R[k].d;
     for (int r = 0; r < 3; ++r) tan[24 + r] = x.t[r].d;
