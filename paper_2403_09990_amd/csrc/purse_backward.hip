@@ -1662,39 +1662,71 @@ __device__ __forceinline__ uint8_t run_trajectory_group(const InstRec &I, const 
   return PURSE_MASK_FEASIBLE | PURSE_MASK_PULLED_IN;
 }
 
-// Tangents of a remote 2D-3D anchor, after k_bwd_frame: the trajectory from the
-// centre in dual numbers (without the pull-in, as the anchor's own), G lanes per
-// direction, 64 / G directions per workgroup.  (An instance with such an anchor is rare and its chain long: one
-// lane per direction inside k_bwd_frame took a 512-instance batch that holds
-// one of 42 keypoints from 1.5 to 4.3 ms; spread, to 2.3 ms.)
+// Tangents of the remote 2D-3D anchors, after k_bwd_frame: the trajectory from
+// the centre in dual numbers (without the pull-in, as the anchor's own), G lanes
+// per direction, 64 / G directions per workgroup and item.  Instances with such an
+// anchor are rare and their chains long: one lane per direction inside
+// k_bwd_frame took a 512-instance batch that holds one of 42 keypoints from 1.5
+// to 4.3 ms; spread, to 2.3 ms.  The workgroups find the instances themselves
+// (wavefronts of 64 records, kAnchorRecs of them in flight) and deal the items
+// of all of them out in turn; a workgroup for every instance and direction
+// block instead was nearly always one that left at once, 3 % of the backward of
+// 60,000 instances of 64 keypoints (18.57 -> 18.04 ms).
+constexpr int kAnchorGrid = 1024, kAnchorRecs = 8;
 template <int G>
 __global__ void __launch_bounds__(64) k_bwd_anchor2d(DevBatch b, DevParams p, const InstRec *__restrict__ inst,
                                                      const KpRec *__restrict__ kprec, float *tan_all, int max_dirs) {
-  const int j = blockIdx.x;
-  const int st = inst[j].status;
-  if (!(st & PURSE_INST_ANCHOR_ITERATED) || (st & 0xFF) != PURSE_INST_OK || inst[j].kind != PURSE_KIND_2D3D) return;
-  const InstRec I = inst[j];
+  constexpr int kPer = 64 / G;  // directions of an item
   const int dpk = dirs_per_kp(PURSE_KIND_2D3D);
-  const int d = blockIdx.y * (64 / G) + threadIdx.x / G, q = threadIdx.x % G;
-  // (see k_bwd_frame; whole lane groups leave past the last direction)
-  if (!inst_record_ok(I, inst_view(b, j)) || !I.has_anchor || d >= I.n_kp * dpk) return;
-  const int i_d = d / dpk, c = d % dpk;
-  float *tan = tan_all + ((int64_t)j * max_dirs + d) * 27;
-  FrameT<DF> F;
-  PoseT<DF> x;
-  for (int k = 0; k < 9; ++k) F.Rc[k] = F.Ra[k] = x.R[k] = DF(I.Rc[k], tan[k]);
-  for (int r = 0; r < 3; ++r) {
-    F.tc[r] = F.ta[r] = x.t[r] = DF(I.tc[r], tan[9 + r]);
-    F.oc[r] = DF(I.oc[r], tan[12 + r]);
-  }
-  KpDual kpl;
-  kpl.kp = kprec + I.kp_off;
-  kpl.i_d = i_d;
-  kp_tangent(I, kprec[I.kp_off + i_d], b.shapes + 4 * (I.kp_off + i_d), b.bounds[I.kp_off + i_d], p.kappa, c, kpl.tk);
-  iterate_group<G>(I, F, kpl, q, x, p);
-  if (q == 0) {
-    for (int k = 0; k < 9; ++k) tan[15 + k] = x.R[k].d;
-    for (int r = 0; r < 3; ++r) tan[24 + r] = x.t[r].d;
+  const int lane = threadIdx.x, q = lane % G;
+  int64_t base = 0;  // items of the instances before
+  for (int j0 = 0; j0 < b.n_inst; j0 += 64 * kAnchorRecs) {
+    int items[kAnchorRecs];
+#pragma unroll
+    for (int u = 0; u < kAnchorRecs; ++u) {
+      const InstRec &r = inst[min(j0 + 64 * u + lane, b.n_inst - 1)];
+      const bool remote = (r.status & PURSE_INST_ANCHOR_ITERATED) && (r.status & 0xFF) == PURSE_INST_OK &&
+                          r.kind == PURSE_KIND_2D3D && r.has_anchor;
+      const int n = min(max(r.n_kp, 0), PURSE_MAX_KP);
+      items[u] = remote && j0 + 64 * u + lane < b.n_inst ? (n * dpk + kPer - 1) / kPer : 0;
+    }
+#pragma unroll
+    for (int u = 0; u < kAnchorRecs; ++u) {
+      for (unsigned long long left = __ballot(items[u] > 0); left; left &= left - 1ull) {
+        const int l = (int)__ffsll((long long)left) - 1, j = j0 + 64 * u + l;
+        const int n_items = __builtin_amdgcn_readlane(items[u], l);
+        const int64_t from = base;
+        base += n_items;
+        int64_t z = ((int64_t)blockIdx.x - from) % (int64_t)gridDim.x;
+        if (z < 0) z += gridDim.x;
+        if (z >= n_items) continue;
+        const InstRec I = inst[j];
+        if (!inst_record_ok(I, inst_view(b, j))) continue;  // (see k_bwd_frame)
+        for (; z < n_items; z += gridDim.x) {
+          const int d = (int)z * kPer + lane / G;
+          if (d >= I.n_kp * dpk) continue;  // (whole lane groups)
+          const int i_d = d / dpk, c = d % dpk;
+          float *tan = tan_all + ((int64_t)j * max_dirs + d) * 27;
+          FrameT<DF> F;
+          PoseT<DF> x;
+          for (int k = 0; k < 9; ++k) F.Rc[k] = F.Ra[k] = x.R[k] = DF(I.Rc[k], tan[k]);
+          for (int r = 0; r < 3; ++r) {
+            F.tc[r] = F.ta[r] = x.t[r] = DF(I.tc[r], tan[9 + r]);
+            F.oc[r] = DF(I.oc[r], tan[12 + r]);
+          }
+          KpDual kpl;
+          kpl.kp = kprec + I.kp_off;
+          kpl.i_d = i_d;
+          kp_tangent(I, kprec[I.kp_off + i_d], b.shapes + 4 * (I.kp_off + i_d), b.bounds[I.kp_off + i_d], p.kappa, c,
+                     kpl.tk);
+          iterate_group<G>(I, F, kpl, q, x, p);
+          if (q == 0) {
+            for (int k = 0; k < 9; ++k) tan[15 + k] = x.R[k].d;
+            for (int r = 0; r < 3; ++r) tan[24 + r] = x.t[r].d;
+          }
+        }
+      }
+    }
   }
 }
 
@@ -3130,7 +3162,8 @@ hipError_t launch_backward(const DevBatch &b, const DevParams &p, const float *p
   const int n = b.n_inst;
   const int ck = ckpt_spacing(p.ckpt_every);
   const int max_dirs = 6 * b.max_kp;
-  const dim3 ga(n, (max_dirs + 64 / kTrajGroup - 1) / (64 / kTrajGroup));
+  const int64_t anchor_items = (int64_t)n * ((max_dirs + 64 / kTrajGroup - 1) / (64 / kTrajGroup));
+  const dim3 ga((unsigned)std::min<int64_t>(kAnchorGrid, anchor_items));
   // k_bwd_frame (and the remote anchors' tangents) on the device's auxiliary stream, concurrently with
   // k_bwd_megb (a fork and a join by events, which graph capture records as
   // edges); on the caller's stream when there is none
