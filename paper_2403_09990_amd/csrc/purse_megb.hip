@@ -33,7 +33,10 @@ namespace {
 constexpr int kBlock = 256;
 constexpr int kWaves = kBlock / 64;
 constexpr int kBins = 256;
-constexpr int kScanSteps = 16;   // steps of a stage of scan steps
+// Steps of a stage of scan steps; after every rescan that left no shell to step
+// on, twice as many, up to kScanMax (samples at one distance from the centre:
+// a rescan costs 6 to 15 scans and changes nothing).
+constexpr int kScanSteps = 16, kScanMax = 1024;
 // samples per thread of the per-sample passes (k_megb_prep, k_megb_radii):
 // kPassPer on instances of at least kPassPerMin samples, else one
 constexpr int kPassPer = 4;
@@ -931,6 +934,7 @@ __device__ __forceinline__ void chain_run(const ChainShared &S, const int64_t *_
 #pragma unroll
   for (int k = 0; k < 9; ++k) acc[k] = 0.f;
   bool stalled = false;
+  int scan_len = kScanSteps;
   int recentre = kRecentreChunks;  // chunks a shell step may scan (set by each rescan)
   int stage_groups = 0;
 
@@ -940,6 +944,7 @@ __device__ __forceinline__ void chain_run(const ChainShared &S, const int64_t *_
     if (i0 > T) break;
     const bool early = i0 <= kEarlyFull;
     const bool global = (no_prune || stalled || early) && n_feas > cap;
+    bool barren = stalled;  // scan steps because the last rescan left no shell
     if (use_dm && !in_dm(C0)) use_dm = false;
     float4 Cref = C0;
     DomBall ball = DomBall{INFINITY, FLT_MAX, -1.f, FLT_MAX};
@@ -1052,6 +1057,7 @@ __device__ __forceinline__ void chain_run(const ChainShared &S, const int64_t *_
         if (tid == 0) st_mode = 1;
         __syncthreads();
       } else if (n_kept > cap) {
+        barren = true;
         for (int level = 0; level < 2; ++level) {
           const float lo = st_lo, wdt = st_w;
           if (!(wdt > 0.f)) {
@@ -1181,29 +1187,39 @@ __device__ __forceinline__ void chain_run(const ChainShared &S, const int64_t *_
       int par = 0;
       if (tid == 0) ++sdg.n_global;
       const bool from_dm = use_dm && !no_prune;
-      const float4 *src = from_dm ? gpt : D;
-      const int n_src = from_dm ? sg.n : M;
-      const int i_end = no_prune ? T : (early ? min(T, kEarlyFull) : min(T, i0 + kScanSteps - 1));
+      const int n_src = sg.n;
+      const int i_end = no_prune ? T : (early ? min(T, kEarlyFull) : min(T, i0 + (barren ? scan_len : kScanSteps) - 1));
+      if (barren) scan_len = min(2 * scan_len, kScanMax);
       while (i <= i_end) {
         if (from_dm && !in_dm(C)) break;  // (never on the stage's first step)
         float bk = -1.f;
         int bi = INT32_MAX;
-        stream_rounds<BLK>(src, n_src, make_float4(-2.f, 0.f, 0.f, 0.f), [&](const float4 *a, int s0) {
+        auto take = [&](float k, int s) {
+          if (better(k, s, bk, bi)) {
+            bk = k;
+            bi = s;
+          }
+        };
+        if (from_dm) {
+          stream_rounds<BLK>(gpt, n_src, make_float4(-2.f, 0.f, 0.f, 0.f), [&](const float4 *a, int s0) {
 #pragma unroll
-          for (int u = 0; u < kUnroll; ++u) {
-            const int q = s0 + u * BLK + tid;
-            if (q < n_src && feasible_pt(a[u], chain)) {
-              const float k = sqdist(C, a[u], chain);
-              if (k >= bk) {
-                const int s = from_dm ? gid[q] : q;
-                if (better(k, s, bk, bi)) {
-                  bk = k;
-                  bi = s;
-                }
+            for (int u = 0; u < kUnroll; ++u) {
+              const int q = s0 + u * BLK + tid;
+              if (q < n_src && feasible_pt(a[u], chain)) {
+                const float k = sqdist(C, a[u], chain);
+                if (k >= bk) take(k, gid[q]);
               }
             }
-          }
-        });
+          });
+        } else {
+          stream_rounds<BLK>(D, M, make_float4(-2.f, 0.f, 0.f, 0.f), [&](const float4 *a, int s0) {
+#pragma unroll
+            for (int u = 0; u < kUnroll; ++u) {
+              const int s = s0 + u * BLK + tid;
+              if (s < M && feasible_pt(a[u], chain)) take(sqdist(C, a[u], chain), s);
+            }
+          });
+        }
         float wk;
         int wi;
         wave_argmax(bk, bi, wk, wi);
@@ -1677,6 +1693,7 @@ __device__ __forceinline__ void chain_run(const ChainShared &S, const int64_t *_
       }
       // after a stage that made no step, a stage of scan steps
       stalled = st_i == i0;
+      if (!stalled) scan_len = kScanSteps;
     }
   }
   // ------------------------------------------------------------------ centre
