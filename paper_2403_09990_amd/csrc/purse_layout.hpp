@@ -125,11 +125,16 @@ struct WsLayout {
 };
 
 // First-phase scratch per (instance, chain): the packed (key, ~id) argmax of
-// every workgroup for two consecutive steps and the centre for two consecutive
-// steps.
+// every workgroup for two consecutive steps, the centre for two consecutive
+// steps, and what each turn to gather the undominated samples left (their ball
+// and their number; a turn that was not taken: 0).
+constexpr int kGathers = 4;
 struct EarlyScratch {
   unsigned long long part[2][kEarlyWG];
   float4 cbuf[2];
+  float4 dm_c[kGathers];
+  float dm_rho[kGathers];
+  int32_t dm_n[kGathers];
 };
 
 // Tile schedule of the sampler, one per launch group (3D-3D; 2D-3D with the

@@ -37,6 +37,7 @@ constexpr int kBins = 256;
 // on, twice as many, up to kScanMax (samples at one distance from the centre:
 // a rescan costs 6 to 15 scans and changes nothing).
 constexpr int kScanSteps = 16, kScanMax = 1024;
+constexpr int kScanRest = 8;  // last steps that are scanned rather than rescanned for
 // samples per thread of the per-sample passes (k_megb_prep, k_megb_radii):
 // kPassPer on instances of at least kPassPerMin samples, else one
 constexpr int kPassPer = 4;
@@ -420,16 +421,54 @@ constexpr int kEarlyBlock = 256;
 constexpr int kEarlyList = 4096;  // undominated samples of a workgroup held in LDS before they are written
 
 // Steps of the first phase: until the undominated samples (about 6, 1.5, 0.6
-// and 0.3 % of all after 16, 32, 48 and 64 steps) are few enough for one
-// workgroup to scan them as fast as a launch takes its step (5 us, about
-// 20,000 entries in the wide variant).
-inline int early_steps(int64_t max_samples, bool wide) {
-  const int64_t m = wide ? max_samples : 4 * max_samples;
-  return m <= (1 << 19) ? kEarlyFull + 1 : (m <= (1 << 21) ? 49 : 65);
+// and 0.3 % of all after 16, 32, 48 and 64 steps of the 2D-3D clouds, up to twice
+// that of the 3D-3D ones) are few enough for one workgroup to scan them as fast
+// as a launch takes its step (5 us, about 20,000 entries in the wide variant),
+// and fit their slots: a chain that starts without them pays rescans over every
+// sample, 1.5 us per 1,000 samples each, so the larger the instance the longer
+// the phase.  Milliseconds with 17, 25 and 33 steps: one instance of 40,000
+// (2D-3D) 0.74, 0.78, 0.81; of 65,536 1.20, 1.24, 1.28 (2D-3D) and 1.50, 1.15, 1.10
+// (3D-3D); of 300,000 (3D-3D) 1.43, 1.33, 1.34; eight of 262,144 1.80, 1.76, 1.51;
+// 130 of 65,536 (narrow) 3.05, 3.73, 3.67 (2D-3D) and 3.59, 4.09, 4.17 (3D-3D), of
+// 100,000 5.27, 5.73, 4.35 and 6.08, 4.60, 4.76.  A short descent ends the phase
+// where its last avg iterates begin.
+inline int early_steps(int64_t m, bool wide, int T, int avg) {
+  int most;
+  if (wide)
+    most = m < (1 << 16) ? 17 : (m <= (1 << 17) ? 25 : (m <= (1 << 19) ? 33 : (m <= (1 << 21) ? 49 : 65)));
+  else
+    most = m <= (1 << 16) ? 17 : (m <= (1 << 17) ? 33 : (m <= (1 << 19) ? 49 : 65));
+  // (narrow: the chains' own workgroups fill the chip, and scan a short descent as fast)
+  return wide || T > 2 * kEarlyFull + avg ? min(most, T - avg) : 0;
 }
 
-__host__ __device__ inline bool early_phase_applies(int64_t M, int T, int avg, int no_prune, int n_early) {
-  return M >= kBigInstance && T > n_early + avg && !no_prune;
+__host__ __device__ inline bool early_phase_applies(int64_t M, int no_prune, int n_early) {
+  return M >= kBigInstance && n_early > 0 && !no_prune;
+}
+
+// The step of each turn to gather.
+__host__ __device__ constexpr int gather_step(int turn) {
+  return turn == 0 ? kEarlyFull + 1 : (turn == 1 ? 25 : (turn == 2 ? 33 : 49));
+}
+
+// The undominated samples held before step i: the ball and the number of the
+// last turn that gathered any (n = 0: none).
+struct Held {
+  float4 C;
+  float rho;
+  int n;
+};
+__device__ __forceinline__ Held held_before(const EarlyScratch &e, int i) {
+  Held h{make_float4(0.f, 0.f, 0.f, 0.f), 0.f, 0};
+  if (i > gather_step(0)) {  // (the loads of all turns in flight together)
+    Held t[kGathers];
+#pragma unroll
+    for (int a = 0; a < kGathers; ++a) t[a] = Held{e.dm_c[a], e.dm_rho[a], e.dm_n[a]};
+#pragma unroll
+    for (int a = 0; a < kGathers; ++a)
+      if (gather_step(a) < i && t[a].n > 0) h = t[a];
+  }
+  return h;
 }
 
 // Elements [sb, se) of workgroup b of a chain: kEarlyWG ranges of a multiple
@@ -482,7 +521,9 @@ __device__ __forceinline__ float4 early_complete(const EarlyScratch &e, int i, c
 // consecutive launches, so a launch never writes what it reads.  Launch
 // kEarlyFull + 1 also gathers the undominated samples about its centre (in
 // LDS, written with one atomic reservation per few thousand), and the later
-// ones scan those while the centre is in their ball.  (2^20 samples: a full
+// ones scan those while the centre is in their ball; when they were too many for
+// their slots, or the centre has left the ball, a later turn gathers again (its
+// state is a turn's own, so that a launch reads none that it writes).  (2^20 samples: a full
 // scan is bound by HBM, 0.36 ms for 64 instances; 64 instances of 2^20 took
 // 32 of them and three passes for a shell by distance, 12.6 ms, and take 17
 // and 32 over the undominated samples.)
@@ -497,7 +538,7 @@ __global__ void __launch_bounds__(kEarlyBlock) k_megb_early(const int64_t *__res
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int64_t off, M64;
   sample_range(sample_off, j, total, max_m, off, M64);
-  if (!early_phase_applies(M64, T, avg, no_prune, n_early)) return;
+  if (!early_phase_applies(M64, no_prune, n_early)) return;
   const int M = (int)M64;  // >= kBigInstance here
   const int first = rec[j].first;
   if (first == INT32_MAX || (int64_t)rec[j].n_feasible <= cap) return;
@@ -517,17 +558,22 @@ __global__ void __launch_bounds__(kEarlyBlock) k_megb_early(const int64_t *__res
   if (b == 0 && tid == 0) {
     e.cbuf[(i + 1) & 1] = C;
     if (chain == 0 && (i - 1) % ck == 0) ckq[(i - 1) / ck] = C;
+    if (i == 1)
+      for (int a = 0; a < kGathers; ++a) e.dm_n[a] = 0;
   }
-  const bool gather = i == kEarlyFull + 1;
   const int slots = M / kShellDiv;
   int32_t *gid = gid_all + chain * gstride + off / kShellDiv;
   float4 *gpt = gpt_all + chain * gstride + off / kShellDiv;
-  const float rho = rec[j].dm_rho[chain];
-  const int n_dm = rec[j].dm_n[chain];
-  const bool pruned = !gather && i > kEarlyFull && rho > 0.f && n_dm <= slots &&
-                      euclid_sq(C, rec[j].dm_c[chain], chain) <= rho * rho * (1.f - 1e-5f);
+  const Held held = held_before(e, i);
+  const bool pruned = held.n > 0 && held.n <= slots &&
+                      euclid_sq(C, held.C, chain) <= held.rho * held.rho * (1.f - 1e-5f);
+  int turn = -1;
+#pragma unroll
+  for (int a = 0; a < kGathers; ++a)
+    if (i == gather_step(a)) turn = a;
+  const bool gather = !pruned && turn >= 0;
   const float4 *src = pruned ? gpt : D;
-  const int n_src = pruned ? n_dm : M;
+  const int n_src = pruned ? held.n : M;
   int sb, se;
   early_range(n_src, b, sb, se);
   __shared__ float red_k[kEarlyBlock / 64];
@@ -545,7 +591,7 @@ __global__ void __launch_bounds__(kEarlyBlock) k_megb_early(const int64_t *__res
   if (keep) ball = dom_ball(dom, dom.rho);
   auto flush = [&]() {  // (whole workgroup)
     const int n = n_list;
-    if (tid == 0) base_s = n ? atomicAdd(&rec[j].dm_n[chain], n) : 0;
+    if (tid == 0) base_s = n ? atomicAdd(&e.dm_n[turn], n) : 0;
     __syncthreads();
     const int base = base_s;
     for (int p = tid; p < n; p += kEarlyBlock)
@@ -594,8 +640,8 @@ __global__ void __launch_bounds__(kEarlyBlock) k_megb_early(const int64_t *__res
     __syncthreads();
     flush();
     if (b == 0 && tid == 0) {
-      rec[j].dm_c[chain] = dom.C;
-      rec[j].dm_rho[chain] = dom.rho;
+      e.dm_c[turn] = dom.C;
+      e.dm_rho[turn] = dom.rho;
     }
   }
   float wk;
@@ -928,7 +974,7 @@ __device__ __forceinline__ void chain_run(const ChainShared &S, const int64_t *_
   const int n_feas = (int)rec[j].n_feasible;
   // the first steps were taken by k_megb_early when the rule selects it, which
   // also gathered the undominated samples
-  const bool ep = early_phase_applies(M64, T, avg, no_prune, n_early) && n_feas > cap;
+  const bool ep = early_phase_applies(M64, no_prune, n_early) && n_feas > cap;
   int32_t *gid = gid_all + chain * gstride + off / kShellDiv;
   float4 *gpt = gpt_all + chain * gstride + off / kShellDiv;
   // Undominated samples whose ball the centre has left are gathered again by
@@ -948,9 +994,11 @@ __device__ __forceinline__ void chain_run(const ChainShared &S, const int64_t *_
     if (lane == 0) {
       st_C = C1;
       st_i = ep ? n_early + 1 : 1;
-      sg.n = ep && rec[j].dm_n[chain] <= slots ? rec[j].dm_n[chain] : 0;
-      sg.rho = ep ? rec[j].dm_rho[chain] : 0.f;
-      sg.C = rec[j].dm_c[chain];
+      Held held{make_float4(0.f, 0.f, 0.f, 0.f), 0.f, 0};
+      if (ep) held = held_before(es[2 * j + chain], n_early + 1);
+      sg.n = held.n <= slots ? held.n : 0;
+      sg.rho = held.rho;
+      sg.C = held.C;
       sg.n_built = 0;
       sdg = ChainDiag{0, 0, 0, 0, 0, 0ll, __builtin_amdgcn_s_memrealtime()};
     }
@@ -961,6 +1009,8 @@ __device__ __forceinline__ void chain_run(const ChainShared &S, const int64_t *_
   float acc[9];
 #pragma unroll
   for (int k = 0; k < 9; ++k) acc[k] = 0.f;
+  // (a descent that is over soon after them scans 2 kEarlyFull steps)
+  const int n_full = !ep && T <= 2 * kEarlyFull + avg ? 2 * kEarlyFull : kEarlyFull;
   bool stalled = false;
   int scan_len = kScanSteps;
   int recentre = kRecentreChunks;  // chunks a shell step may scan (set by each rescan)
@@ -970,10 +1020,10 @@ __device__ __forceinline__ void chain_run(const ChainShared &S, const int64_t *_
     const float4 C0 = st_C;  // the centre; distances and bounds are about Cref, near it
     const int i0 = st_i;
     if (i0 > T) break;
-    const bool early = i0 <= kEarlyFull;
-    const bool global = (no_prune || stalled || early) && n_feas > cap;
-    bool barren = stalled;  // scan steps because the last rescan left no shell
+    const bool early = i0 <= n_full;
     if (use_dm && !in_dm(C0)) use_dm = false;
+    const bool global = (no_prune || stalled || early || (!use_dm && T - i0 < kScanRest)) && n_feas > cap;
+    bool barren = stalled;  // scan steps because the last rescan left no shell
     float4 Cref = C0;
     DomBall ball = DomBall{INFINITY, FLT_MAX, -1.f, FLT_MAX};
     float rref = 0.f;
@@ -1220,7 +1270,7 @@ __device__ __forceinline__ void chain_run(const ChainShared &S, const int64_t *_
       if (tid == 0) ++sdg.n_global;
       const bool from_dm = use_dm && !no_prune;
       const int n_src = sg.n;
-      const int i_end = no_prune ? T : (early ? min(T, kEarlyFull) : min(T, i0 + (barren ? scan_len : kScanSteps) - 1));
+      const int i_end = no_prune ? T : (early ? min(T, n_full) : min(T, i0 + (barren ? scan_len : kScanSteps) - 1));
       if (barren) scan_len = min(2 * scan_len, kScanMax);
       while (i <= i_end) {
         if (from_dm && !in_dm(C)) break;  // (never on the stage's first step)
@@ -2335,8 +2385,8 @@ void launch_megb(const DevBatch &b, const DevParams &p, const float *poses, cons
   const size_t lds = (size_t)cap * (sizeof(float4) + sizeof(int));
   const int no_prune = (p.flags & PURSE_FLAG_NO_PRUNING) ? 1 : 0;
   const int64_t gstride = undominated_stride(total_samples, max_samples);
-  const int n_early = early_steps(max_samples, wide);
-  if (early_phase_applies(max_samples, p.megb_iters, p.megb_avg, no_prune, n_early)) {
+  const int n_early = early_steps(max_samples, wide, p.megb_iters, p.megb_avg);
+  if (early_phase_applies(max_samples, no_prune, n_early)) {
     const dim3 eg((unsigned)kEarlyWG, 2u, (unsigned)n);
     for (int i = 1; i <= n_early; ++i)
       hipLaunchKernelGGL(k_megb_early, eg, dim3(kEarlyBlock), 0, stream, b.sample_off, total_samples, max_samples,
