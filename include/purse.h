@@ -179,7 +179,10 @@ typedef struct purse_params {
  * ckpt_every 5, centre_gn 50, tile 0, flags 0.  Returns PURSE_E_NULL if p is NULL. */
 purse_status purse_default_params(purse_params *p);
 
-/* Bytes of workspace every call below needs for this batch and params. */
+/* Bytes of workspace every call below asks for, for this batch and params.  (With
+ * instances of at least 32,768 samples 5 bytes a sample of it hold samples the
+ * descent searches again; a workspace with half of that, the size asked for
+ * before it grew, is accepted and gives the same results, the ball more slowly.) */
 purse_status purse_workspace_size(const purse_batch *b, const purse_params *p, size_t *bytes);
 
 /*

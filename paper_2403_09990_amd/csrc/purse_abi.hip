@@ -108,15 +108,16 @@ purse::DevParams dev_params(const purse_params *p) {
   return d;
 }
 
-purse::WsLayout layout_for(const purse_batch *b, const purse_params *p) {
+purse::WsLayout layout_for(const purse_batch *b, const purse_params *p, int slot_shift = purse::kSlotShift) {
   return purse::ws_layout(b->n_inst, b->total_kp, b->total_samples, b->max_samples, b->max_kp, p->megb_iters,
-                          p->ckpt_every);
+                          p->ckpt_every, slot_shift);
 }
 
 purse_status check_ws(const purse_batch *b, const purse_params *p, void *ws, size_t ws_bytes) {
   if (!ws) return fail(PURSE_E_NULL, "workspace is NULL");
   if (reinterpret_cast<uintptr_t>(ws) % purse::kAlign) return fail(PURSE_E_WORKSPACE, "workspace not 256-byte aligned");
-  if (ws_bytes < layout_for(b, p).total) return fail(PURSE_E_WORKSPACE, "workspace too small");
+  // (only the undominated samples' slots, the last region, depend on the shift)
+  if (ws_bytes < layout_for(b, p, purse::kSlotShiftMin).total) return fail(PURSE_E_WORKSPACE, "workspace too small");
   return PURSE_OK;
 }
 
@@ -263,14 +264,16 @@ purse_status purse_megb(const purse_batch *b, const purse_params *p, const float
     return fail(PURSE_E_NULL, "an argument is NULL");
   if ((s = check_ws(b, p, ws, ws_bytes))) return s;
   if ((s = check_device())) return s;
-  const purse::WsLayout L = layout_for(b, p);
+  const int shift = ws_bytes >= layout_for(b, p).total ? purse::kSlotShift : purse::kSlotShiftMin;
+  const purse::WsLayout L = layout_for(b, p, shift);
   const purse::DevBatch db = dev_batch(b);
   const purse::DevParams dp = dev_params(p);
+  const purse::DmSlots dms{at<int32_t>(ws, L.gid), at<float4>(ws, L.gpt),
+                           purse::undominated_stride(b->total_samples, b->max_samples, shift), shift};
   purse::launch_megb(db, dp, poses, mask, at<purse::MegbRec>(ws, L.megb), at<float4>(ws, L.quat),
                      at<float4>(ws, L.trans), at<float>(ws, L.dref), at<float4>(ws, L.ckpt),
-                     at<purse::EarlyScratch>(ws, L.early), at<int32_t>(ws, L.gid), at<float4>(ws, L.gpt), centre,
-                     radii, n_feasible, trace, inst_status, b->max_samples, b->total_samples,
-                     static_cast<hipStream_t>(stream));
+                     at<purse::EarlyScratch>(ws, L.early), dms, centre, radii, n_feasible, trace, inst_status,
+                     b->max_samples, b->total_samples, static_cast<hipStream_t>(stream));
   return hip_check(hipGetLastError(), "megb launch");
 }
 

@@ -69,21 +69,29 @@ static_assert(sizeof(MegbRec) == 192, "MegbRec layout");
 // Instances of at least kBigInstance samples take their first descent steps
 // in kEarlyWG workgroups per chain, one launch per step.  The first
 // kEarlyFull steps scan every sample; the next one also gathers the
-// undominated samples (at most one in kShellDiv of the instance's, else none
+// undominated samples (at most one in eight of the instance's, else none
 // are kept), which the later steps and the chain's rescans stream instead of
 // every sample.
 constexpr int64_t kBigInstance = 32768;
 constexpr int kEarlyFull = 16;
 constexpr int kEarlyWG = 64;
 constexpr int kShellBins = 256;
-constexpr int kShellDiv = 8;
 
-// Slots of an instance's undominated samples: [off / kShellDiv, off / kShellDiv
-// + M / kShellDiv) in each chain's array (disjoint between instances, since
-// floor(a) + floor(b) <= floor(a + b)).
-__host__ __device__ inline int64_t undominated_stride(int64_t total_samples, int64_t max_samples) {
-  return max_samples >= kBigInstance ? total_samples / kShellDiv + 1 : 0;
+// Slots of the undominated samples: one for every 2^shift samples, those of an
+// instance [off >> shift, (off >> shift) + (M >> shift)) in each chain's array
+// (disjoint between instances, since floor(a) + floor(b) <= floor(a + b)).
+// kSlotShift in a workspace of the size asked for; a smaller one with room for
+// kSlotShiftMin (2.5 bytes a sample less) is used with that.
+constexpr int kSlotShift = 3, kSlotShiftMin = 4;
+__host__ __device__ inline int64_t undominated_stride(int64_t total_samples, int64_t max_samples, int shift) {
+  return max_samples >= kBigInstance ? (total_samples >> shift) + 1 : 0;
 }
+struct DmSlots {
+  int32_t *id;    // sample ids, [2][stride]
+  float4 *pt;     // their points (quaternion or translation), [2][stride]
+  int64_t stride;
+  int shift;
+};
 
 // Per-step term of the signature that ties the stored iterates to the
 // rotation argmax trace they belong to: the splitmix64 finaliser of (i, id),
@@ -146,7 +154,7 @@ __host__ __device__ inline size_t sched_ints(int64_t n_inst) { return 2 * (size_
 
 // Byte offsets of the workspace regions.
 inline WsLayout ws_layout(int64_t n_inst, int64_t total_kp, int64_t total_samples, int64_t max_samples, int max_kp,
-                          int megb_iters, int ckpt_every) {
+                          int megb_iters, int ckpt_every, int slot_shift = kSlotShift) {
   WsLayout L;
   size_t o = 0;
   L.inst = o;
@@ -178,7 +186,7 @@ inline WsLayout ws_layout(int64_t n_inst, int64_t total_kp, int64_t total_sample
   const bool big = max_samples >= kBigInstance;
   L.early = o;  // [n_inst][2] first-phase scratch
   o += big ? align_up(sizeof(EarlyScratch) * 2 * (size_t)n_inst) : 0;
-  const size_t gs = (size_t)undominated_stride(total_samples, max_samples);
+  const size_t gs = (size_t)undominated_stride(total_samples, max_samples, slot_shift);
   L.gid = o;  // [2][stride] ids of the undominated samples
   o += align_up(sizeof(int32_t) * 2 * gs);
   L.gpt = o;  // [2][stride] their points (quaternion or translation)

@@ -532,8 +532,7 @@ __global__ void __launch_bounds__(kEarlyBlock) k_megb_early(const int64_t *__res
                                                             const float4 *__restrict__ trans, MegbRec *rec,
                                                             EarlyScratch *es, int32_t *trace, float4 *ckpt, int ck,
                                                             int T, int avg, int cap, int no_prune, int n_early,
-                                                            int32_t *gid_all, float4 *gpt_all, int64_t gstride,
-                                                            int i) {
+                                                            DmSlots dms, int i) {
   const int j = blockIdx.z, chain = blockIdx.y, b = blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int64_t off, M64;
@@ -561,9 +560,9 @@ __global__ void __launch_bounds__(kEarlyBlock) k_megb_early(const int64_t *__res
     if (i == 1)
       for (int a = 0; a < kGathers; ++a) e.dm_n[a] = 0;
   }
-  const int slots = M / kShellDiv;
-  int32_t *gid = gid_all + chain * gstride + off / kShellDiv;
-  float4 *gpt = gpt_all + chain * gstride + off / kShellDiv;
+  const int slots = M >> dms.shift;
+  int32_t *gid = dms.id + chain * dms.stride + (off >> dms.shift);
+  float4 *gpt = dms.pt + chain * dms.stride + (off >> dms.shift);
   const Held held = held_before(e, i);
   const bool pruned = held.n > 0 && held.n <= slots &&
                       euclid_sq(C, held.C, chain) <= held.rho * held.rho * (1.f - 1e-5f);
@@ -924,8 +923,7 @@ __device__ __forceinline__ void chain_run(const ChainShared &S, const int64_t *_
                                           int64_t max_m, const float4 *__restrict__ pts, MegbRec *rec,
                                           float *dref_all, int64_t total_samples, int32_t *trace,
                                           float4 *ckpt_all, int ck, int T, int avg, int cap, int no_prune,
-                                          int n_early, const EarlyScratch *es, int32_t *__restrict__ gid_all,
-                                          float4 *__restrict__ gpt_all, int64_t gstride) {
+                                          int n_early, const EarlyScratch *es, DmSlots dms) {
   __shared__ float4 st_C;
   __shared__ int st_i;
   __shared__ float st_theta, st_lo, st_w;
@@ -975,13 +973,13 @@ __device__ __forceinline__ void chain_run(const ChainShared &S, const int64_t *_
   // the first steps were taken by k_megb_early when the rule selects it, which
   // also gathered the undominated samples
   const bool ep = early_phase_applies(M64, no_prune, n_early) && n_feas > cap;
-  int32_t *gid = gid_all + chain * gstride + off / kShellDiv;
-  float4 *gpt = gpt_all + chain * gstride + off / kShellDiv;
+  int32_t *__restrict__ gid = dms.id + chain * dms.stride + (off >> dms.shift);
+  float4 *__restrict__ gpt = dms.pt + chain * dms.stride + (off >> dms.shift);
   // Undominated samples whose ball the centre has left are gathered again by
   // the next pass over every sample.  Their state, which only rescans and scan
   // steps read, and the diagnostics live in LDS (thread 0 writes them between
   // barriers), so that the stepping loops keep their registers.
-  const int slots = ep ? M / kShellDiv : 0;
+  const int slots = ep ? M >> dms.shift : 0;
   __shared__ ChainDm sg;
   __shared__ ChainDiag sdg;
   if (wave == 0) {
@@ -1822,8 +1820,7 @@ __global__ void __launch_bounds__(chain_block<V>(), V == kChainWide ? 1 : 4) k_m
                                                             float *dref_all, int64_t total_samples,
                                                             int32_t *trace, float4 *ckpt, int ck, int T, int avg,
                                                             int cap, int no_prune, int n_early,
-                                                            const EarlyScratch *es, int32_t *gid, float4 *gpt,
-                                                            int64_t gstride) {
+                                                            const EarlyScratch *es, DmSlots dms) {
   extern __shared__ float4 sh_pt[];
   __shared__ unsigned int hist[kBins];
   __shared__ unsigned int cursor[kBins];
@@ -1833,10 +1830,10 @@ __global__ void __launch_bounds__(chain_block<V>(), V == kChainWide ? 1 : 4) k_m
   const ChainShared S{sh_pt, reinterpret_cast<int *>(sh_pt + cap), hist, cursor, chunk_ub, red_k, red_i};
   if (blockIdx.x & 1)
     chain_run<1, V>(S, sample_off, max_m, trans, rec, dref_all, total_samples, trace, ckpt, ck, T, avg, cap,
-                       no_prune, n_early, es, gid, gpt, gstride);
+                       no_prune, n_early, es, dms);
   else
     chain_run<0, V>(S, sample_off, max_m, quat, rec, dref_all, total_samples, trace, ckpt, ck, T, avg, cap,
-                       no_prune, n_early, es, gid, gpt, gstride);
+                       no_prune, n_early, es, dms);
 }
 
 // Signature of an instance's descent, stored with the checkpoints it left, so
@@ -2067,7 +2064,7 @@ __device__ __forceinline__ bool exact_circumsphere(const double P[5][4], int k, 
 __global__ void __launch_bounds__(kBlock) k_megb_exact(const int64_t *__restrict__ sample_off, int64_t total,
                                                        int64_t max_m, const float4 *__restrict__ quat,
                                                        const float4 *__restrict__ trans, MegbRec *rec,
-                                                       const float4 *__restrict__ gpt_all, int64_t gstride) {
+                                                       DmSlots dms) {
   const int j = blockIdx.x >> 1, chain = blockIdx.x & 1;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int64_t off, M64;
@@ -2076,7 +2073,7 @@ __global__ void __launch_bounds__(kBlock) k_megb_exact(const int64_t *__restrict
   const float dm_rho = rec[j].dm_rho[chain];
   const int dm_n = rec[j].dm_n[chain];
   const float4 dm_c = rec[j].dm_c[chain];
-  bool pruned = dm_rho > 0.f && dm_n > 0 && dm_n <= (int)(M64 / kShellDiv);
+  bool pruned = dm_rho > 0.f && dm_n > 0 && dm_n <= (int)(M64 >> dms.shift);
   const int dim = chain ? 3 : 4;
   __shared__ double pts[kExactCap][4];
   __shared__ int hist[kExactBins];
@@ -2126,7 +2123,7 @@ __global__ void __launch_bounds__(kBlock) k_megb_exact(const int64_t *__restrict
     __syncthreads();
   };
   for (;;) {
-    const float4 *D = pruned ? gpt_all + chain * gstride + off / kShellDiv : (chain ? trans : quat) + off;
+    const float4 *D = pruned ? dms.pt + chain * dms.stride + (off >> dms.shift) : (chain ? trans : quat) + off;
     const int M = pruned ? dm_n : (int)M64;
     double dmax = -1.0;
     int imax = INT32_MAX;
@@ -2353,9 +2350,9 @@ __global__ void k_megb_final(int n_inst, const MegbRec *rec, float *centre, doub
 }
 
 void launch_megb(const DevBatch &b, const DevParams &p, const float *poses, const uint8_t *mask, MegbRec *rec,
-                 float4 *quat, float4 *trans, float *dref, float4 *ckpt, EarlyScratch *es, int32_t *gid, float4 *gpt,
-                 float *centre, double *radii, int64_t *n_feasible, int32_t *trace, int32_t *inst_status,
-                 int64_t max_samples, int64_t total_samples, hipStream_t stream) {
+                 float4 *quat, float4 *trans, float *dref, float4 *ckpt, EarlyScratch *es, DmSlots dms, float *centre,
+                 double *radii, int64_t *n_feasible, int32_t *trace, int32_t *inst_status, int64_t max_samples,
+                 int64_t total_samples, hipStream_t stream) {
   const int ck = ckpt_spacing(p.ckpt_every);
   const int n = b.n_inst;
   hipLaunchKernelGGL(k_megb_init, dim3((n + 255) / 256), dim3(256), 0, stream, n, rec);
@@ -2384,26 +2381,25 @@ void launch_megb(const DevBatch &b, const DevParams &p, const float *poses, cons
   const int cap = wide ? chain_cap<kChainWide>() : chain_cap<kChainNarrow>();
   const size_t lds = (size_t)cap * (sizeof(float4) + sizeof(int));
   const int no_prune = (p.flags & PURSE_FLAG_NO_PRUNING) ? 1 : 0;
-  const int64_t gstride = undominated_stride(total_samples, max_samples);
   const int n_early = early_steps(max_samples, wide, p.megb_iters, p.megb_avg);
   if (early_phase_applies(max_samples, no_prune, n_early)) {
     const dim3 eg((unsigned)kEarlyWG, 2u, (unsigned)n);
     for (int i = 1; i <= n_early; ++i)
       hipLaunchKernelGGL(k_megb_early, eg, dim3(kEarlyBlock), 0, stream, b.sample_off, total_samples, max_samples,
-                         quat, trans, rec, es, trace, ckpt, ck, p.megb_iters, p.megb_avg, cap, no_prune, n_early, gid,
-                         gpt, gstride, i);
+                         quat, trans, rec, es, trace, ckpt, ck, p.megb_iters, p.megb_avg, cap, no_prune, n_early,
+                         dms, i);
   }
   if (wide)
     hipLaunchKernelGGL(k_megb_chain<kChainWide>, dim3(2 * n), dim3(chain_block<kChainWide>()), lds, stream,
                        b.sample_off, max_samples, quat, trans, rec, dref, total_samples, trace, ckpt, ck, p.megb_iters,
-                       p.megb_avg, cap, no_prune, n_early, es, gid, gpt, gstride);
+                       p.megb_avg, cap, no_prune, n_early, es, dms);
   else
     hipLaunchKernelGGL(k_megb_chain<kChainNarrow>, dim3(2 * n), dim3(chain_block<kChainNarrow>()), lds, stream,
                        b.sample_off, max_samples, quat, trans, rec, dref, total_samples, trace, ckpt, ck, p.megb_iters,
-                       p.megb_avg, cap, no_prune, n_early, es, gid, gpt, gstride);
+                       p.megb_avg, cap, no_prune, n_early, es, dms);
   if (p.flags & PURSE_FLAG_EXACT_MEB)
     hipLaunchKernelGGL(k_megb_exact, dim3(2 * n), dim3(kBlock), 0, stream, b.sample_off, total_samples, max_samples,
-                       quat, trans, rec, gpt, gstride);
+                       quat, trans, rec, dms);
   if (per4)
     hipLaunchKernelGGL(k_megb_radii<kPassPer>, rgrid, dim3(kBlock), 0, stream, b.sample_off, total_samples,
                        max_samples, poses, mask, rec, trace, p.megb_iters, ck);
