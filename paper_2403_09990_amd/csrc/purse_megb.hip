@@ -1057,7 +1057,11 @@ __device__ __forceinline__ void chain_run(const ChainShared &S, const int64_t *_
       stream_rounds<BLK>(src, n_src, make_float4(-2.f, 0.f, 0.f, 0.f), [&](const float4 *a, int s0) {
 #pragma unroll
         for (int h = 0; h < kUnroll; h += kPer) {
-          const unsigned out = any_dom ? dominated<kPer>(dom, ball, a + h, chain) : 0u;
+          // (a few entries fill the first lanes of a round only)
+          unsigned out = 0u;
+          if (any_dom && s0 + h * BLK < n_src)
+            out = s0 + (h + 1) * BLK < n_src ? dominated<kPer>(dom, ball, a + h, chain)
+                                             : dominated<1>(dom, ball, a + h, chain);
 #pragma unroll
           for (int u = 0; u < kPer; ++u) {
             const int s = s0 + (h + u) * BLK + tid;
