@@ -15,9 +15,11 @@
 //    and anchor (of a converged fit by implicit differentiation of its normal
 //    equations; else the fit re-run in float64 dual numbers from its start).
 //    A remote 2D-3D anchor's tangents are k_bwd_anchor2d's.
-// 3. k_bwd_traj: per (active sample, input direction), the trajectory re-run
-//    in float32 dual numbers gives the tangent of the sample's pose, dotted
-//    with its cotangent.
+// 3. k_bwd_rev2d, k_bwd_rev3d: per active sample, the trajectory recomputed in
+//    float64 and one float32 reverse sweep through it, dotted with the tangents
+//    of the frame; or (by flag, or when the trajectory's poses exceed the LDS)
+//    k_bwd_traj: per (active sample, input direction), the trajectory re-run in
+//    float32 dual numbers, its pose's tangent dotted with the cotangent.
 // 4. k_bwd_reduce: per direction, the sum over active samples in a fixed
 //    order, scattered into the gradient arrays.
 #include <algorithm>

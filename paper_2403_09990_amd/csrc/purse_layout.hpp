@@ -69,13 +69,12 @@ static_assert(sizeof(MegbRec) == 192, "MegbRec layout");
 // Instances of at least kBigInstance samples take their first descent steps
 // in kEarlyWG workgroups per chain, one launch per step.  The first
 // kEarlyFull steps scan every sample; the next one also gathers the
-// undominated samples (at most one in eight of the instance's, else none
-// are kept), which the later steps and the chain's rescans stream instead of
-// every sample.
+// undominated samples (as many as there are slots for, else none are kept and
+// a later step gathers again), which the later steps and the chain's rescans
+// stream instead of every sample.
 constexpr int64_t kBigInstance = 32768;
 constexpr int kEarlyFull = 16;
 constexpr int kEarlyWG = 64;
-constexpr int kShellBins = 256;
 
 // Slots of the undominated samples: one for every 2^shift samples, those of an
 // instance [off >> shift, (off >> shift) + (M >> shift)) in each chain's array
