@@ -95,10 +95,11 @@ __device__ __forceinline__ void exp_coeffs_bd(double z, double &B, double &Dc, d
   }
 }
 
-// Reciprocal and reciprocal square root for chains of float64 steps: in float64 the hardware approximation (2^-26 or better) and two Newton steps, a
-// few units in the last place and a third of the instructions of the
-// correctly rounded forms (arguments are depths, squared radii and pivots, far
-// from the ends of the range).
+// Reciprocal and reciprocal square root for chains of float64 steps: in float64
+// the hardware approximation (2^-26 or better) and two Newton steps, a few units
+// in the last place and a third of the instructions of the correctly rounded
+// forms (arguments are depths, squared radii and pivots, far from the ends of
+// the range).
 __device__ __forceinline__ float near_rcp(float x) { return drcp(x); }
 __device__ __forceinline__ float near_rsq(float x) { return drsqrt(x); }
 __device__ __forceinline__ double near_rcp(double x) {
